@@ -11,9 +11,8 @@
 //
 // The likelihood is the hot loop: l = sum_k lse_j(c_j - lambda_j (y_k -
 // mu_j)^2 / 2), c_j = log omega_j + eta_j / 2 - log(2 pi) / 2, i.e. n K
-// "mixture terms" per particle, each a subtract, a multiply, a fused
-// multiply-add, a max, an exponential and an add, plus one logarithm per
-// data point.  A workgroup holds 64 particles (one per lane) and W waves;
+// "mixture terms" per particle, each a multiply-add, a square, an
+// exponential and a multiply-add, plus one logarithm per 128 points.  A workgroup holds 64 particles (one per lane) and W waves;
 // wave w walks its own contiguous chunk of the data with wave-uniform
 // (scalar) loads of y, every lane keeps its particle's 3K constants and its
 // accumulators in registers, and the W partial sums are combined in wave
@@ -101,39 +100,81 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 // log p(y) = log sum_j exp(c_j - (lambda_j / 2) (y - mu_j)^2) with
 // c_j = log omega_j + eta_j / 2 - log(2 pi) / 2, summed over the data.
 //
-// The log-sum-exp of each point runs in base 2: a_j = c_j log2(e) - u_j^2
-// with u_j = g_j (y - mu_j) = g_j y - g_j mu_j, g_j = sqrt(lambda_j log2(e)
-// / 2), the maximum m of the a_j factored out, s = sum_j 2^(a_j - m) in
-// [1, K].  Instead of a logarithm per point, the sums s are multiplied
-// together and the product's logarithm is taken every FLUSH points (a
-// product of at most 64 factors <= 16 stays below 2^256), so
-// log p = ln 2 * sum m + sum log(prod).
+// Fast form (K > 1): the density itself, s = sum_j W_j 2^-(u_j^2) with
+// W_j = 2^SHIFT exp(c_j), u_j = g_j (y - mu_j) = g_j y - g_j mu_j, g_j =
+// sqrt(lambda_j log2(e) / 2): per term a multiply-add for u, the square,
+// fraction and integer part, ten multiply-adds for the power, its scaling
+// and the multiply-add into s.  Nothing is factored out of s (the scale
+// 2^SHIFT centres its range); the densities of two points are multiplied and
+// split into exponent (summed as an integer) and mantissa (multiplied; one
+// logarithm per FLUSH points).  A group of points with an s not above S_MIN
+// in some lane -- a point some forty standard deviations from every
+// component, or a NaN -- is left out of that lane's sums and taken after the
+// segment by redo(), which factors the largest term out of each point (its
+// code and registers stay out of the loop).
+// With W_j 2^-SHIFT in [W_MIN, W_MAX] and g_j mu_j finite (checked by setup()
+// for all lanes of the wave; weights and precisions within e^+-41 of 1) the powers that make
+// up an s above S_MIN are far from the denormal range, so its relative error
+// is that of its terms, and a product of two s stays inside the exponent
+// range.  Otherwise the whole chunk runs in the cold form.
 //
-// Gradient (GRAD): with responsibilities r_j = 2^(a_j - m) / s and
+// Bound: FP64 vector issue (every instruction of the loop is full rate).
+// 16 instructions per term and 3.5 per point; factoring the maximum out of
+// every point (a maximum, a subtraction and a separate constant more per
+// term) took 19 per term and 3 per point.  With the gradient at K = 6, 2^14
+// vectors, 10^4 points: 727 -> 673 us a call, 46 TFLOP/s.
+//
+// Gradient (GRAD): with responsibilities r_j = W_j 2^-(u_j^2) / s and
 // lambda_j d_j = 2 ln2 g_j u_j, lambda_j d_j^2 / 2 = ln2 u_j^2:
 //   d/d mu_j  = sum r_j lambda_j (y - mu_j)        = 2 ln2 g_j sum r_j u_j
 //   d/d eta_j = sum r_j (1/2 - lambda_j d_j^2 / 2) = sum r_j / 2 - ln2 sum r_j u_j^2
-// accumulated as sum r u (in gmu), sum r u^2 (in geta) and sum r (in gr)
-// and converted once in finish().
+// accumulated without the factor W_j as sum r u (in gmu), sum r u^2 (in
+// geta) and sum r (in gr) and converted once in finish().
 template <int K, bool GRAD>
 struct MixLik {
-    static constexpr int FLUSH = 64;
-    double g[K], gm[K], c[K];
+    // points per group: independent chains for the two waves a SIMD holds,
+    // as far as the registers allow (the gradient keeps every term of the
+    // group until its reciprocal is known)
+    static constexpr int GROUP = K > 8 || (GRAD && K > 6) ? 1 : (GRAD || K > 4 ? 2 : 4);
+    static constexpr int FLUSH = 128;  // points per logarithm; cold() keeps prod below 16^FLUSH
+    static constexpr double W_MIN = 0x1p-60, W_MAX = 0x1p60;
+    static constexpr int SHIFT = 418;
+    // s <= K W_MAX 2^SHIFT <= 2^482; s > 2^-500 has a power above 2^-982
+    static constexpr double S_MIN = 0x1p-500;
+    // stand-in for a density out of range, and its log2
+    static constexpr double OUT_S = 0x1p1000;
+    static constexpr int OUT = 1000;
+    double g[K], gm[K];
+    double c[K];  // W_j, or c_j log2(e) in the cold form (fast == false) and for K = 1
+    bool fast;
     double ll;  // after chunk(): sum of log p(y_k) over the chunk
     double m2, lsum, prod;
+    int ex;
+    bool bad;  // a group of the current segment waits for redo()
     double gmu[GRAD ? K : 1], geta[GRAD ? K : 1], gr[GRAD ? K : 1];
 
     __device__ __forceinline__ void setup(const double (&phi)[3 * K - 1 > 0 ? 3 * K - 1 : 1],
                                           const double (&logw)[K])
     {
+        bool ok = K > 1;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             g[j] = sqrt((0.5 * detail::kLog2e) * exp_d(phi[K + j]));
             gm[j] = g[j] * phi[j];
-            c[j] = detail::kLog2e * (logw[j] + 0.5 * phi[K + j] - kHalfLog2Pi);
+            c[j] = logw[j] + 0.5 * phi[K + j] - kHalfLog2Pi;
+            if (K > 1) {
+                const double w = exp_d(c[j]);
+                ok = ok && w >= W_MIN && w <= W_MAX && fabs(gm[j]) < 0x1p500;
+            }
         }
+        fast = __all(ok);
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            c[j] = fast ? ldexp(exp_d(c[j]), SHIFT) : detail::kLog2e * c[j];
         ll = m2 = lsum = 0.0;
         prod = 1.0;
+        ex = 0;
+        bad = false;
         if (GRAD) {
 #pragma unroll
             for (int j = 0; j < K; ++j)
@@ -141,25 +182,20 @@ struct MixLik {
         }
     }
 
-    // FAST: the terms' 2^x without the clamp that maps x = -inf to 0 (the
-    // same value for every finite x; see chunk())
-    template <bool FAST = false>
-    __device__ __forceinline__ void point(double y)
+    // One point with the maximum m of the a_j = c_j log2(e) - u_j^2 factored
+    // out, s = sum_j 2^(a_j - m) in [1, K]; a_j = -inf is a zero term.
+    template <bool FAST>
+    __device__ void cold(double y)
     {
         double e[K], u[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             u[j] = fma(g[j], y, -gm[j]);
-            e[j] = fma(-u[j], u[j], c[j]);
-        }
-        if constexpr (K == 1) {
-            m2 += e[0];
-            if (GRAD) {
-                gmu[0] += u[0];
-                geta[0] = fma(u[0], u[0], geta[0]);
-                gr[0] += 1.0;
-            }
-            return;
+            double cj = c[j];
+            asm volatile("" : "+v"(cj));  // one term at a time, nothing kept
+                                          // across points: few registers
+            e[j] = fma(-u[j], u[j], FAST ? fma(detail::kLog2e, log_d(cj), -SHIFT) : cj);
+            __builtin_amdgcn_sched_barrier(0);
         }
         double m = e[0];
 #pragma unroll
@@ -168,25 +204,123 @@ struct MixLik {
         double s = 0.0;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            e[j] = FAST ? exp2_nonpos_finite(e[j] - m) : exp2_nonpos(e[j] - m);
+            e[j] = exp2_nonpos(e[j] - m);
             s = j == 0 ? e[0] : s + e[j];
+            __builtin_amdgcn_sched_barrier(0);
         }
         m2 += m;
         prod *= s;
         if (GRAD) {
-            // 1/s for s in [1, K]: hardware estimate and two Newton steps
-            double inv = __builtin_amdgcn_rcp(s);
-            inv = fma(inv, fma(-s, inv, 1.0), inv);
-            inv = fma(inv, fma(-s, inv, 1.0), inv);
+            // 1/s for s in [1, K]
+            const double inv = recip(s);
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                const double r = e[j] * inv;
+                double cj = c[j];
+                asm volatile("" : "+v"(cj));
+                const double r = FAST ? e[j] * inv / cj : e[j] * inv;
                 const double ru = r * u[j];
                 gmu[j] += ru;
                 geta[j] = fma(ru, u[j], geta[j]);
                 gr[j] += r;
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
+    }
+
+    // hardware estimate and two Newton steps (s and 1/s normal)
+    static __device__ __forceinline__ double recip(double s)
+    {
+        double inv = __builtin_amdgcn_rcp(s);
+        inv = fma(inv, fma(-s, inv, 1.0), inv);
+        return fma(inv, fma(-s, inv, 1.0), inv);
+    }
+
+    // The terms and densities of N points (GROUP, or 1 for the remainder of a
+    // chunk) in the fast form; whether every density is in range (false for
+    // NaN).  No step of it can be contracted differently from one use to the
+    // next, so the answer is the same in group() and redo().
+    template <int N>
+    __device__ __forceinline__ bool densities(const double (&y)[N], double (&u)[N][K],
+                                              double (&e)[N][K], double (&s)[N])
+    {
+        bool good = true;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                u[i][j] = fma(g[j], y[i], -gm[j]);
+                e[i][j] = exp2_neg(u[i][j] * u[i][j]);
+                s[i] = j == 0 ? c[0] * e[i][0] : fma(c[j], e[i][j], s[i]);
+            }
+            good = good & (s[i] > S_MIN);
+        }
+        return good;
+    }
+
+    template <int N>
+    __device__ __forceinline__ void group(const double (&y)[N])
+    {
+        double u[N][K], e[N][K], s[N];
+        const bool good = densities<N>(y, u, e, s);
+        bad = bad | !good;
+#pragma unroll
+        for (int i = 0; i < N; i += 2) {
+            const bool two = i + 1 < N;
+            // no branch, so that the loads of the next group stay ahead: a
+            // group out of range counts as a density OUT_S (taken back by
+            // redo()), which leaves nothing of it in the gradient's sums
+            const double p = two ? s[i] * s[two ? i + 1 : i] : s[i];
+            const double q = good ? p : OUT_S;
+            prod *= __builtin_amdgcn_frexp_mant(q);
+            ex += __builtin_amdgcn_frexp_exp(q) - (two ? 2 * SHIFT : SHIFT);
+            if (GRAD) {
+                const double iq = recip(q);
+#pragma unroll
+                for (int h = i; h < i + 2 && h < N; ++h) {
+                    // 1 / s_h = (the other s) / q
+                    const double inv = two ? iq * s[h == i ? i + (two ? 1 : 0) : i] : iq;
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        const double r = e[h][j] * inv;
+                        const double ru = r * u[h][j];
+                        gmu[j] += ru;
+                        geta[j] = fma(ru, u[h][j], geta[j]);
+                        gr[j] += r;
+                    }
+                }
+            }
+        }
+    }
+
+    // The groups of N points of a segment that group() left out of a lane's
+    // sums, each point with its largest term factored out.
+    template <int N>
+    __device__ __forceinline__ void redo(const double *__restrict__ y, int64_t k, int64_t kend)
+    {
+        if (bad) {
+#pragma nounroll
+            for (; k < kend; k += N) {
+                double a[N], u[N][K], e[N][K], s[N];
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+                    a[i] = y[k + i];
+                if (!densities<N>(a, u, e, s)) {
+                    m2 -= ((N + 1) / 2) * OUT - N * SHIFT;
+#pragma nounroll
+                    for (int i = 0; i < N; ++i)
+                        cold<true>(y[k + i]);
+                }
+            }
+        }
+        bad = false;
+    }
+
+    __device__ __forceinline__ void flush()
+    {
+        lsum += log_pos_d(prod);
+        m2 += (double)ex;
+        prod = 1.0;
+        ex = 0;
     }
 
     __device__ __forceinline__ void finish()
@@ -195,84 +329,72 @@ struct MixLik {
         if (GRAD) {
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                gmu[j] *= (2.0 * detail::kLn2) * g[j];
-                geta[j] = fma(-detail::kLn2, geta[j], 0.5 * gr[j]);
+                const double w = fast ? c[j] : 1.0;
+                gmu[j] *= (2.0 * detail::kLn2) * g[j] * w;
+                geta[j] = w * fma(-detail::kLn2, geta[j], 0.5 * gr[j]);
+                gr[j] *= w;
             }
         }
     }
 
-    // the running sums of a chunk back to their start (the constants of
-    // setup() stay)
-    __device__ __forceinline__ void reset()
-    {
-        ll = m2 = lsum = 0.0;
-        prod = 1.0;
-        if (GRAD) {
-#pragma unroll
-            for (int j = 0; j < K; ++j)
-                gmu[j] = geta[j] = gr[j] = 0.0;
-        }
-    }
-
-    // the points [k0, k1) in FLUSH-point segments with wave-uniform loads;
-    // in the two-point loop the next pair is loaded one iteration ahead
-    template <bool FAST>
-    __device__ __forceinline__ void run(const double *__restrict__ y, int64_t k0, int64_t k1)
-    {
-        int64_t k = k0;
-        while (k < k1) {
-            const int64_t kend = min(k + FLUSH, k1);
-            if (K <= 8) {  // two points per iteration while registers allow
-                if (k + 2 <= kend) {
-                    double y0 = y[k], y1 = y[k + 1];
-                    if constexpr (FAST && !GRAD) {
-                        // unrolled once more: the prefetched pair alternates
-                        // between two register pairs instead of being moved
-#pragma unroll 2
-                        for (; k + 4 <= kend; k += 2) {
-                            const double n0 = y[k + 2], n1 = y[k + 3];
-                            point<FAST>(y0);
-                            point<FAST>(y1);
-                            y0 = n0;
-                            y1 = n1;
-                        }
-                    } else {
-                        for (; k + 4 <= kend; k += 2) {
-                            const double n0 = y[k + 2], n1 = y[k + 3];
-                            point<FAST>(y0);
-                            point<FAST>(y1);
-                            y0 = n0;
-                            y1 = n1;
-                        }
-                    }
-                    point<FAST>(y0);
-                    point<FAST>(y1);
-                    k += 2;
-                }
-            }
-            for (; k < kend; ++k)
-                point<FAST>(y[k]);
-            lsum += log_d(prod);
-            prod = 1.0;
-        }
-        finish();
-    }
-
-    // accumulate a contiguous chunk of the data: first with the terms' 2^x
-    // unclamped; a non-finite term makes the log-likelihood NaN, and then the
-    // chunk is summed again with the clamp, so the results are those of the
-    // clamped form for every input
+    // accumulate the points [k0, k1) (uniform across the wave): wave-uniform
+    // loads, the next group fetched one group ahead
     __device__ __forceinline__ void chunk(const double *__restrict__ y, int64_t k0, int64_t k1)
     {
-        if constexpr (K > 1) {
-            run<true>(y, k0, k1);
-            if (!(ll == ll)) {
-                reset();
-                run<false>(y, k0, k1);
+        int64_t k = k0;
+        if constexpr (K == 1) {
+            for (; k < k1; ++k) {
+                const double u = fma(g[0], y[k], -gm[0]);
+                m2 += fma(-u, u, c[0]);
+                if (GRAD) {
+                    gmu[0] += u;
+                    geta[0] = fma(u, u, geta[0]);
+                    gr[0] += 1.0;
+                }
+            }
+        } else if (fast) {
+            while (k + GROUP <= k1) {
+                const int64_t kseg = k;
+                const int groups = (int)min((int64_t)FLUSH, k1 - k) / GROUP;
+                const double *__restrict__ p = y + k;
+                double a[GROUP];
+#pragma unroll
+                for (int i = 0; i < GROUP; ++i)
+                    a[i] = p[i];
+                for (int r = 1; r < groups; ++r) {
+                    double b[GROUP];
+                    p += GROUP;
+#pragma unroll
+                    for (int i = 0; i < GROUP; ++i)
+                        b[i] = p[i];
+                    group<GROUP>(a);
+#pragma unroll
+                    for (int i = 0; i < GROUP; ++i)
+                        a[i] = b[i];
+                }
+                group<GROUP>(a);
+                k += (int64_t)groups * GROUP;
+                redo<GROUP>(y, kseg, k);
+                flush();
+            }
+            if (GROUP > 1 && k < k1) {
+                const int64_t kseg = k;
+                for (; k < k1; ++k) {
+                    const double a[1] = {y[k]};
+                    group<1>(a);
+                }
+                redo<1>(y, kseg, k1);
+                flush();
             }
         } else {
-            run<false>(y, k0, k1);
+            while (k < k1) {
+                const int64_t kend = min(k + FLUSH, k1);
+                for (; k < kend; ++k)
+                    cold<false>(y[k]);
+                flush();
+            }
         }
+        finish();
     }
 
     static constexpr int NACC = GRAD ? 1 + 3 * K : 1;
@@ -696,8 +818,11 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_step_kernel(
 // Log-likelihood (and gradient) for separate parameter arrays (the adjoint
 // entry point).
 // ---------------------------------------------------------------------------
+// Four waves per SIMD (128 registers) where that costs no spill: K = 4 with
+// the gradient would take 141, and 2^16 vectors of 1000 points 249 us against
+// 224).
 template <int K, bool GRAD>
-__global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_loglik_kernel(
+__global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 ? 4 : 2) void gmm_loglik_kernel(
     const double *__restrict__ mu, const double *__restrict__ eta, const double *__restrict__ z,
     int64_t n, const double *__restrict__ y, int64_t nd, int W, double *__restrict__ ll,
     double *__restrict__ grad)

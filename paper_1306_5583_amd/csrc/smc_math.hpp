@@ -9,11 +9,11 @@
 //  exp_d(x):   x = k ln2 + r with k = rint(x / ln2) and |r| <= ln2/2 (Cody &
 //              Waite reduction with ln2 in two parts), e^r by its Taylor series
 //              to degree 13 (truncation below 5e-18), then scaled by 2^k.
-//  exp2_nonpos(x): 2^x for x <= 0 (the terms of a log-sum-exp taken in base
-//              2): x = k + r with k = rint(x), |r| <= 1/2 exact, 2^r by the
-//              degree-10 minimax polynomial on [-1/2, 1/2] (Remez exchange,
-//              2.8e-16 relative error; coefficients from gen_exp2_poly.py),
-//              scaled by 2^k.
+//  exp2_neg(a): 2^-a for a >= 0 (the terms of a log-sum-exp taken in base
+//              2): a = n + f with n = floor(a) and f in [0, 1) exact, 2^-f by
+//              the degree-10 minimax polynomial with constant term 1 (Remez
+//              exchange, 2.3e-16 relative error; coefficients from
+//              gen_exp2_poly.py), scaled by 2^-n.
 //  sincospi_d: sin(pi x), cos(pi x) by exact reduction to r = x - n/2,
 //              |r| <= 1/4, and the Taylor series of sin(pi r), cos(pi r)
 //              to r^17 / r^16 (truncation below 1e-17 for |pi r| <= pi/4),
@@ -50,13 +50,13 @@ constexpr double kExpC[14] = {exp_c(0), exp_c(1), exp_c(2),  exp_c(3),  exp_c(4)
                               exp_c(10), exp_c(11), exp_c(12), exp_c(13)};
 constexpr double kLog2e = 1.4426950408889634073599246810019;
 constexpr double kLn2 = 0.69314718055994530941723212145818;
-// 2^r ~ sum_j kExp2C[j] r^j on [-1/2, 1/2]: degree-10 minimax in relative
-// error (Remez exchange, gen_exp2_poly.py), 2.8e-16 after rounding
+// 2^-f ~ sum_j kExp2C[j] f^j on [0, 1], kExp2C[0] = 1: degree-10 minimax in
+// relative error (Remez exchange, gen_exp2_poly.py), 2.3e-16 after rounding
 constexpr double kExp2C[11] = {
-    0x1.0000000000000p+0,  0x1.62e42fefa3a17p-1,  0x1.ebfbdff82c3b9p-3,
-    0x1.c6b08d703d48ap-5,  0x1.3b2ab6fbde0f7p-7,  0x1.5d87fe9cc5d6fp-10,
-    0x1.4309126056718p-13, 0x1.ffcb55e82f22cp-17, 0x1.62c157ee59177p-20,
-    0x1.b6740fc28f781p-24, 0x1.e3991e644e6abp-28};
+    0x1.0000000000000p+0,   -0x1.62e42fefa38cap-1,  0x1.ebfbdff81f083p-3,
+    -0x1.c6b08d6ce972dp-5,  0x1.3b2ab68e51132p-7,   -0x1.5d87ee7d3cf77p-10,
+    0x1.43079ee0aac33p-13,  -0x1.ffa0707bb4816p-17, 0x1.611aa9e1420f2p-20,
+    -0x1.a11af6e0d35bap-24, 0x1.5696f50dd8aa2p-28};
 constexpr double kSinC[10] = {sin_c(0), sin_c(1), sin_c(2), sin_c(3), sin_c(4),
                               sin_c(5), sin_c(6), sin_c(7), sin_c(8), sin_c(9)};
 constexpr double kCosC[10] = {cos_c(0), cos_c(1), cos_c(2), cos_c(3), cos_c(4),
@@ -164,35 +164,33 @@ __host__ __device__ inline double exp_d(double x)
     return v;
 }
 
+// 2^-a for a >= 0.  On the device the fraction and the (saturating) integer
+// conversion with its sign are one instruction each, so a term costs the ten
+// multiply-adds and three more; a beyond the exponent range (and +inf, whose
+// fraction the hardware takes as 0 or NaN) gives 0, a denormal result or NaN.
+// 2^-0 = 1 exactly.
+__host__ __device__ inline double exp2_neg(double a)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double f = __builtin_amdgcn_fract(a);
+    int n;
+    asm("v_cvt_i32_f64_e64 %0, -%1" : "=v"(n) : "v"(a));
+#else
+    const double k = floor(a);
+    const double f = a - k;
+    const int n = -(int)k;
+#endif
+    double p = detail::kExp2C[10];
+#pragma unroll
+    for (int j = 9; j >= 0; --j)
+        p = fma(p, f, detail::kExp2C[j]);
+    return ldexp(p, n);
+}
+
 // 2^x for x <= 0: x below -1100 (and -inf) gives 0 through gradual
 // underflow; so does NaN (the caller guarantees x is not NaN).  2^0 = 1
 // exactly.
-__host__ __device__ inline double exp2_nonpos(double x)
-{
-    const double xc = fmax(x, -1100.0);
-    const double k = rint(xc);
-    const double r = xc - k;  // exact
-    double p = detail::kExp2C[10];
-#pragma unroll
-    for (int j = 9; j >= 0; --j)
-        p = fma(p, r, detail::kExp2C[j]);
-    return ldexp(p, (int)k);
-}
-
-// 2^x for finite x <= 0 without the lower clamp (device code: the
-// exponent conversion saturates): the same value as exp2_nonpos for every
-// finite x, one instruction less; -inf or NaN gives NaN, which a caller
-// detects and redoes with exp2_nonpos.
-__device__ inline double exp2_nonpos_finite(double x)
-{
-    const double k = rint(x);
-    const double r = x - k;  // exact
-    double p = detail::kExp2C[10];
-#pragma unroll
-    for (int j = 9; j >= 0; --j)
-        p = fma(p, r, detail::kExp2C[j]);
-    return ldexp(p, (int)k);
-}
+__host__ __device__ inline double exp2_nonpos(double x) { return exp2_neg(fmin(-x, 1100.0)); }
 
 // Square root of a >= 0 that is 0 or at least 2^-767 (device code): the
 // hardware reciprocal square-root estimate refined by one Goldschmidt step

@@ -325,6 +325,47 @@ def test_loglik_far_components(lib, orc, K, grad):
         assert_close_l1(ll[i], v, abs(v) + 50, 1e-12, "ll")
 
 
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("K,nd", [(2, 1), (2, 129), (3, 3), (4, 127), (4, 1001), (6, 258),
+                                  (7, 130), (9, 131)])
+def test_loglik_out_of_range_points(lib, orc, K, nd, grad):
+    # points out of range of the product form (hundreds of standard
+    # deviations from every component) in some lanes only, at the edges of its
+    # groups and segments; and whole waves whose weights are out of range
+    pkg, L = lib
+    n = 192
+    rng = np.random.default_rng(1000 * K + nd)
+    y = rng.normal(0.0, 2.0, nd)
+    y[rng.random(nd) < 0.1] = 300.0
+    y[[0, nd - 1]] = 40.0, -250.0
+    mu = rng.normal(0, 3, (K, n))
+    eta = rng.normal(0.4, 0.8, (K, n))
+    z = rng.normal(0, 0.5, (K - 1, n))
+    near = np.arange(n) % 5 == 0           # a wide component: every point in range
+    eta[0, near] = -12.0
+    z[0, 64:128:7] = 70.0                  # second wave: weights beyond e^+-41
+    z[K - 2, 65:128:9] = -300.0
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+    mu_d, eta_d, z_d, y_d = dev(mu), dev(eta), dev(z), dev(y)
+    ll = torch.zeros(n, dtype=torch.float64, device="cuda")
+    g = torch.zeros((3 * K - 1, n), dtype=torch.float64, device="cuda")
+    L.smc_gmm_loglik_grad(mu_d.data_ptr(), eta_d.data_ptr(), z_d.data_ptr(), n, K,
+                          y_d.data_ptr(), nd, ll.data_ptr(), g.data_ptr() if grad else 0,
+                          torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    ll, g = ll.cpu().numpy(), g.cpu().numpy()
+    for i in range(n):
+        phi = np.concatenate([mu[:, i], eta[:, i], z[:, i]])
+        v, gr = orc.gmm_loglik(phi, K, y, grad=True)
+        assert_close_l1(ll[i], v, abs(v) + 50, 1e-12, "ll %d" % i)
+        if grad:
+            # no summand of any derivative exceeds this at any point
+            d = np.abs(y[None, :] - mu[:, i, None])
+            lam = np.exp(eta[:, i, None])
+            mass = 2.0 * nd + (lam * d * (1.0 + d)).max(0).sum()
+            assert_close_l1(g[:, i], gr, mass, 1e-12, "grad %d" % i)
+
+
 def test_autograd_function_gradcheck(lib, orc):
     pkg, L = lib
     K, n, nd = 3, 8, 40
