@@ -100,23 +100,22 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 // log p(y) = log sum_j exp(c_j - (lambda_j / 2) (y - mu_j)^2) with
 // c_j = log omega_j + eta_j / 2 - log(2 pi) / 2, summed over the data.
 //
-// Fast form (K > 1): the density itself, s = sum_j W_j 2^-(u_j^2) with
-// W_j = 2^SHIFT exp(c_j), u_j = g_j (y - mu_j) = g_j y - g_j mu_j, g_j =
-// sqrt(lambda_j log2(e) / 2): per term a multiply-add for u, the square,
-// fraction and integer part, ten multiply-adds for the power, its scaling
-// and the multiply-add into s.  Nothing is factored out of s (the scale
-// 2^SHIFT centres its range); the densities of two points are multiplied and
-// split into exponent (summed as an integer) and mantissa (multiplied; one
-// logarithm per FLUSH points).  A group of points with an s not above S_MIN
-// in some lane -- a point some forty standard deviations from every
-// component, or a NaN -- is left out of that lane's sums and taken after the
-// segment by redo(), which factors the largest term out of each point (its
-// code and registers stay out of the loop).
-// With W_j 2^-SHIFT in [W_MIN, W_MAX] and g_j mu_j finite (checked by setup()
-// for all lanes of the wave; weights and precisions within e^+-41 of 1) the powers that make
-// up an s above S_MIN are far from the denormal range, so its relative error
-// is that of its terms, and a product of two s stays inside the exponent
-// range.  Otherwise the whole chunk runs in the cold form.
+// Fast form (K > 1): the density itself, up to a power of two of the
+// parameter vector: s = sum_j 2^(SHIFT - a_j), a_j = u_j^2 + d_j with u_j =
+// g_j (y - mu_j) = g_j y - g_j mu_j, g_j = sqrt(lambda_j log2(e) / 2), d_j =
+// O - c_j log2(e) >= 0 and O the integer above the largest c_j log2(e).  Per
+// term two multiply-adds, fraction and integer part, ten multiply-adds for
+// the power, its scaling and the addition to s.  Nothing is factored out of
+// s (SHIFT centres its range); the densities of two points are multiplied
+// and split into exponent (summed as an integer) and mantissa (multiplied;
+// one logarithm per FLUSH points).  A group of points with an s not above
+// S_MIN in some lane -- a point some thirty-five standard deviations from
+// every component, or a NaN -- is left out of that lane's sums; at the end of
+// its segment to_safe() takes it again and moves the wave to the safe form,
+// which factors the largest term out of each point, for the rest of the chunk
+// (a vector far from the data is out of range at most points; the first
+// segment is one group, so such a wave changes over at once).  A wave with a
+// parameter that is not finite takes the whole chunk in the safe form.
 //
 // Bound: FP64 vector issue (every instruction of the loop is full rate).
 // 16 instructions per term and 3.5 per point; factoring the maximum out of
@@ -124,53 +123,68 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 // term) took 19 per term and 3 per point.  With the gradient at K = 6, 2^14
 // vectors, 10^4 points: 727 -> 673 us a call, 46 TFLOP/s.
 //
-// Gradient (GRAD): with responsibilities r_j = W_j 2^-(u_j^2) / s and
+// Gradient (GRAD): with responsibilities r_j = 2^(SHIFT - a_j) / s and
 // lambda_j d_j = 2 ln2 g_j u_j, lambda_j d_j^2 / 2 = ln2 u_j^2:
 //   d/d mu_j  = sum r_j lambda_j (y - mu_j)        = 2 ln2 g_j sum r_j u_j
 //   d/d eta_j = sum r_j (1/2 - lambda_j d_j^2 / 2) = sum r_j / 2 - ln2 sum r_j u_j^2
-// accumulated without the factor W_j as sum r u (in gmu), sum r u^2 (in
-// geta) and sum r (in gr) and converted once in finish().
+// accumulated as sum r u (in gmu), sum r u^2 (in geta) and sum r (in gr)
+// and converted once in finish().
 template <int K, bool GRAD>
 struct MixLik {
     // points per group: independent chains for the two waves a SIMD holds,
     // as far as the registers allow (the gradient keeps every term of the
     // group until its reciprocal is known)
     static constexpr int GROUP = K > 8 || (GRAD && K > 6) ? 1 : (GRAD || K > 4 ? 2 : 4);
-    static constexpr int FLUSH = 128;  // points per logarithm; cold() keeps prod below 16^FLUSH
-    static constexpr double W_MIN = 0x1p-60, W_MAX = 0x1p60;
-    static constexpr int SHIFT = 418;
-    // s <= K W_MAX 2^SHIFT <= 2^482; s > 2^-500 has a power above 2^-982
+    static constexpr int SEG = 32;     // points per segment after the first
+    // the gradient of K > 3 goes back to the chunk's start instead of
+    // to_safe(), whose registers would spill (four or more components all out
+    // of range are rare)
+    static constexpr bool RESTART = GRAD && K > 3;
+    static constexpr int FLUSH = 128;  // points per logarithm (safe form: factors <= 16)
+    // s <= K 2^SHIFT <= 2^494; s > 2^-500 has a power above 2^-504, so every
+    // s that counts, the product of two and its reciprocal are normal
+    static constexpr int SHIFT = 490;
     static constexpr double S_MIN = 0x1p-500;
     // stand-in for a density out of range, and its log2
     static constexpr double OUT_S = 0x1p1000;
     static constexpr int OUT = 1000;
     double g[K], gm[K];
-    double c[K];  // W_j, or c_j log2(e) in the cold form (fast == false) and for K = 1
-    bool fast;
+    double c[K];  // d_j, or c_j log2(e) in the safe form (fast == false) and for K = 1
+    int off;      // O
+    bool fast;    // uniform across the wave
     double ll;  // after chunk(): sum of log p(y_k) over the chunk
     double m2, lsum, prod;
     int ex;
-    bool bad;  // a group of the current segment waits for redo()
+    bool bad;  // a group of the current segment waits for to_safe()
     double gmu[GRAD ? K : 1], geta[GRAD ? K : 1], gr[GRAD ? K : 1];
 
     __device__ __forceinline__ void setup(const double (&phi)[3 * K - 1 > 0 ? 3 * K - 1 : 1],
                                           const double (&logw)[K])
     {
         bool ok = K > 1;
+        double cmax = -INFINITY;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             g[j] = sqrt((0.5 * detail::kLog2e) * exp_d(phi[K + j]));
             gm[j] = g[j] * phi[j];
-            c[j] = logw[j] + 0.5 * phi[K + j] - kHalfLog2Pi;
-            if (K > 1) {
-                const double w = exp_d(c[j]);
-                ok = ok && w >= W_MIN && w <= W_MAX && fabs(gm[j]) < 0x1p500;
-            }
+            c[j] = detail::kLog2e * (logw[j] + 0.5 * phi[K + j] - kHalfLog2Pi);
+            ok = ok && fabs(c[j]) < 0x1p20 && fabs(gm[j]) < 0x1p500;
+            cmax = fmax(cmax, c[j]);
         }
         fast = __all(ok);
+        off = 0;
+        if (fast) {
+            const double o = ceil(cmax);
+            off = (int)o;
 #pragma unroll
-        for (int j = 0; j < K; ++j)
-            c[j] = fast ? ldexp(exp_d(c[j]), SHIFT) : detail::kLog2e * c[j];
+            for (int j = 0; j < K; ++j)
+                c[j] = o - c[j];
+        }
+        reset();
+    }
+
+    __device__ __forceinline__ void reset()
+    {
         ll = m2 = lsum = 0.0;
         prod = 1.0;
         ex = 0;
@@ -182,20 +196,16 @@ struct MixLik {
         }
     }
 
-    // One point with the maximum m of the a_j = c_j log2(e) - u_j^2 factored
-    // out, s = sum_j 2^(a_j - m) in [1, K]; a_j = -inf is a zero term.
-    template <bool FAST>
-    __device__ void cold(double y)
+    // One point in the safe form: the maximum m of the a_j = cl_j - u_j^2
+    // (cl_j = c_j log2(e)) factored out, s = sum_j 2^(a_j - m) in [1, K];
+    // a_j = -inf is a zero term.
+    __device__ __forceinline__ void point(double y, const double (&cl)[K])
     {
         double e[K], u[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             u[j] = fma(g[j], y, -gm[j]);
-            double cj = c[j];
-            asm volatile("" : "+v"(cj));  // one term at a time, nothing kept
-                                          // across points: few registers
-            e[j] = fma(-u[j], u[j], FAST ? fma(detail::kLog2e, log_d(cj), -SHIFT) : cj);
-            __builtin_amdgcn_sched_barrier(0);
+            e[j] = fma(-u[j], u[j], cl[j]);
         }
         double m = e[0];
 #pragma unroll
@@ -206,23 +216,18 @@ struct MixLik {
         for (int j = 0; j < K; ++j) {
             e[j] = exp2_nonpos(e[j] - m);
             s = j == 0 ? e[0] : s + e[j];
-            __builtin_amdgcn_sched_barrier(0);
         }
         m2 += m;
         prod *= s;
         if (GRAD) {
-            // 1/s for s in [1, K]
             const double inv = recip(s);
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                double cj = c[j];
-                asm volatile("" : "+v"(cj));
-                const double r = FAST ? e[j] * inv / cj : e[j] * inv;
+                const double r = e[j] * inv;
                 const double ru = r * u[j];
                 gmu[j] += ru;
                 geta[j] = fma(ru, u[j], geta[j]);
                 gr[j] += r;
-                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
@@ -238,8 +243,9 @@ struct MixLik {
     // The terms and densities of N points (GROUP, or 1 for the remainder of a
     // chunk) in the fast form; whether every density is in range (false for
     // NaN).  No step of it can be contracted differently from one use to the
-    // next, so the answer is the same in group() and redo().
-    template <int N>
+    // next, so the answer is the same in group() and to_safe(), which takes
+    // the terms one at a time (LEAN: few registers).
+    template <int N, bool LEAN>
     __device__ __forceinline__ bool densities(const double (&y)[N], double (&u)[N][K],
                                               double (&e)[N][K], double (&s)[N])
     {
@@ -249,8 +255,10 @@ struct MixLik {
 #pragma unroll
             for (int j = 0; j < K; ++j) {
                 u[i][j] = fma(g[j], y[i], -gm[j]);
-                e[i][j] = exp2_neg(u[i][j] * u[i][j]);
-                s[i] = j == 0 ? c[0] * e[i][0] : fma(c[j], e[i][j], s[i]);
+                e[i][j] = exp2_neg<SHIFT>(fma(u[i][j], u[i][j], c[j]));
+                s[i] = j == 0 ? e[i][0] : s[i] + e[i][j];
+                if (LEAN)
+                    __builtin_amdgcn_sched_barrier(0);
             }
             good = good & (s[i] > S_MIN);
         }
@@ -261,19 +269,20 @@ struct MixLik {
     __device__ __forceinline__ void group(const double (&y)[N])
     {
         double u[N][K], e[N][K], s[N];
-        const bool good = densities<N>(y, u, e, s);
+        const bool good = densities<N, false>(y, u, e, s);
         bad = bad | !good;
 #pragma unroll
         for (int i = 0; i < N; i += 2) {
             const bool two = i + 1 < N;
             // no branch, so that the loads of the next group stay ahead: a
             // group out of range counts as a density OUT_S (taken back by
-            // redo()), which leaves nothing of it in the gradient's sums
+            // to_safe()), which leaves nothing of it in the gradient's sums
             const double p = two ? s[i] * s[two ? i + 1 : i] : s[i];
             const double q = good ? p : OUT_S;
             prod *= __builtin_amdgcn_frexp_mant(q);
-            ex += __builtin_amdgcn_frexp_exp(q) - (two ? 2 * SHIFT : SHIFT);
+            ex += __builtin_amdgcn_frexp_exp(q) + (two ? 2 : 1) * (off - SHIFT);
             if (GRAD) {
+                static_assert(!GRAD || GROUP <= 2, "OUT_S covers a pair");
                 const double iq = recip(q);
 #pragma unroll
                 for (int h = i; h < i + 2 && h < N; ++h) {
@@ -292,29 +301,6 @@ struct MixLik {
         }
     }
 
-    // The groups of N points of a segment that group() left out of a lane's
-    // sums, each point with its largest term factored out.
-    template <int N>
-    __device__ __forceinline__ void redo(const double *__restrict__ y, int64_t k, int64_t kend)
-    {
-        if (bad) {
-#pragma nounroll
-            for (; k < kend; k += N) {
-                double a[N], u[N][K], e[N][K], s[N];
-#pragma unroll
-                for (int i = 0; i < N; ++i)
-                    a[i] = y[k + i];
-                if (!densities<N>(a, u, e, s)) {
-                    m2 -= ((N + 1) / 2) * OUT - N * SHIFT;
-#pragma nounroll
-                    for (int i = 0; i < N; ++i)
-                        cold<true>(y[k + i]);
-                }
-            }
-        }
-        bad = false;
-    }
-
     __device__ __forceinline__ void flush()
     {
         lsum += log_pos_d(prod);
@@ -323,16 +309,52 @@ struct MixLik {
         ex = 0;
     }
 
+    // The constants of the safe form.
+    __device__ __forceinline__ void safe_constants()
+    {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            c[j] = (double)off - c[j];
+        fast = false;
+    }
+
+    // From the fast to the safe form, with the groups of N points of the
+    // segment [k, kend) that group() left out of a lane's sums.
+    template <int N>
+    __device__ __forceinline__ void to_safe(const double *__restrict__ y, int64_t k, int64_t kend)
+    {
+        flush();
+        if (bad) {
+            double cl[K];
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                cl[j] = (double)off - c[j];
+#pragma nounroll
+            for (; k < kend; k += N) {
+                double a[N], u[N][K], e[N][K], s[N];
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+                    a[i] = y[k + i];
+                if (!densities<N, true>(a, u, e, s)) {
+                    m2 -= ((N + 1) / 2) * OUT + N * (off - SHIFT);
+#pragma nounroll
+                    for (int i = 0; i < N; ++i)
+                        point(y[k + i], cl);
+                }
+            }
+        }
+        flush();
+        safe_constants();
+    }
+
     __device__ __forceinline__ void finish()
     {
         ll = fma(detail::kLn2, m2, lsum);
         if (GRAD) {
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                const double w = fast ? c[j] : 1.0;
-                gmu[j] *= (2.0 * detail::kLn2) * g[j] * w;
-                geta[j] = w * fma(-detail::kLn2, geta[j], 0.5 * gr[j]);
-                gr[j] *= w;
+                gmu[j] *= (2.0 * detail::kLn2) * g[j];
+                geta[j] = fma(-detail::kLn2, geta[j], 0.5 * gr[j]);
             }
         }
     }
@@ -352,10 +374,11 @@ struct MixLik {
                     gr[0] += 1.0;
                 }
             }
-        } else if (fast) {
-            while (k + GROUP <= k1) {
+        } else {
+            int len = GROUP, since = 0;
+            while (fast && k + GROUP <= k1) {
                 const int64_t kseg = k;
-                const int groups = (int)min((int64_t)FLUSH, k1 - k) / GROUP;
+                const int groups = (int)min((int64_t)len, k1 - k) / GROUP;
                 const double *__restrict__ p = y + k;
                 double a[GROUP];
 #pragma unroll
@@ -373,24 +396,56 @@ struct MixLik {
                         a[i] = b[i];
                 }
                 group<GROUP>(a);
-                k += (int64_t)groups * GROUP;
-                redo<GROUP>(y, kseg, k);
-                flush();
+                k += groups * GROUP;
+                since += groups * GROUP;
+                len = SEG;
+                if (__any(bad)) {
+                    if constexpr (RESTART) {
+                        reset();
+                        safe_constants();
+                        k = k0;
+                    } else {
+                        to_safe<GROUP>(y, kseg, k);
+                    }
+                } else if (since + SEG > FLUSH) {
+                    flush();
+                    since = 0;
+                }
             }
-            if (GROUP > 1 && k < k1) {
+            if (GROUP > 1 && fast && k < k1) {
                 const int64_t kseg = k;
                 for (; k < k1; ++k) {
                     const double a[1] = {y[k]};
                     group<1>(a);
                 }
-                redo<1>(y, kseg, k1);
-                flush();
+                if (__any(bad)) {
+                    if constexpr (RESTART) {
+                        reset();
+                        safe_constants();
+                        k = k0;
+                    } else {
+                        to_safe<1>(y, kseg, k1);
+                    }
+                }
             }
-        } else {
-            while (k < k1) {
-                const int64_t kend = min(k + FLUSH, k1);
+            flush();
+            while (k < k1) {  // the safe form
+                const int64_t kend = min(k + FLUSH / 2, k1);
+                if (K <= 8 && k + 2 <= kend) {  // two points at a time
+                    double y0 = y[k], y1 = y[k + 1];
+                    for (; k + 4 <= kend; k += 2) {
+                        const double n0 = y[k + 2], n1 = y[k + 3];
+                        point(y0, c);
+                        point(y1, c);
+                        y0 = n0;
+                        y1 = n1;
+                    }
+                    point(y0, c);
+                    point(y1, c);
+                    k += 2;
+                }
                 for (; k < kend; ++k)
-                    cold<false>(y[k]);
+                    point(y[k], c);
                 flush();
             }
         }
@@ -792,8 +847,10 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
 // and leaves the tile's state in LDS; each later block reads the state the
 // previous block's wave 0 left there (visible to the workgroup after the
 // barrier), and the last one writes the whole state to `dst`.
+// A random walk with K <= 4 fits two workgroups of eight waves on a compute
+// unit (128 registers).
 template <int K, bool MALA>
-__global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_step_kernel(
+__global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : 2) void gmm_step_kernel(
     Prob P, const double *__restrict__ src, double *__restrict__ dst, int full, int W, uint32_t t,
     int sweeps, double alpha, double s0, double s1, double s2, int32_t step)
 {
