@@ -23,7 +23,7 @@ struct KGroup {
     bool mala = false;
     int2 *map64 = nullptr;
     int64_t tiles64 = 0;
-    int W = 1;
+    GmmSplit split{1, 0};  // of the initialisation
     int64_t sum_n = 0;
     int64_t max_nd = 0;
 };
@@ -394,7 +394,7 @@ smc_status smc_batch_create(const smc_batch_problem *probs, int32_t nprob, void 
         KGroup g = grp[pl.keys[k]];
         g.map64 = reinterpret_cast<int2 *>(b->table + pl.map64[k]);
         g.tiles64 = pl.tiles64[k];
-        g.W = gmm_waves(g.sum_n, g.max_nd);
+        g.split = gmm_split(g.sum_n, g.max_nd, GMM_SETUP_INIT);
         const auto &v = m64[pl.keys[k]];
         e = hipMemcpy(g.map64, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice);
         b->groups.push_back(g);
@@ -427,7 +427,7 @@ smc_status smc_batch_waves(const smc_batch *b, int32_t K, int32_t *waves)
         return SMC_ERR_INVALID_ARG;
     for (const KGroup &g : b->groups)
         if (g.K == K) {
-            *waves = g.W;
+            *waves = g.split.W;
             return SMC_OK;
         }
     return SMC_ERR_INVALID_ARG;
@@ -446,7 +446,7 @@ smc_status smc_batch_init(smc_batch *b)
         e = launch_pf_init_batch(b->dprobs, b->map_pf, b->pf_tiles, s);
     for (const KGroup &g : b->groups)
         if (e == hipSuccess)
-            e = launch_gmm_init_batch(b->dprobs, g.map64, g.tiles64, g.K, g.W, g.mala, s);
+            e = launch_gmm_init_batch(b->dprobs, g.map64, g.tiles64, g.K, g.split, g.mala, s);
     if (e == hipSuccess)
         e = launch_const_partials_batch(b->dprobs, b->map_gmm, b->gmm_tiles, s);
     if (e == hipSuccess)

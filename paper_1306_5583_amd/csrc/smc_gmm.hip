@@ -5,6 +5,8 @@
 // smc_gmm_impl.hpp and instantiated in smc_gmm_k*.hip.
 #include <math.h>
 
+#include <algorithm>
+
 #include "smc_gmm_impl.hpp"
 #include "smc_tiles.hpp"
 
@@ -70,6 +72,46 @@ int gmm_waves(int64_t n, int64_t nd)
     return W;
 }
 
+// The split with the least modelled time, in units of one data point's terms.
+// A lane's chain is `setup` (what a launch does besides its data, overlapped
+// by the waves sharing the SIMD to three quarters) plus its points, which the
+// SIMD's waves share at about 85 % of issue; compute units take workgroups in
+// whole turns.  The model puts the line where the measurements have it
+// (random-walk step, K = 4, 1000 points; setup 60, us):
+//   particles   8 waves x 64   best sliced            model
+//   64          119            23 (4 waves x 1)       64 lanes a particle
+//   1000        118            33 (4 waves x 4)       the same
+//   4000        118            55 (4 waves x 16)      the same
+//   12000       121            105 (4 waves x 16)     the same
+//   16384       125            128 (4 waves x 32)     unsliced
+//   20000       220            166 (4 waves x 16)     the same
+//   40000       328            290 (4 waves x 32)     the same
+// and K = 6 with the gradient, 1000 vectors, 10^4 points: 633 -> 57 us.
+// Above 2^17 particles the turns are many and the split no longer matters.
+GmmSplit gmm_split(int64_t n, int64_t nd, double setup)
+{
+    constexpr int CUS = 256, SIMDS = 4;
+    const auto cost = [&](const GmmSplit &sp) {
+        const int64_t turns = ceil_div(ceil_div(n, WAVE >> sp.lsl), CUS);
+        const double w = std::max(1.0, (double)turns * sp.W / SIMDS);  // waves of a SIMD
+        const double points = (double)nd / ((double)sp.W * (1 << sp.lsl));
+        return setup * (1.0 + 0.25 * (w - 1.0)) + points * (0.15 + 0.85 * w);
+    };
+    GmmSplit best{gmm_waves(n, nd), 0};
+    if (n > (1 << 17))
+        return best;
+    double t = 0.97 * cost(best);
+    for (int lsl = 0; lsl <= 6 && (int64_t)4 << lsl <= nd; ++lsl) {
+        const GmmSplit sp{4, lsl};
+        const double c = cost(sp);
+        if (c < t) {
+            t = c;
+            best = sp;
+        }
+    }
+    return best;
+}
+
 #define SMC_K_SWITCH(K_, CALL)                                                                   \
     switch (K_) {                                                                                \
     case 1: return CALL(1);                                                                      \
@@ -93,8 +135,8 @@ int gmm_waves(int64_t n, int64_t nd)
 
 hipError_t launch_gmm_init(Ctx &c)
 {
-    const int W = gmm_waves(c.n, c.cfg.n_data);
-#define CALL_INIT(k) GmmK<k>::init(c, W)
+    const GmmSplit sp = gmm_split(c.n, c.cfg.n_data, GMM_SETUP_INIT);
+#define CALL_INIT(k) GmmK<k>::init(c, sp)
     hipError_t e;
     {
         auto f = [&]() -> hipError_t { SMC_K_SWITCH(c.cfg.K, CALL_INIT) };
@@ -120,10 +162,10 @@ hipError_t launch_gmm_reweight(Ctx &c, double dalpha, bool reset_check)
 hipError_t launch_gmm_move(Ctx &c, int32_t step, const smc_move_args &a, bool gather_check)
 {
     // every block of every sweep in one launch (gmm_step_kernel)
-    const int W = gmm_waves(c.n, c.cfg.n_data);
+    const GmmSplit sp = gmm_split(c.n, c.cfg.n_data, GMM_SETUP_STEP);
     const int sweeps = a.sweeps > 0 ? a.sweeps : (c.cfg.sweeps > 0 ? c.cfg.sweeps : 1);
     const double scale[3] = {a.scale[0], a.scale[1], a.scale[2]};
-#define CALL_STEP(k) GmmK<k>::step(c, W, step, sweeps, a.alpha, scale, gather_check)
+#define CALL_STEP(k) GmmK<k>::step(c, sp, step, sweeps, a.alpha, scale, gather_check)
     hipError_t e;
     {
         auto f = [&]() -> hipError_t { SMC_K_SWITCH(c.cfg.K, CALL_STEP) };
@@ -145,14 +187,14 @@ hipError_t launch_gmm_loglik_grad(const double *mu, const double *eta, const dou
 }
 
 // ---------------------------------------------------------------------------
-// Batched initialisation (one launch per K group; W waves per 64-particle tile)
+// Batched initialisation (one launch per K group)
 // ---------------------------------------------------------------------------
 hipError_t launch_gmm_init_batch(const Prob *probs, const int2 *map64, int64_t tiles64, int K,
-                                 int W, bool mala, hipStream_t s)
+                                 GmmSplit sp, bool mala, hipStream_t s)
 {
     if (tiles64 == 0)
         return hipSuccess;
-#define CALL_IB(k) GmmK<k>::init_batch(probs, map64, tiles64, W, mala, s)
+#define CALL_IB(k) GmmK<k>::init_batch(probs, map64, tiles64, sp, mala, s)
     SMC_K_SWITCH(K, CALL_IB)
 #undef CALL_IB
 }

@@ -12,12 +12,15 @@
 // The likelihood is the hot loop: l = sum_k lse_j(c_j - lambda_j (y_k -
 // mu_j)^2 / 2), c_j = log omega_j + eta_j / 2 - log(2 pi) / 2, i.e. n K
 // "mixture terms" per particle, each a multiply-add, a square, an
-// exponential and a multiply-add, plus one logarithm per 128 points.  A workgroup holds 64 particles (one per lane) and W waves;
-// wave w walks its own contiguous chunk of the data with wave-uniform
+// exponential and an addition, plus one logarithm per 128 points.  A
+// workgroup holds 64 particles (one per lane) and W waves; wave w walks its
+// own contiguous chunk of the data with wave-uniform
 // (scalar) loads of y, every lane keeps its particle's 3K constants and its
 // accumulators in registers, and the W partial sums are combined in wave
 // order through LDS.  Nothing here is a dense contraction, so the vector ALU
-// (FP64) is the roofline, not the matrix cores.
+// (FP64) is the roofline, not the matrix cores.  A population too small to
+// fill the chip that way gives each particle 2^lsl neighbouring lanes, which
+// share its data (gmm_split()).
 #include <math.h>
 
 #pragma once
@@ -115,13 +118,22 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 // which factors the largest term out of each point, for the rest of the chunk
 // (a vector far from the data is out of range at most points; the first
 // segment is one group, so such a wave changes over at once).  A wave with a
-// parameter that is not finite takes the whole chunk in the safe form.
+// parameter that is not finite takes the whole chunk in the safe form, and a
+// sum that comes out NaN is taken again with zero for the terms that are not
+// finite.
+//
+// Tournament form (K <= 8 without the gradient, K = 2 with it): the largest
+// a_j = c_j log2(e) - u_j^2 is carried through K - 1 maxima, the loser of each
+// match kept, so that only K - 1 powers 2^-(m - loser) are taken, s = 1 +
+// their sum.  2 (K - 1) comparisons replace a power of 13 instructions, and
+// no point is out of range; the gradient needs every term in its place, which
+// two components get back by a selection.
 //
 // Bound: FP64 vector issue (every instruction of the loop is full rate).
-// 16 instructions per term and 3.5 per point; factoring the maximum out of
-// every point (a maximum, a subtraction and a separate constant more per
-// term) took 19 per term and 3 per point.  With the gradient at K = 6, 2^14
-// vectors, 10^4 points: 727 -> 673 us a call, 46 TFLOP/s.
+// Per point 16 K + 3.5 instructions (fast form) or 17 K - 11 (tournament);
+// factoring the maximum out of every point took 19 K + 3.  Value at K = 4,
+// 2^14 vectors, 2000 points 95 -> 73 us; with the gradient at K = 6, 2^14
+// vectors, 10^4 points 727 -> 673 us a call, 46 TFLOP/s.
 //
 // Gradient (GRAD): with responsibilities r_j = 2^(SHIFT - a_j) / s and
 // lambda_j d_j = 2 ln2 g_j u_j, lambda_j d_j^2 / 2 = ln2 u_j^2:
@@ -129,18 +141,25 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 //   d/d eta_j = sum r_j (1/2 - lambda_j d_j^2 / 2) = sum r_j / 2 - ln2 sum r_j u_j^2
 // accumulated as sum r u (in gmu), sum r u^2 (in geta) and sum r (in gr)
 // and converted once in finish().
+// Largest K without the gradient that takes the tournament form: the two
+// forms cross there (value of 2^14 vectors at 2000 points, us: K = 2 33
+// against 50, K = 4 73 / 86, K = 6 120 / 123, K = 8 163 / 157, K = 12
+// 244 / 238; the tournament has no points out of range, so it keeps K = 8).
+constexpr int TOURN_MAX_K = 8;
+
 template <int K, bool GRAD>
 struct MixLik {
     // points per group: independent chains for the two waves a SIMD holds,
     // as far as the registers allow (the gradient keeps every term of the
     // group until its reciprocal is known)
     static constexpr int GROUP = K > 8 || (GRAD && K > 6) ? 1 : (GRAD || K > 4 ? 2 : 4);
-    static constexpr int SEG = 32;     // points per segment after the first
+    static constexpr bool TOURN = K > 1 && (GRAD ? K == 2 : K <= TOURN_MAX_K);
     // the gradient of K > 3 goes back to the chunk's start instead of
     // to_safe(), whose registers would spill (four or more components all out
     // of range are rare)
     static constexpr bool RESTART = GRAD && K > 3;
-    static constexpr int FLUSH = 128;  // points per logarithm (safe form: factors <= 16)
+    // points per segment, one logarithm each (safe form: factors <= 16).  Segments of 32 points cost 3 %.
+    static constexpr int FLUSH = 128;
     // s <= K 2^SHIFT <= 2^494; s > 2^-500 has a power above 2^-504, so every
     // s that counts, the product of two and its reciprocal are normal
     static constexpr int SHIFT = 490;
@@ -168,12 +187,12 @@ struct MixLik {
             g[j] = sqrt((0.5 * detail::kLog2e) * exp_d(phi[K + j]));
             gm[j] = g[j] * phi[j];
             c[j] = detail::kLog2e * (logw[j] + 0.5 * phi[K + j] - kHalfLog2Pi);
-            ok = ok && fabs(c[j]) < 0x1p20 && fabs(gm[j]) < 0x1p500;
+            ok = ok && fabs(c[j]) < 0x1p20 && g[j] < 0x1p500 && fabs(gm[j]) < 0x1p500;
             cmax = fmax(cmax, c[j]);
         }
         fast = __all(ok);
         off = 0;
-        if (fast) {
+        if (!TOURN && fast) {
             const double o = ceil(cmax);
             off = (int)o;
 #pragma unroll
@@ -197,8 +216,10 @@ struct MixLik {
     }
 
     // One point in the safe form: the maximum m of the a_j = cl_j - u_j^2
-    // (cl_j = c_j log2(e)) factored out, s = sum_j 2^(a_j - m) in [1, K];
-    // a_j = -inf is a zero term.
+    // (cl_j = c_j log2(e)) factored out, s = sum_j 2^(a_j - m) in [1, K].
+    // CLAMP: a_j = -inf or NaN is a zero term (without it the sums become
+    // NaN).
+    template <bool CLAMP>
     __device__ __forceinline__ void point(double y, const double (&cl)[K])
     {
         double e[K], u[K];
@@ -214,7 +235,7 @@ struct MixLik {
         double s = 0.0;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            e[j] = exp2_nonpos(e[j] - m);
+            e[j] = CLAMP ? exp2_nonpos(e[j] - m) : exp2_neg(m - e[j]);
             s = j == 0 ? e[0] : s + e[j];
         }
         m2 += m;
@@ -265,9 +286,58 @@ struct MixLik {
         return good;
     }
 
+    // One point in the tournament form (finite parameters; a_j = -inf, from a
+    // point that is not finite, makes the sums NaN or counts as zero).
+    __device__ __forceinline__ void tournament(double y)
+    {
+        double e[K], u[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            u[j] = fma(g[j], y, -gm[j]);
+            e[j] = fma(-u[j], u[j], c[j]);
+        }
+        if constexpr (GRAD) {  // K == 2
+            const double d = e[0] - e[1];
+            m2 += fmax(e[0], e[1]);
+            const double w = exp2_neg(fabs(d));
+            const double s = 1.0 + w;
+            prod *= s;
+            const double inv = recip(s), low = w * inv;
+            const bool first = d >= 0.0;
+            const double r[2] = {first ? inv : low, first ? low : inv};
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const double ru = r[j] * u[j];
+                gmu[j] += ru;
+                geta[j] = fma(ru, u[j], geta[j]);
+                gr[j] += r[j];
+            }
+        } else {
+            double m = e[0];
+#pragma unroll
+            for (int j = 1; j < K; ++j) {
+                const double lo = fmin(m, e[j]);
+                m = fmax(m, e[j]);
+                e[j] = lo;
+            }
+            m2 += m;
+            double s = 0.0;
+#pragma unroll
+            for (int j = 1; j < K; ++j)
+                s += exp2_neg(m - e[j]);
+            prod = fma(prod, s, prod);
+        }
+    }
+
     template <int N>
     __device__ __forceinline__ void group(const double (&y)[N])
     {
+        if constexpr (TOURN) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                tournament(y[i]);
+            return;
+        }
         double u[N][K], e[N][K], s[N];
         const bool good = densities<N, false>(y, u, e, s);
         bad = bad | !good;
@@ -318,10 +388,11 @@ struct MixLik {
         fast = false;
     }
 
-    // From the fast to the safe form, with the groups of N points of the
-    // segment [k, kend) that group() left out of a lane's sums.
+    // From the fast to the safe form, with the groups of N points at k, k +
+    // step, .. below kend that group() left out of a lane's sums.
     template <int N>
-    __device__ __forceinline__ void to_safe(const double *__restrict__ y, int64_t k, int64_t kend)
+    __device__ __forceinline__ void to_safe(const double *__restrict__ y, int64_t k, int64_t kend,
+                                            int step)
     {
         flush();
         if (bad) {
@@ -330,7 +401,7 @@ struct MixLik {
             for (int j = 0; j < K; ++j)
                 cl[j] = (double)off - c[j];
 #pragma nounroll
-            for (; k < kend; k += N) {
+            for (; k < kend; k += step) {
                 double a[N], u[N][K], e[N][K], s[N];
 #pragma unroll
                 for (int i = 0; i < N; ++i)
@@ -339,7 +410,7 @@ struct MixLik {
                     m2 -= ((N + 1) / 2) * OUT + N * (off - SHIFT);
 #pragma nounroll
                     for (int i = 0; i < N; ++i)
-                        point(y[k + i], cl);
+                        point<false>(y[k + i], cl);
                 }
             }
         }
@@ -359,13 +430,20 @@ struct MixLik {
         }
     }
 
-    // accumulate the points [k0, k1) (uniform across the wave): wave-uniform
-    // loads, the next group fetched one group ahead
-    __device__ __forceinline__ void chunk(const double *__restrict__ y, int64_t k0, int64_t k1)
+    // The points [k0, k1) (uniform across the wave) of this lane's particle.
+    // Unsliced, every lane takes all of them: wave-uniform loads, the next
+    // group fetched one group ahead.  SLICED, the 2^lsl lanes of a particle
+    // share them, a group each in turn (neighbouring lanes read neighbouring
+    // groups), the remainder point by point.
+    template <bool SLICED>
+    __device__ __forceinline__ void chunk(const double *__restrict__ y, int64_t k0, int64_t k1,
+                                          int lsl)
     {
+        const int slice = SLICED ? lane_id() & ((1 << lsl) - 1) : 0;
+        const int one = SLICED ? 1 << lsl : 1;  // stride of single points
         int64_t k = k0;
         if constexpr (K == 1) {
-            for (; k < k1; ++k) {
+            for (k += slice; k < k1; k += one) {
                 const double u = fma(g[0], y[k], -gm[0]);
                 m2 += fma(-u, u, c[0]);
                 if (GRAD) {
@@ -375,18 +453,20 @@ struct MixLik {
                 }
             }
         } else {
-            int len = GROUP, since = 0;
-            while (fast && k + GROUP <= k1) {
+            const int step = GROUP * one;
+            const double *__restrict__ yg = y + slice * GROUP;  // this lane's groups
+            int len = TOURN ? FLUSH / GROUP : 1;
+            while (fast && k + step <= k1) {
                 const int64_t kseg = k;
-                const int groups = (int)min((int64_t)len, k1 - k) / GROUP;
-                const double *__restrict__ p = y + k;
+                const int groups = (int)min((int64_t)len, (k1 - k) / step);
+                const double *__restrict__ p = yg + k;
                 double a[GROUP];
 #pragma unroll
                 for (int i = 0; i < GROUP; ++i)
                     a[i] = p[i];
                 for (int r = 1; r < groups; ++r) {
                     double b[GROUP];
-                    p += GROUP;
+                    p += step;
 #pragma unroll
                     for (int i = 0; i < GROUP; ++i)
                         b[i] = p[i];
@@ -396,60 +476,89 @@ struct MixLik {
                         a[i] = b[i];
                 }
                 group<GROUP>(a);
-                k += groups * GROUP;
-                since += groups * GROUP;
-                len = SEG;
-                if (__any(bad)) {
+                k += (int64_t)groups * step;
+                // three components are out of range more often: a short
+                // second segment
+                len = K <= 3 && len == 1 ? 16 / GROUP : FLUSH / GROUP;
+                if (!TOURN && __any(bad)) {
                     if constexpr (RESTART) {
                         reset();
                         safe_constants();
                         k = k0;
                     } else {
-                        to_safe<GROUP>(y, kseg, k);
+                        to_safe<GROUP>(yg, kseg, k, step);
                     }
-                } else if (since + SEG > FLUSH) {
+                } else {
                     flush();
-                    since = 0;
                 }
             }
-            if (GROUP > 1 && fast && k < k1) {
-                const int64_t kseg = k;
-                for (; k < k1; ++k) {
-                    const double a[1] = {y[k]};
+            if ((SLICED || GROUP > 1) && fast && k < k1) {
+                for (int64_t q = k + slice; q < k1; q += one) {
+                    const double a[1] = {y[q]};
                     group<1>(a);
                 }
-                if (__any(bad)) {
+                if (!TOURN && __any(bad)) {
                     if constexpr (RESTART) {
                         reset();
                         safe_constants();
                         k = k0;
                     } else {
-                        to_safe<1>(y, kseg, k1);
+                        to_safe<1>(y + slice, k, k1 - slice, one);
+                        k = k1;
                     }
+                } else {
+                    k = k1;
                 }
             }
             flush();
-            while (k < k1) {  // the safe form
-                const int64_t kend = min(k + FLUSH / 2, k1);
+            if constexpr (TOURN) {
+                if (!fast)
+                    m2 = __builtin_nan("");
+                k = k1;
+            }
+            // the safe form
+            if constexpr (SLICED) {
+                int m = 0;
+                for (k += slice; k < k1; k += one) {
+                    point<false>(y[k], c);
+                    if (++m == FLUSH) {
+                        flush();
+                        m = 0;
+                    }
+                }
+                flush();
+            }
+            while (k < k1) {
+                const int64_t kend = min(k + FLUSH, k1);
                 if (K <= 8 && k + 2 <= kend) {  // two points at a time
                     double y0 = y[k], y1 = y[k + 1];
+#pragma unroll 2
                     for (; k + 4 <= kend; k += 2) {
                         const double n0 = y[k + 2], n1 = y[k + 3];
-                        point(y0, c);
-                        point(y1, c);
+                        point<false>(y0, c);
+                        point<false>(y1, c);
                         y0 = n0;
                         y1 = n1;
                     }
-                    point(y0, c);
-                    point(y1, c);
+                    point<false>(y0, c);
+                    point<false>(y1, c);
                     k += 2;
                 }
                 for (; k < kend; ++k)
-                    point(y[k], c);
+                    point<false>(y[k], c);
                 flush();
             }
         }
         finish();
+        if (K > 1 && ll != ll) {  // a term that is not finite: once more, clamped
+            reset();
+#pragma nounroll
+            for (k = k0 + slice; k < k1; k += one) {
+                point<true>(y[k], c);
+                flush();
+            }
+            finish();
+        }
     }
 
     static constexpr int NACC = GRAD ? 1 + 3 * K : 1;
@@ -465,12 +574,34 @@ struct MixLik {
     }
 };
 
-// Combines the accumulators of the W waves in wave order; wave 0 ends with
-// the totals.  `red` holds GMM_RED_GROUP * GMM_MAXW * 64 doubles.
+// Sums over the 2^lsl neighbouring lanes of a particle, complete in the last
+// of them (the steps of the wave scan, as many as the slices need).
 template <int K, bool GRAD>
-__device__ __forceinline__ void combine_waves(MixLik<K, GRAD> &L, int W, double *red)
+__device__ __forceinline__ void combine_slices(MixLik<K, GRAD> &L, int lsl)
+{
+#define SMC_SLICE_STEP(STEP, ...)                                                                 \
+    if (lsl > STEP) {                                                                             \
+        _Pragma("unroll") for (int q = 0; q < MixLik<K, GRAD>::NACC; ++q)                         \
+            L.acc(q) += dpp::mov<__VA_ARGS__>(L.acc(q), 0.0);                                     \
+    }
+    SMC_SLICE_STEP(0, dpp::ROW_SHR1)
+    SMC_SLICE_STEP(1, dpp::ROW_SHR2)
+    SMC_SLICE_STEP(2, dpp::ROW_SHR4)
+    SMC_SLICE_STEP(3, dpp::ROW_SHR8)
+    SMC_SLICE_STEP(4, dpp::ROW_BCAST15, 0xA)
+    SMC_SLICE_STEP(5, dpp::ROW_BCAST31, 0xC)
+#undef SMC_SLICE_STEP
+}
+
+// Combines the accumulators of the W waves in wave order; wave 0 ends with
+// the totals (SLICED: in the last lane of each particle).  `red` holds
+// GMM_RED_GROUP * GMM_MAXW * 64 doubles.
+template <int K, bool GRAD, bool SLICED>
+__device__ __forceinline__ void combine_waves(MixLik<K, GRAD> &L, int W, int lsl, double *red)
 {
     constexpr int NACC = MixLik<K, GRAD>::NACC;
+    if (SLICED)
+        combine_slices<K, GRAD>(L, lsl);
     const int w = wave_id(), lane = lane_id();
     for (int q0 = 0; q0 < NACC; q0 += GMM_RED_GROUP) {
         __syncthreads();
@@ -503,6 +634,23 @@ __device__ __forceinline__ void data_chunk(int64_t nd, int W, int64_t *k0, int64
     *k1 = min(*k0 + per, nd);
 }
 
+// The particle and column of a lane when 2^lsl neighbouring lanes share a
+// particle (lsl = 0: one lane each): `tile` covers 64 >> lsl particles; the
+// last lane of a particle leads (its sums are complete, its LDS column holds
+// the particle's state).
+struct LaneMap {
+    int64_t i;  // particle
+    int col;    // the particle's leading lane
+    bool lead;
+    __device__ __forceinline__ LaneMap(int64_t tile, int lsl)
+    {
+        const int lane = lane_id();
+        i = tile * (WAVE >> lsl) + (lane >> lsl);
+        col = lane | ((1 << lsl) - 1);
+        lead = col == lane;
+    }
+};
+
 // z-gradient from the accumulated responsibilities: sum_k (r_kj - omega_j)
 template <int K>
 __device__ __forceinline__ double z_grad(double gr_j, double logw_j, int64_t nd)
@@ -517,8 +665,8 @@ __device__ __forceinline__ double z_grad(double gr_j, double logw_j, int64_t nd)
 // 64 + 1024 + 64 j); then log prior and log-likelihood (and its gradient for
 // MALA); log-weights 0.
 // ---------------------------------------------------------------------------
-template <int K, bool GRAD>
-__device__ __forceinline__ void gmm_init_tile(const Prob &P, int W, int64_t tile)
+template <int K, bool GRAD, bool SLICED>
+__device__ __forceinline__ void gmm_init_tile(const Prob &P, int W, int64_t tile, int lsl)
 {
     constexpr int D = 3 * K - 1;
     __shared__ double red[GMM_RED_GROUP * GMM_MAXW * WAVE];
@@ -531,7 +679,8 @@ __device__ __forceinline__ void gmm_init_tile(const Prob &P, int W, int64_t tile
     const GmmPrior pr = P.prior;
     const double mu_sd = P.mu_sd;
     int32_t *__restrict__ counters = P.counters;
-    const int64_t i = tile * WAVE + lane_id();
+    const LaneMap lm(tile, SLICED ? lsl : 0);
+    const int64_t i = lm.i;
     const bool valid = i < n;
     const uint32_t ii = (uint32_t)(valid ? i : 0);
     double phi[D > 0 ? D : 1];
@@ -563,9 +712,9 @@ __device__ __forceinline__ void gmm_init_tile(const Prob &P, int W, int64_t tile
     L.setup(phi, logw);
     int64_t k0, k1;
     data_chunk(nd, W, &k0, &k1);
-    L.chunk(y, k0, k1);
-    combine_waves<K, GRAD>(L, W, red);
-    if (wave_id() == 0 && valid) {
+    L.template chunk<SLICED>(y, k0, k1, lsl);
+    combine_waves<K, GRAD, SLICED>(L, W, lsl, red);
+    if (wave_id() == 0 && valid && lm.lead) {
 #pragma unroll
         for (int q = 0; q < D; ++q)
             st[(int64_t)q * n + i] = phi[q];
@@ -586,18 +735,20 @@ __device__ __forceinline__ void gmm_init_tile(const Prob &P, int W, int64_t tile
     }
 }
 
-template <int K, bool GRAD>
-__global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_init_kernel(Prob P, int W)
+template <int K, bool GRAD, bool SLICED>
+__global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_init_kernel(Prob P, int W, int lsl)
 {
-    gmm_init_tile<K, GRAD>(P, W, blockIdx.x);
+    gmm_init_tile<K, GRAD, SLICED>(P, W, blockIdx.x, lsl);
 }
 
-template <int K, bool GRAD>
+// 2^lsl workgroups take the parts of each 64-particle tile of the map.
+template <int K, bool GRAD, bool SLICED>
 __global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_init_batch_kernel(
-    const Prob *__restrict__ probs, const int2 *__restrict__ map, int W)
+    const Prob *__restrict__ probs, const int2 *__restrict__ map, int W, int lsl)
 {
-    const int2 pm = map[blockIdx.x];
-    gmm_init_tile<K, GRAD>(probs[pm.x], W, pm.y);
+    const int2 pm = map[SLICED ? blockIdx.x >> lsl : blockIdx.x];
+    const int64_t tile = SLICED ? ((int64_t)pm.y << lsl) + (blockIdx.x & ((1u << lsl) - 1)) : pm.y;
+    gmm_init_tile<K, GRAD, SLICED>(probs[pm.x], W, tile, lsl);
 }
 
 // ---------------------------------------------------------------------------
@@ -693,9 +844,9 @@ constexpr int gmm_stash_doubles() { return BlockStash<K, MALA>::ROWS * WAVE; }
 // the LDS hand-off modes `io`, `hand` (gmm_hand_doubles(K, MALA)) are the
 // caller's LDS.  With GMM_IO_GLOBAL the block reads `src` and writes `dst`
 // (every row when `full`, else the accepted rows in place).
-template <int K, bool MALA>
+template <int K, bool MALA, bool SLICED>
 __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__restrict__ src,
-                                               double *__restrict__ dst, int full, int W,
+                                               double *__restrict__ dst, int full, int W, int lsl,
                                                int64_t tile, uint32_t t, int block, int sweep,
                                                double alpha, double scale, int32_t step,
                                                double *red, double *stash, int io = GMM_IO_GLOBAL,
@@ -716,12 +867,13 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
     const int64_t hist_len = P.hist_len;
     const bool gather = full && !in_lds && P.scalars[SMC_S_RESAMPLED] != 0.0;
     const int lane = lane_id();
-    const int64_t i = tile * WAVE + lane;
+    const LaneMap lm(tile, SLICED ? lsl : 0);
+    const int64_t i = lm.i;
     const bool valid = i < n;
     // the state is read from column si of rows of length sn (global: the
-    // particle or its ancestor; LDS: the lane) and written to column wi of
-    // rows of length wn
-    const int64_t si = in_lds ? lane : (valid ? (gather ? (int64_t)anc[i] : i) : 0);
+    // particle or its ancestor; LDS: the particle's leading lane) and written
+    // by that lane to column wi of rows of length wn
+    const int64_t si = in_lds ? lm.col : (valid ? (gather ? (int64_t)anc[i] : i) : 0);
     const int64_t sn = in_lds ? WAVE : n;
     const double *__restrict__ rs = in_lds ? hand : src;
     double *__restrict__ ws = out_lds ? hand : dst;
@@ -761,13 +913,13 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
     }
     int64_t k0, k1;
     data_chunk(nd, W, &k0, &k1);
-    L.chunk(y, k0, k1);
+    L.template chunk<SLICED>(y, k0, k1, lsl);
     double ll0 = 0.0, lp0 = 0.0;
     if (wave_id() == 0) {
         ll0 = rs[(int64_t)D * sn + si];
         lp0 = rs[(int64_t)(D + 1) * sn + si];
     }
-    combine_waves<K, MALA>(L, W, red);
+    combine_waves<K, MALA, SLICED>(L, W, lsl, red);
     if (wave_id() != 0)
         return;
     double phi[D > 0 ? D : 1];
@@ -800,8 +952,8 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
         }
         logr += (stash[S::FWD * WAVE + lane] - bwd) / (2.0 * h2);
     }
-    const bool acc = valid && stash[S::LOGU * WAVE + lane] <= logr;
-    if (valid || out_lds) {
+    const bool acc = valid && lm.lead && stash[S::LOGU * WAVE + lane] <= logr;
+    if (lm.lead && (valid || out_lds)) {
         if (out_all) {
 #pragma unroll
             for (int q = 0; q < D; ++q) {
@@ -849,9 +1001,10 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
 // barrier), and the last one writes the whole state to `dst`.
 // A random walk with K <= 4 fits two workgroups of eight waves on a compute
 // unit (128 registers).
-template <int K, bool MALA>
+template <int K, bool MALA, bool SLICED>
 __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : 2) void gmm_step_kernel(
-    Prob P, const double *__restrict__ src, double *__restrict__ dst, int full, int W, uint32_t t,
+    Prob P, const double *__restrict__ src, double *__restrict__ dst, int full, int W, int lsl,
+    uint32_t t,
     int sweeps, double alpha, double s0, double s1, double s2, int32_t step)
 {
     __shared__ double red[GMM_RED_DOUBLES];
@@ -864,10 +1017,10 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : 2) void gmm_s
             const bool last = sw == sweeps - 1 && b == nb - 1;
             if (!first)
                 __syncthreads();
-            gmm_block_tile<K, MALA>(P, src, dst, first ? full : 0, W, blockIdx.x, t, b, sw, alpha,
-                                    b == 0 ? s0 : (b == 1 ? s1 : s2), step, red, stash,
-                                    first ? GMM_IO_FIRST : (last ? GMM_IO_LAST : GMM_IO_LDS),
-                                    hand);
+            gmm_block_tile<K, MALA, SLICED>(
+                P, src, dst, first ? full : 0, W, lsl, blockIdx.x, t, b, sw, alpha,
+                b == 0 ? s0 : (b == 1 ? s1 : s2), step, red, stash,
+                first ? GMM_IO_FIRST : (last ? GMM_IO_LAST : GMM_IO_LDS), hand);
         }
 }
 
@@ -878,15 +1031,16 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : 2) void gmm_s
 // Four waves per SIMD (128 registers) where that costs no spill: K = 4 with
 // the gradient would take 141, and 2^16 vectors of 1000 points 249 us against
 // 224).
-template <int K, bool GRAD>
+template <int K, bool GRAD, bool SLICED>
 __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 ? 4 : 2) void gmm_loglik_kernel(
     const double *__restrict__ mu, const double *__restrict__ eta, const double *__restrict__ z,
-    int64_t n, const double *__restrict__ y, int64_t nd, int W, double *__restrict__ ll,
+    int64_t n, const double *__restrict__ y, int64_t nd, int W, int lsl, double *__restrict__ ll,
     double *__restrict__ grad)
 {
     constexpr int D = 3 * K - 1;
     __shared__ double red[GMM_RED_GROUP * GMM_MAXW * WAVE];
-    const int64_t i = (int64_t)blockIdx.x * WAVE + lane_id();
+    const LaneMap lm(blockIdx.x, SLICED ? lsl : 0);
+    const int64_t i = lm.i;
     const bool valid = i < n;
     const int64_t si = valid ? i : 0;
     double phi[D > 0 ? D : 1];
@@ -903,9 +1057,9 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 ? 4 : 2) void gmm_loglik_ker
     L.setup(phi, logw);
     int64_t k0, k1;
     data_chunk(nd, W, &k0, &k1);
-    L.chunk(y, k0, k1);
-    combine_waves<K, GRAD>(L, W, red);
-    if (wave_id() == 0 && valid) {
+    L.template chunk<SLICED>(y, k0, k1, lsl);
+    combine_waves<K, GRAD, SLICED>(L, W, lsl, red);
+    if (wave_id() == 0 && valid && lm.lead) {
         ll[i] = L.ll;
         if (GRAD) {
 #pragma unroll
@@ -921,60 +1075,74 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 ? 4 : 2) void gmm_loglik_ker
 
 // Host launchers of the K-templated kernels; explicitly instantiated in the
 // smc_gmm_k*.hip translation units (compiled in parallel).
-int gmm_waves(int64_t n, int64_t nd);
-
 template <int K>
 struct GmmK {
-    static hipError_t init(Ctx &c, int W);
-    static hipError_t step(Ctx &c, int W, int32_t step, int sweeps, double alpha,
+    static hipError_t init(Ctx &c, GmmSplit sp);
+    static hipError_t step(Ctx &c, GmmSplit sp, int32_t step, int sweeps, double alpha,
                            const double (&scale)[3], bool gather_check);
     static hipError_t loglik(const double *mu, const double *eta, const double *z, int64_t n,
                              const double *y, int64_t nd, double *ll, double *grad, hipStream_t s);
-    static hipError_t init_batch(const Prob *probs, const int2 *map, int64_t tiles, int W,
+    static hipError_t init_batch(const Prob *probs, const int2 *map, int64_t tiles, GmmSplit sp,
                                  bool mala, hipStream_t s);
 };
 
 template <int K>
-hipError_t GmmK<K>::init(Ctx &c, int W)
+hipError_t GmmK<K>::init(Ctx &c, GmmSplit sp)
 {
-    const dim3 grid((unsigned)ceil_div(c.n, WAVE)), block((unsigned)(W * WAVE));
-    const Key key = make_key(c.cfg.seed);
+    const dim3 grid((unsigned)ceil_div(c.n, WAVE >> sp.lsl)), block((unsigned)(sp.W * WAVE));
     const Prob P = make_prob(c);
-    (void)key;
-    if (c.cfg.move_kind == SMC_MOVE_MALA)
-        hipLaunchKernelGGL((gmm_init_kernel<K, true>), grid, block, 0, c.stream, P, W);
-    else
-        hipLaunchKernelGGL((gmm_init_kernel<K, false>), grid, block, 0, c.stream, P, W);
+#define SMC_INIT(GRAD, SLICED)                                                                    \
+    hipLaunchKernelGGL((gmm_init_kernel<K, GRAD, SLICED>), grid, block, 0, c.stream, P, sp.W,     \
+                       sp.lsl)
+    if (c.cfg.move_kind == SMC_MOVE_MALA) {
+        if (sp.lsl > 0)
+            SMC_INIT(true, true);
+        else
+            SMC_INIT(true, false);
+    } else {
+        if (sp.lsl > 0)
+            SMC_INIT(false, true);
+        else
+            SMC_INIT(false, false);
+    }
+#undef SMC_INIT
     return hipGetLastError();
 }
 
 template <int K>
-hipError_t GmmK<K>::step(Ctx &c, int W, int32_t step, int sweeps, double alpha,
+hipError_t GmmK<K>::step(Ctx &c, GmmSplit sp, int32_t step, int sweeps, double alpha,
                          const double (&scale)[3], bool gather_check)
 {
-    const dim3 grid((unsigned)ceil_div(c.n, WAVE)), blk((unsigned)(W * WAVE));
+    const dim3 grid((unsigned)ceil_div(c.n, WAVE >> sp.lsl)), blk((unsigned)(sp.W * WAVE));
     const double *src = (const double *)c.state_ptr();
     double *dst = gather_check ? (double *)c.other_ptr() : (double *)c.state_ptr();
     const Prob P = make_prob(c);
     hipEvent_t e0, e1;
     const bool timed = c.prof_take(&e0, &e1);
 #define SMC_STEP_ARGS                                                                             \
-    P, src, dst, (int)gather_check, W, (uint32_t)step, sweeps, alpha, scale[0], scale[1],         \
-        scale[2], step
+    P, src, dst, (int)gather_check, sp.W, sp.lsl, (uint32_t)step, sweeps, alpha, scale[0],        \
+        scale[1], scale[2], step
+#define SMC_STEP(MALA, SLICED)                                                                    \
+    do {                                                                                          \
+        if (timed)                                                                                \
+            hipExtLaunchKernelGGL((gmm_step_kernel<K, MALA, SLICED>), grid, blk, 0, c.stream, e0, \
+                                  e1, 0, SMC_STEP_ARGS);                                          \
+        else                                                                                      \
+            hipLaunchKernelGGL((gmm_step_kernel<K, MALA, SLICED>), grid, blk, 0, c.stream,        \
+                               SMC_STEP_ARGS);                                                    \
+    } while (0)
     if (c.cfg.move_kind == SMC_MOVE_MALA) {
-        if (timed)
-            hipExtLaunchKernelGGL((gmm_step_kernel<K, true>), grid, blk, 0, c.stream, e0, e1, 0,
-                                  SMC_STEP_ARGS);
+        if (sp.lsl > 0)
+            SMC_STEP(true, true);
         else
-            hipLaunchKernelGGL((gmm_step_kernel<K, true>), grid, blk, 0, c.stream, SMC_STEP_ARGS);
+            SMC_STEP(true, false);
     } else {
-        if (timed)
-            hipExtLaunchKernelGGL((gmm_step_kernel<K, false>), grid, blk, 0, c.stream, e0, e1, 0,
-                                  SMC_STEP_ARGS);
+        if (sp.lsl > 0)
+            SMC_STEP(false, true);
         else
-            hipLaunchKernelGGL((gmm_step_kernel<K, false>), grid, blk, 0, c.stream,
-                               SMC_STEP_ARGS);
+            SMC_STEP(false, false);
     }
+#undef SMC_STEP
 #undef SMC_STEP_ARGS
     return hipGetLastError();
 }
@@ -984,26 +1152,46 @@ hipError_t GmmK<K>::loglik(const double *mu, const double *eta, const double *z,
                                   const double *y, int64_t nd, double *ll, double *grad,
                                   hipStream_t s)
 {
-    const int W = gmm_waves(n, nd);
-    const dim3 grid((unsigned)ceil_div(n, WAVE)), blk((unsigned)(W * WAVE));
-    if (grad)
-        hipLaunchKernelGGL((gmm_loglik_kernel<K, true>), grid, blk, 0, s, mu, eta, z, n, y, nd,
-                           W, ll, grad);
-    else
-        hipLaunchKernelGGL((gmm_loglik_kernel<K, false>), grid, blk, 0, s, mu, eta, z, n, y, nd,
-                           W, ll, grad);
+    const GmmSplit sp = gmm_split(n, nd, GMM_SETUP_LOGLIK);
+    const dim3 grid((unsigned)ceil_div(n, WAVE >> sp.lsl)), blk((unsigned)(sp.W * WAVE));
+#define SMC_LOGLIK(GRAD, SLICED)                                                                  \
+    hipLaunchKernelGGL((gmm_loglik_kernel<K, GRAD, SLICED>), grid, blk, 0, s, mu, eta, z, n, y,   \
+                       nd, sp.W, sp.lsl, ll, grad)
+    if (grad) {
+        if (sp.lsl > 0)
+            SMC_LOGLIK(true, true);
+        else
+            SMC_LOGLIK(true, false);
+    } else {
+        if (sp.lsl > 0)
+            SMC_LOGLIK(false, true);
+        else
+            SMC_LOGLIK(false, false);
+    }
+#undef SMC_LOGLIK
     return hipGetLastError();
 }
 
 template <int K>
-hipError_t GmmK<K>::init_batch(const Prob *probs, const int2 *map, int64_t tiles, int W,
+hipError_t GmmK<K>::init_batch(const Prob *probs, const int2 *map, int64_t tiles, GmmSplit sp,
                                       bool mala, hipStream_t s)
 {
-    const dim3 grid((unsigned)tiles), blk((unsigned)(W * WAVE));
-    if (mala)
-        hipLaunchKernelGGL((gmm_init_batch_kernel<K, true>), grid, blk, 0, s, probs, map, W);
-    else
-        hipLaunchKernelGGL((gmm_init_batch_kernel<K, false>), grid, blk, 0, s, probs, map, W);
+    const dim3 grid((unsigned)(tiles << sp.lsl)), blk((unsigned)(sp.W * WAVE));
+#define SMC_INIT(GRAD, SLICED)                                                                    \
+    hipLaunchKernelGGL((gmm_init_batch_kernel<K, GRAD, SLICED>), grid, blk, 0, s, probs, map,     \
+                       sp.W, sp.lsl)
+    if (mala) {
+        if (sp.lsl > 0)
+            SMC_INIT(true, true);
+        else
+            SMC_INIT(true, false);
+    } else {
+        if (sp.lsl > 0)
+            SMC_INIT(false, true);
+        else
+            SMC_INIT(false, false);
+    }
+#undef SMC_INIT
     return hipGetLastError();
 }
 

@@ -99,9 +99,9 @@ __device__ __attribute__((noinline)) void gmm_item(const Prob &P, int64_t tile0,
             for (int b = 0; b < nb; ++b) {
                 const bool first = sw == 0 && b == 0;
                 __syncthreads();  // LDS and the rows the previous block wrote
-                gmm_block_tile<K, MALA>(P, first ? prev : cur, cur, first ? 1 : 0, NWAVES,
-                                        tile0 + q, (uint32_t)t, b, sw, a, sch[1 + b], t, red,
-                                        stash);
+                gmm_block_tile<K, MALA, false>(P, first ? prev : cur, cur, first ? 1 : 0, NWAVES,
+                                               0, tile0 + q, (uint32_t)t, b, sw, a, sch[1 + b],
+                                               t, red, stash);
             }
     }
 }
