@@ -247,9 +247,10 @@ smc_status smc_resample(smc_ctx *ctx, int32_t step, int32_t force);
  * takes another order).  For a filter of at most 1024 particles (one tile)
  * with systematic or stratified resampling and no monitor pending from an
  * earlier move, the three are one launch of a single workgroup (a small
- * filter is bound by latency, not by work); otherwise it makes the three
- * calls.  The one-launch form carries no timing events
- * (smc_profile_start). */
+ * filter is bound by latency, not by work); with systematic resampling of up
+ * to 262144 particles the normalisation and the resampling are one launch;
+ * otherwise it makes the three calls.  The one-launch form carries no timing
+ * events (smc_profile_start). */
 smc_status smc_step(smc_ctx *ctx, int32_t step, const smc_move_args *args, int32_t force);
 
 /* Importance-sampling estimate (Section 2.1 estimator 3; Section 4.1

@@ -603,6 +603,14 @@ smc_status smc_step(smc_ctx *ctx, int32_t step, const smc_move_args *args, int32
                             c.mon_pending_step < 0;
     if (!one_launch) {
         smc_status s = smc_move(ctx, step, args);
+        if (s == SMC_OK && c.cfg.scheme == SMC_RS_SYSTEMATIC && c.ntiles <= NR_MAX_TILES) {
+            // the move left new weights and nothing pending: the checks of
+            // the two calls hold
+            const hipError_t e = launch_normalise_resample(c, step, force);
+            if (e == hipSuccess)
+                c.normalised = c.armed_lw = c.armed_gather = true;
+            return hip_status(c, e, "smc_step");
+        }
         if (s == SMC_OK)
             s = smc_ess(ctx, step, nullptr);
         if (s == SMC_OK)

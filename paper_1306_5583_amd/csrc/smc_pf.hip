@@ -87,13 +87,44 @@ __global__ __launch_bounds__(TPB) void pf_move_kernel(Prob P, uint32_t t, int32_
                                reset_check != 0);
 }
 
+// One particle a lane (pf_move_wide), for populations of at most
+// MOVE_WIDE_TILES tiles; writes the same partials.
+template <typename T, bool MON>
+__global__ __launch_bounds__(TILE) void pf_move_wide_kernel(Prob P, uint32_t t, int32_t obs_index,
+                                                            int gather_check, int reset_check)
+{
+    __shared__ WideLds<MON> L;
+    const int64_t tile = blockIdx.x;
+    const double m = pf_move_wide<T, MON>(P, (const T *)P.state[0], (T *)P.state[1], tile, t,
+                                          P.data + 2 * (int64_t)obs_index, gather_check != 0,
+                                          reset_check != 0, L);
+    if (threadIdx.x == 0)
+        P.partials[tile] = TilePartial{m, L.total(0), L.total(1), 0.0};
+    if (MON && threadIdx.x < 5)
+        P.mon[(int64_t)threadIdx.x * P.ntiles + tile] = L.total(MON ? 2 + threadIdx.x : 0);
+}
+
 template <typename T, bool FUSE, bool MON>
 static void launch_move_t(Ctx &c, int32_t step, int32_t obs_index, bool gather_check,
                           bool reset_check)
 {
     const Prob P = make_prob(c);
     hipEvent_t e0, e1;
-    if (c.prof_take(&e0, &e1))
+    const bool timed = c.prof_take(&e0, &e1);
+    if constexpr (FUSE) {
+        if (c.ntiles <= MOVE_WIDE_TILES) {
+            if (timed)
+                hipExtLaunchKernelGGL((pf_move_wide_kernel<T, MON>), dim3((unsigned)c.ntiles),
+                                      dim3(TILE), 0, c.stream, e0, e1, 0, P, (uint32_t)step,
+                                      obs_index, (int)gather_check, (int)reset_check);
+            else
+                hipLaunchKernelGGL((pf_move_wide_kernel<T, MON>), dim3((unsigned)c.ntiles),
+                                   dim3(TILE), 0, c.stream, P, (uint32_t)step, obs_index,
+                                   (int)gather_check, (int)reset_check);
+            return;
+        }
+    }
+    if (timed)
         hipExtLaunchKernelGGL((pf_move_kernel<T, FUSE, MON>), dim3((unsigned)c.ntiles), dim3(TPB),
                               0, c.stream, e0, e1, 0, P, (uint32_t)step, obs_index,
                               (int)gather_check, (int)reset_check);

@@ -283,6 +283,75 @@ __device__ __forceinline__ void normalise_one_pass(const TilePartial *__restrict
     *S2_out = S2;
 }
 
+// L, L2, ESS and the resampling decision from the totals.
+struct Normalised {
+    double L, L2, ess;
+    int flag;
+    bool bad;  // the total is not a positive finite number
+};
+
+__device__ __forceinline__ Normalised normalise_from_logs(const Prob &P, double M, double S1,
+                                                          double log1, double log2)
+{
+    Normalised r;
+    const double threshold = P.threshold;
+    r.L = M + log1;
+    r.L2 = 2.0 * M + log2;
+    r.ess = exp(2.0 * r.L - r.L2);
+    if (threshold >= 1.0)
+        r.flag = 1;
+    else if (threshold <= 0.0)
+        r.flag = 0;
+    else
+        r.flag = r.ess < threshold * (double)P.n;
+    r.bad = !(S1 > 0.0) || !isfinite(S1) || !isfinite(M);
+    if (r.bad)
+        r.flag = 0;
+    return r;
+}
+
+__device__ __forceinline__ Normalised normalise_scalars(const Prob &P, double M, double S1,
+                                                        double S2)
+{
+    return normalise_from_logs(P, M, S1, log(S1), log(S2));
+}
+
+// The same by one whole wave, the two logarithms in two of its lanes.
+__device__ __forceinline__ Normalised normalise_scalars_wave(const Prob &P, double M, double S1,
+                                                             double S2)
+{
+    const double lg = log(lane_id() == 0 ? S1 : S2);
+    return normalise_from_logs(P, M, S1, dpp::readlane(lg, 0), dpp::readlane(lg, 1));
+}
+
+// One lane: scalars, error word and history row of a normalisation.
+__device__ __forceinline__ void write_normalisation(const Prob &P, int32_t step,
+                                                    const Normalised &r, double M, double S1,
+                                                    double Lprev, double logz_prev)
+{
+    double *__restrict__ scalars = P.scalars;
+    const double dlogz = r.L - Lprev;
+    const double logz = logz_prev + dlogz;
+    if (r.bad)
+        atomicOr(&P.counters[CNT_ERR], SMC_DEVERR_NONFINITE);
+    scalars[SMC_S_L] = r.L;
+    scalars[SMC_S_L2] = r.L2;
+    scalars[SMC_S_ESS] = r.ess;
+    scalars[SMC_S_DLOGZ] = dlogz;
+    scalars[SMC_S_LOGZ] = logz;
+    scalars[SMC_S_FLAG] = (double)r.flag;
+    scalars[SMC_S_M] = M;
+    scalars[SMC_S_STOT] = S1;
+    if (P.hist && step >= 0 && step < P.hist_len) {
+        double *h = P.hist + (int64_t)step * SMC_HIST_COLS;
+        h[SMC_H_ESS] = r.ess;
+        h[SMC_H_FLAG] = (double)r.flag;
+        h[SMC_H_DLOGZ] = dlogz;
+        h[SMC_H_LOGZ] = logz;
+        h[SMC_H_L] = r.L;
+    }
+}
+
 // Normalisation (one workgroup): global max M, tile offsets of the
 // cumulative weights, S1 = sum exp(lw - M), S2 = sum exp(2 (lw - M)),
 // L = M + log S1, L2 = 2M + log S2, ESS = exp(2L - L2), dlogZ = L - L_prev,
@@ -330,41 +399,8 @@ __device__ __forceinline__ void normalise_block(const Prob &P, int32_t step)
             prefix, red);
         S2 = block_sum<(NT / WAVE)>(s2, red);
     }
-    if (tid == 0) {
-        const double threshold = P.threshold;
-        const double L = M + log(S1);
-        const double L2 = 2.0 * M + log(S2);
-        const double ess = exp(2.0 * L - L2);
-        const double dlogz = L - Lprev;
-        const double logz = logz_prev + dlogz;
-        int flag;
-        if (threshold >= 1.0)
-            flag = 1;
-        else if (threshold <= 0.0)
-            flag = 0;
-        else
-            flag = ess < threshold * (double)n;
-        if (!(S1 > 0.0) || !isfinite(S1) || !isfinite(M)) {
-            atomicOr(&P.counters[CNT_ERR], SMC_DEVERR_NONFINITE);
-            flag = 0;
-        }
-        scalars[SMC_S_L] = L;
-        scalars[SMC_S_L2] = L2;
-        scalars[SMC_S_ESS] = ess;
-        scalars[SMC_S_DLOGZ] = dlogz;
-        scalars[SMC_S_LOGZ] = logz;
-        scalars[SMC_S_FLAG] = (double)flag;
-        scalars[SMC_S_M] = M;
-        scalars[SMC_S_STOT] = S1;
-        if (P.hist && step >= 0 && step < P.hist_len) {
-            double *h = P.hist + (int64_t)step * SMC_HIST_COLS;
-            h[SMC_H_ESS] = ess;
-            h[SMC_H_FLAG] = (double)flag;
-            h[SMC_H_DLOGZ] = dlogz;
-            h[SMC_H_LOGZ] = logz;
-            h[SMC_H_L] = L;
-        }
-    }
+    if (tid == 0)
+        write_normalisation(P, step, normalise_scalars(P, M, S1, S2), M, S1, Lprev, logz_prev);
 }
 
 // Completion of monitor partials carried by a move (importance-sampling
@@ -681,13 +717,18 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
 // range marks the range's first slot with its index and an inclusive
 // max-scan spreads it over the range, which keeps the stores coalesced and
 // the work even however the slots fall on the particles.
-__device__ __forceinline__ void resample_sys_tile(const Prob &P, int64_t b, uint32_t t,
-                                                  int32_t force)
+struct TileWeights {
+    double flag, M, stot;  // decision, global maximum, total
+    double Pb, Pb1, mb;    // the tile's cumulative offsets and maximum
+    double L;              // the normalisation's L (block 0)
+};
+
+__device__ __forceinline__ void resample_sys_fill(const Prob &P, int64_t b, uint32_t t,
+                                                  int32_t force, const TileWeights &tw,
+                                                  const double (&l)[ITEMS])
 {
     constexpr int QPT = RS_UCAP / TPB;  // chunk slots per lane
-    const double *__restrict__ lw = P.lw;
-    const double *__restrict__ prefix = P.prefix;
-    const int64_t n = P.n, ntiles = P.ntiles;
+    const int64_t n = P.n;
     double *__restrict__ scalars = P.scalars;
     int32_t *__restrict__ anc = P.anc;
     __shared__ double red[NWAVES];
@@ -700,17 +741,7 @@ __device__ __forceinline__ void resample_sys_tile(const Prob &P, int64_t b, uint
     __shared__ double sh_U;
     const int tid = threadIdx.x;
     const int64_t base = b * TILE;
-    const int len = (int)min((int64_t)TILE, n - base);
-    // every load of the tile in one round trip: the decision, the
-    // normalisation and the log-weights (the last read in vain on steps that
-    // do not resample)
-    const double flag = scalars[SMC_S_FLAG];
-    const double M = scalars[SMC_S_M];
-    const double stot = prefix[ntiles];
-    const double Pb = prefix[b], Pb1 = prefix[b + 1];
-    const double mb = P.partials[b].m;
-    double l[ITEMS];
-    tile_load_lw(lw, base, len, l);
+    const double flag = tw.flag, M = tw.M, stot = tw.stot, Pb = tw.Pb, Pb1 = tw.Pb1, mb = tw.mb;
     const bool go = force != 0 || flag != 0.0;
     if (!go) {
         if (b == 0 && tid == 0)
@@ -802,9 +833,127 @@ __device__ __forceinline__ void resample_sys_tile(const Prob &P, int64_t b, uint
     }
     if (b == 0 && tid == 0) {
         scalars[SMC_S_RESAMPLED] = 1.0;
-        scalars[SMC_S_LPRE] = scalars[SMC_S_L];
+        scalars[SMC_S_LPRE] = tw.L;
         scalars[SMC_S_L] = log(nd);
         scalars[SMC_S_U] = U;
+    }
+}
+
+__device__ __forceinline__ void resample_sys_tile(const Prob &P, int64_t b, uint32_t t,
+                                                  int32_t force)
+{
+    const int64_t base = b * TILE;
+    // every load of the tile in one round trip: the decision, the
+    // normalisation and the log-weights (the last read in vain on steps that
+    // do not resample)
+    const TileWeights tw{P.scalars[SMC_S_FLAG], P.scalars[SMC_S_M], P.prefix[P.ntiles],
+                         P.prefix[b], P.prefix[b + 1], P.partials[b].m, P.scalars[SMC_S_L]};
+    double l[ITEMS];
+    tile_load_lw(P.lw, base, (int)min((int64_t)TILE, P.n - base), l);
+    resample_sys_fill(P, b, t, force, tw, l);
+}
+
+// ---------------------------------------------------------------------------
+// Normalisation and systematic resampling in one launch, for at most TPB
+// tiles: every workgroup normalises for itself (one tile partial a lane; the
+// same sums in the same order as normalise_block, whose lanes own eight
+// consecutive tiles and whose waves add their squares tile by tile) and then
+// resamples its tile; workgroup 0 writes the scalars and the history row.
+// What it saves is a dependent launch of one workgroup: at 70001 particles
+// the two took 4.2 + 4.8 us and the gap between them.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void normalise_resample_tile(const Prob &P, int32_t step, int64_t b,
+                                                        int32_t force)
+{
+    __shared__ double red[NWAVES], red2[NWAVES];
+    __shared__ double wl[TPB];
+    __shared__ Normalised nsh;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int ntiles = (int)P.ntiles;
+    const int64_t base = b * TILE;
+    double qm = -INFINITY, q1 = 0.0, q2 = 0.0;
+    if (tid < ntiles) {
+        qm = P.partials[tid].m;
+        q1 = P.partials[tid].s1;
+        q2 = P.partials[tid].s2;
+    }
+    double l[ITEMS];
+    tile_load_lw(P.lw, base, (int)min((int64_t)TILE, P.n - base), l);
+    double Lprev = 0.0, logz_prev = 0.0;
+    if (b == 0 && tid == 0) {
+        Lprev = P.scalars[SMC_S_L];
+        logz_prev = P.scalars[SMC_S_LOGZ];
+    }
+    const double M = block_max<NWAVES>(qm, red);
+    const double sc = qm > -INFINITY ? exp_nonpos_d(qm - M) : 0.0;
+    wl[tid] = q1 * sc;
+    const double s2w = wave_sum(fma(q2, sc * sc, 0.0));  // rounded before the first addition
+    if (lane == 0)
+        red2[wave_id()] = s2w;
+    __syncthreads();
+    // lane t owns tiles 8t .. 8t + 7 (every wave for itself)
+    double e[FIN_IT];
+    double run = 0.0;
+#pragma unroll
+    for (int k = 0; k < FIN_IT; ++k) {
+        e[k] = run;
+        run += lane < TPB / FIN_IT ? wl[lane * FIN_IT + k] : 0.0;
+    }
+    const double hi = wave_incl_scan(run);
+    const double lo = lane_prev(hi, 0.0);
+    const double S1 = dpp::readlane(hi, WAVE - 1);
+    const double S2 = ((red2[0] + red2[1]) + red2[2]) + red2[3];
+    auto offset = [&](int tile) {
+        const int k = tile % FIN_IT;
+        double ek = e[0];
+#pragma unroll
+        for (int h = 1; h < FIN_IT; ++h)
+            ek = k == h ? e[h] : ek;
+        return dpp::readlane(fmin(lo + ek, hi), tile / FIN_IT);
+    };
+    TileWeights tw;
+    tw.M = M;
+    tw.stot = S1;
+    tw.Pb = offset((int)b);
+    tw.Pb1 = b + 1 == ntiles ? S1 : offset((int)b + 1);
+    tw.mb = P.partials[b].m;
+    if (wave_id() == 0) {
+        const Normalised r = normalise_scalars_wave(P, M, S1, S2);
+        if (tid == 0) {
+            nsh = r;
+            if (b == 0)
+                write_normalisation(P, step, r, M, S1, Lprev, logz_prev);
+            P.prefix[b] = tw.Pb;
+            if (b + 1 == ntiles)
+                P.prefix[ntiles] = S1;
+        }
+    }
+    __syncthreads();
+    tw.flag = (double)nsh.flag;
+    tw.L = nsh.L;
+    resample_sys_fill(P, b, (uint32_t)step, force, tw, l);
+}
+
+// The almost-constant-velocity transition of particle i at step t.
+template <typename T>
+__device__ __forceinline__ void cv_transition(Key key, uint32_t i, uint32_t t, uint32_t p,
+                                              const Motion &mv, T px, T py, T vx, T vy, T *npx,
+                                              T *npy, T *nvx, T *nvy)
+{
+    if constexpr (sizeof(T) == 8) {
+        const double2 a = normal2(draw(key, i, t, TAG_PF_MOVE, 0, p));
+        const double2 b = normal2(draw(key, i, t, TAG_PF_MOVE, 1, p));
+        *npx = (px + mv.dt * vx) + mv.sd_pos * a.x;
+        *npy = (py + mv.dt * vy) + mv.sd_pos * a.y;
+        *nvx = vx + mv.sd_vel * b.x;
+        *nvy = vy + mv.sd_vel * b.y;
+    } else {
+        const float4 z = normal4f(draw(key, i, t, TAG_PF_MOVE, 0, p));
+        const float dt = (float)mv.dt, sp = (float)mv.sd_pos, sv = (float)mv.sd_vel;
+        *npx = (px + dt * vx) + sp * z.x;
+        *npy = (py + dt * vy) + sp * z.y;
+        *nvx = vx + sv * z.z;
+        *nvy = vy + sv * z.w;
     }
 }
 
@@ -862,21 +1011,7 @@ __device__ __forceinline__ void pf_move_tile(const Prob &P, const T *__restrict_
             }
         }
         T npx, npy, nvx, nvy;
-        if constexpr (sizeof(T) == 8) {
-            const double2 a = normal2(draw(key, (uint32_t)i, t, TAG_PF_MOVE, 0, p));
-            const double2 b = normal2(draw(key, (uint32_t)i, t, TAG_PF_MOVE, 1, p));
-            npx = (px + mv.dt * vx) + mv.sd_pos * a.x;
-            npy = (py + mv.dt * vy) + mv.sd_pos * a.y;
-            nvx = vx + mv.sd_vel * b.x;
-            nvy = vy + mv.sd_vel * b.y;
-        } else {
-            const float4 z = normal4f(draw(key, (uint32_t)i, t, TAG_PF_MOVE, 0, p));
-            const float dt = (float)mv.dt, sp = (float)mv.sd_pos, sv = (float)mv.sd_vel;
-            npx = (px + dt * vx) + sp * z.x;
-            npy = (py + dt * vy) + sp * z.y;
-            nvx = vx + sv * z.z;
-            nvy = vy + sv * z.w;
-        }
+        cv_transition(key, (uint32_t)i, t, p, mv, px, py, vx, vy, &npx, &npy, &nvx, &nvy);
         xout[i] = npx;
         xout[n + i] = npy;
         xout[2 * n + i] = nvx;
@@ -899,6 +1034,106 @@ __device__ __forceinline__ void pf_move_tile(const Prob &P, const T *__restrict_
                 P.mon[(int64_t)r * P.ntiles + tile] = ms[r];
         }
     }
+}
+
+// The same fused move + weight by a workgroup of TILE lanes, one particle a
+// lane, for populations of too few tiles to fill the chip (the 256-lane form
+// leaves each SIMD one wave that runs four particles' chains one after the
+// other).  The sums are taken from LDS in the 256-lane form's order -- lane t
+// of four waves adds particles t, t + 256, .. and the waves' sums are added in
+// wave order -- one (row, wave) pair to a wave, so both forms give the same
+// bits.  70001 particles: 11.8 us a launch in the 256-lane form.  Returns the tile's maximum; L.sum holds s1, s2 and, with MON, the
+// monitor's five sums by wave, complete after the last barrier.
+constexpr int WIDE_WAVES = TILE / WAVE;
+
+template <bool MON>
+struct WideLds {
+    double e[TILE];                 // exp(lw - m)
+    double x[MON ? 5 : 1][TILE];    // monitor: w and the four state rows
+    double red[WIDE_WAVES];
+    double sum[7][NWAVES];
+    __device__ double total(int r) const { return ((sum[r][0] + sum[r][1]) + sum[r][2]) + sum[r][3]; }
+};
+
+template <typename T, bool MON>
+__device__ __forceinline__ double pf_move_wide(const Prob &P, const T *__restrict__ xin,
+                                               T *__restrict__ xout, int64_t tile, uint32_t t,
+                                               const double *__restrict__ y, bool gather_check,
+                                               bool reset_check, WideLds<MON> &L)
+{
+    const int64_t n = P.n;
+    const int tid = threadIdx.x;
+    const int64_t i = tile * TILE + tid;
+    const bool resampled =
+        (gather_check || reset_check) ? P.scalars[SMC_S_RESAMPLED] != 0.0 : false;
+    const bool reset = reset_check && resampled;
+    const double M = MON ? P.scalars[SMC_S_M] : 0.0;
+    const double yx = y[0], yy = y[1];
+    double l = -INFINITY;
+    double w = 0.0;
+    T px = 0, py = 0, vx = 0, vy = 0;
+    if (i < n) {
+        const int64_t src = gather_check && resampled ? (int64_t)P.anc[i] : i;
+        px = xin[src], py = xin[n + src], vx = xin[2 * n + src], vy = xin[3 * n + src];
+        const double lw_in = reset ? 0.0 : P.lw[i];
+        if (MON)
+            w = reset ? 1.0 : exp_nonpos_d(lw_in - M);
+        T npx, npy, nvx, nvy;
+        cv_transition(P.key, (uint32_t)i, t, P.problem_id, P.mv, px, py, vx, vy, &npx, &npy,
+                      &nvx, &nvy);
+        xout[i] = npx;
+        xout[n + i] = npy;
+        xout[2 * n + i] = nvx;
+        xout[3 * n + i] = nvy;
+        // the product is rounded before the subtraction, as in the 256-lane
+        // form (whose two branches meet there)
+        double off = P.obs.term((double)npx, yx, (double)npy, yy);
+        asm("" : "+v"(off));
+        l = lw_in + ((P.obs.c + P.obs.c) - off);
+        P.lw[i] = l;
+    }
+    if (MON) {
+        L.x[0][tid] = w;
+        L.x[MON ? 1 : 0][tid] = (double)px;
+        L.x[MON ? 2 : 0][tid] = (double)py;
+        L.x[MON ? 3 : 0][tid] = (double)vx;
+        L.x[MON ? 4 : 0][tid] = (double)vy;
+    }
+    const double mw = wave_max(l);
+    if (lane_id() == 0)
+        L.red[wave_id()] = mw;
+    __syncthreads();
+    double m = L.red[0];
+#pragma unroll
+    for (int v = 1; v < WIDE_WAVES; ++v)
+        m = fmax(m, L.red[v]);
+    L.e[tid] = m > -INFINITY ? exp_nonpos_d(l - m) : 0.0;
+    __syncthreads();
+    constexpr int TASKS = (MON ? 7 : 2) * NWAVES;
+    for (int q = wave_id(); q < TASKS; q += WIDE_WAVES) {
+        const int r = q / NWAVES, v = q % NWAVES;
+        const int tt = v * WAVE + lane_id();
+        double a = 0.0;
+        if (r == 0) {
+            a = ((L.e[tt] + L.e[TPB + tt]) + L.e[2 * TPB + tt]) + L.e[3 * TPB + tt];
+        } else if (r == 1) {  // (the first two squares fused as the compiler fuses them there)
+            const double e1 = L.e[TPB + tt], e2 = L.e[2 * TPB + tt], e3 = L.e[3 * TPB + tt];
+            a = fma(e3, e3, fma(e2, e2, fma(L.e[tt], L.e[tt], e1 * e1)));
+        } else {
+#pragma unroll
+            for (int k = 0; k < ITEMS; ++k) {
+                const int j = k * TPB + tt;
+                const double wj = L.x[0][j];
+                if (wj != 0.0)
+                    a = r == 2 ? a + wj : fma(wj, L.x[MON ? r - 2 : 0][j], a);
+            }
+        }
+        a = wave_sum(a);
+        if (lane_id() == 0)
+            L.sum[r][v] = a;
+    }
+    __syncthreads();
+    return m;
 }
 
 // ---------------------------------------------------------------------------

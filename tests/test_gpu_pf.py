@@ -311,6 +311,34 @@ def test_unfused_reweight_matches_fused(lib):
     assert torch.equal(a.state(), b.state()) and torch.equal(a.log_weight, b.log_weight)
 
 
+@pytest.mark.parametrize("n", [1025, 2049, 70001, 262143, 262145, 524289])
+@pytest.mark.parametrize("fp32,threshold", [(False, 0.5), (True, 1.0), (False, 0.0)])
+def test_step_matches_three_calls_over_tiles(lib, n, fp32, threshold):
+    # smc_step at the edges of its forms (normalisation and resampling in one
+    # launch and one particle a lane, both up to 256 tiles) against smc_move,
+    # smc_ess and smc_resample, bit for bit
+    pkg, L = lib
+    _, y = synth.pf_trajectory(6, 5)
+    a = pkg.ParticleFilter(n, y, seed=3, fp32_state=fp32, threshold=threshold)
+    b = pkg.ParticleFilter(n, y, seed=3, fp32_state=fp32, threshold=threshold)
+    a.run()
+    b.init()
+    for t in range(1, b.T):
+        m = b._margs
+        m.obs_index, m.monitor_step = t, t - 1
+        L.smc_move(b.ctx, t, m)
+        L.smc_ess(b.ctx, t)
+        L.smc_resample(b.ctx, t)
+    b._mon_pending = b.T - 1
+    b.finish()
+    assert np.array_equal(a.history_host(), b.history_host())
+    assert a.scalars_host() == b.scalars_host()
+    assert torch.equal(a.state(), b.state())
+    assert torch.equal(a.log_weight, b.log_weight)
+    assert torch.equal(a.ancestors, b.ancestors)
+    a.check()
+
+
 @pytest.mark.parametrize("fp32,threshold", [(False, 0.5), (True, 0.5), (False, 0.0)])
 def test_fused_monitor_matches_standalone(lib, fp32, threshold):
     pkg, L = lib
