@@ -417,7 +417,9 @@ smc_status smc_batch_table_size(const smc_batch_problem *probs, int32_t nprob, s
  * mixture samplers' reweight / normalise / resample items, their Metropolis
  * tiles with the most expensive problems first, then the tracking filters'
  * items; order 1 = phase by phase in problem order.  per_item (1 or 2)
- * 64-particle tiles make one Metropolis item.  items receives *count rows of
+ * Metropolis tiles make one Metropolis item; a tile has 64 particles, or 32,
+ * 16 .. of a sampler whose tiles would be too few and too long for the batch.
+ * items receives *count rows of
  * four int32 {kind (0 move, 1 reweight, 2 normalise, 3 resample, 4
  * Metropolis, 5 monitor), problem, tile, tiles in the item (monitor: the
  * problem's Metropolis items)}; with capacity 0 only
@@ -442,7 +444,7 @@ smc_status smc_batch_create(const smc_batch_problem *probs, int32_t nprob, void 
 /* Releases the host object and its captured graph (not the caller's memory). */
 smc_status smc_batch_destroy(smc_batch *b);
 /* Autotuner of the step: for every candidate schedule -- queue order (0, 1),
- * 64-particle tiles per Metropolis item (1, 2), step workgroups per compute
+ * Metropolis tiles per Metropolis item (1, 2), step workgroups per compute
  * unit (1 .. the occupancy limit) -- initialises the batch and times
  * `repeats` steps after a warm-up step (median kept), then keeps the
  * fastest.  With a non-NULL cache_path, a line "<arch> <shape buckets> |
@@ -482,7 +484,7 @@ smc_status smc_batch_init(smc_batch *b);
  * SMC_ERR_UNSUPPORTED past the step that the 32-bit ticket and completion
  * counters can index: step t needs t * (work items + workgroups of the
  * step) < 2^32 and t * (tiles of the largest problem: 1024-particle tiles
- * of a filter, 64-particle tiles of a mixture sampler) < 2^32. */
+ * of a filter, Metropolis tiles of a mixture sampler) < 2^32. */
 smc_status smc_batch_step(smc_batch *b);
 /* Captures one step into a HIP graph (replaces a previous capture); the
  * step index comes from the device, so one capture serves every step. */

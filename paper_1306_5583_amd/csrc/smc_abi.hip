@@ -156,6 +156,7 @@ Prob prob_from(const smc_config &cfg, const smc_buffers &buf, const Workspace &w
     P.mon = reinterpret_cast<double *>(w + ws.mon);
     P.counters = reinterpret_cast<int32_t *>(w + ws.counters);
     P.sched = nullptr;
+    P.lsl = 0;
     return P;
 }
 

@@ -75,10 +75,35 @@ struct Plan {
 
 size_t al(size_t v) { return (v + 255) & ~size_t(255); }
 
+// What the queue needs to know of each problem: its tiles and the relative
+// cost of one Metropolis tile (data points x components, MALA's gradient
+// and the sweeps).
+std::vector<QProblem> queue_problems(const smc_batch_problem *probs, int32_t np)
+{
+    std::vector<QProblem> q;
+    std::vector<int64_t> n, nd;
+    for (int32_t i = 0; i < np; ++i) {
+        const smc_config &c = probs[i].cfg;
+        QProblem r;
+        r.gmm = c.model == SMC_MODEL_GMM_TEMPERED;
+        r.tiles = ceil_div(c.n, TILE);
+        r.mtiles = r.gmm ? ceil_div(c.n, WAVE) : 0;
+        r.cost = r.gmm ? (double)c.n_data * c.K * (c.move_kind == SMC_MOVE_MALA ? 1.4 : 1.0) *
+                             (c.sweeps > 0 ? c.sweeps : 1)
+                       : 0.0;
+        q.push_back(r);
+        n.push_back(c.n);
+        nd.push_back(c.n_data);
+    }
+    split_tiles(q, n, nd);
+    return q;
+}
+
 Plan plan(const smc_batch_problem *probs, int32_t np)
 {
     Plan pl;
     std::map<std::pair<int, bool>, int64_t> t64;
+    const std::vector<QProblem> qp = queue_problems(probs, np);
     for (int32_t i = 0; i < np; ++i) {
         const smc_config &c = probs[i].cfg;
         const int64_t nt = ceil_div(c.n, TILE);
@@ -88,7 +113,7 @@ Plan plan(const smc_batch_problem *probs, int32_t np)
         } else {
             pl.gmm_tiles += nt;
             t64[{c.K, c.move_kind == SMC_MOVE_MALA}] += ceil_div(c.n, WAVE);
-            pl.queue_cap += 2 * nt + 2 + ceil_div(c.n, WAVE);
+            pl.queue_cap += 2 * nt + 2 + qp[i].mtiles;
         }
     }
     size_t off = 0;
@@ -116,26 +141,6 @@ Plan plan(const smc_batch_problem *probs, int32_t np)
     off = al(off + sizeof(uint32_t) * SYNC_WORDS);
     pl.total = off;
     return pl;
-}
-
-// What the queue needs to know of each problem: its tiles and the relative
-// cost of one Metropolis tile (data points x components, MALA's gradient
-// and the sweeps).
-std::vector<QProblem> queue_problems(const smc_batch_problem *probs, int32_t np)
-{
-    std::vector<QProblem> q;
-    for (int32_t i = 0; i < np; ++i) {
-        const smc_config &c = probs[i].cfg;
-        QProblem r;
-        r.gmm = c.model == SMC_MODEL_GMM_TEMPERED;
-        r.tiles = ceil_div(c.n, TILE);
-        r.tiles64 = r.gmm ? ceil_div(c.n, WAVE) : 0;
-        r.cost = r.gmm ? (double)c.n_data * c.K * (c.move_kind == SMC_MOVE_MALA ? 1.4 : 1.0) *
-                             (c.sweeps > 0 ? c.sweeps : 1)
-                       : 0.0;
-        q.push_back(r);
-    }
-    return q;
 }
 
 smc_status bfail(smc_batch *b, smc_status s, const std::string &m)
@@ -353,13 +358,14 @@ smc_status smc_batch_create(const smc_batch_problem *probs, int32_t nprob, void 
         const Workspace ws = plan_workspace(q.cfg);
         Prob P = prob_from(q.cfg, q.buf, ws, q.buf.state, q.buf.state_alt);
         P.sched = q.schedule;
+        P.lsl = b->qp[i].lsl;
         b->P.push_back(P);
         const int64_t nt = ceil_div(q.cfg.n, TILE);
         // counter targets per step: tiles (move, reweight, resampling), and
-        // for a mixture sampler its 64-particle tiles (Metropolis items)
+        // for a mixture sampler its Metropolis tiles
         b->max_count = std::max(b->max_count, q.cfg.model == SMC_MODEL_CV_TRACK
                                                   ? nt
-                                                  : ceil_div(q.cfg.n, WAVE));
+                                                  : b->qp[i].mtiles);
         for (int64_t t = 0; t < nt; ++t) {
             (q.cfg.model == SMC_MODEL_CV_TRACK ? mpf : mgmm).push_back(make_int2(i, (int)t));
             mall.push_back(make_int2(i, (int)t));

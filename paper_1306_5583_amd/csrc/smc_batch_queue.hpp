@@ -25,17 +25,17 @@ enum : int32_t {
 struct QItem {
     int32_t kind;
     int32_t prob;
-    int32_t tile;   // 1024-particle tile (A, R), 64-particle tile (M); 0 for F
-    int32_t count;  // M: consecutive 64-particle tiles of the item; monitor: the
-                    // problem's 64-particle tiles; 1 otherwise
+    int32_t tile;   // 1024-particle tile (A, R), Metropolis tile (M); 0 for F
+    int32_t count;  // M: consecutive Metropolis tiles of the item; monitor: the
+                    // problem's Metropolis tiles; 1 otherwise
 };
 
 // Per-problem completion counters (uint32 each, DEP_STRIDE per problem):
 // DEP_A counts finished A tiles, DEP_F finished normalisations, DEP_R
-// finished resampling tiles of mixture samplers, DEP_M the 64-particle tiles
+// finished resampling tiles of mixture samplers, DEP_M the Metropolis tiles
 // of their finished Metropolis items (an item adds its tile count, so the
 // targets do not depend on the item size a schedule chooses).  At step t the
-// targets are t * tiles (A, R), t (F) and t * 64-particle tiles (the
+// targets are t * tiles (A, R), t (F) and t * Metropolis tiles (the
 // monitor).
 enum : int { DEP_A = 0, DEP_F = 1, DEP_R = 2, DEP_M = 3, DEP_STRIDE = 4 };
 // Launch-wide words: the ticket counter and the abort flag.
@@ -59,11 +59,42 @@ enum : int32_t {
 struct QProblem {
     bool gmm;
     int64_t tiles;     // 1024-particle tiles
-    int64_t tiles64;   // 64-particle tiles
-    double cost;       // relative cost of one 64-particle Metropolis tile
+    int64_t mtiles;    // Metropolis tiles of 64 >> lsl particles
+    double cost;       // relative cost of one of them
+    int lsl = 0;       // 2^lsl lanes share a particle's data
 };
 
-// One step's items.  `per_item` 64-particle tiles make one Metropolis item.
+// A step ends when its longest chain of items does, so a sampler whose
+// 64-particle tiles each cost more than a workgroup slot gets on average has
+// them split, 2^lsl lanes to a particle, while a lane keeps at least 64
+// points per block (every item repeats the proposals in every lane and
+// publishes its tile).  Twelve filters and four samplers of 1550 to 9430
+// particles: 712 us a step with whole tiles, 431 split like this, 488 with
+// half the cost and 32 points for the line; four filters and two samplers
+// 1404 -> 313.
+inline void split_tiles(std::vector<QProblem> &pr, const std::vector<int64_t> &n,
+                        const std::vector<int64_t> &n_data)
+{
+    constexpr double SLOTS = 512;  // two workgroups a compute unit
+    constexpr int WAVES = 4, MIN_POINTS = 64;
+    double total = 0.0;
+    for (const QProblem &p : pr)
+        if (p.gmm)
+            total += (double)p.mtiles * p.cost;
+    for (size_t i = 0; i < pr.size(); ++i) {
+        QProblem &p = pr[i];
+        if (!p.gmm)
+            continue;
+        const double limit = total / SLOTS, whole = p.cost;
+        while (p.lsl < 6 && p.cost > limit &&
+               n_data[i] >= ((int64_t)WAVES * MIN_POINTS << (p.lsl + 1)))
+            p.cost = whole / (double)(1 << ++p.lsl);
+        const int64_t per = 64 >> p.lsl;
+        p.mtiles = (n[i] + per - 1) / per;
+    }
+}
+
+// One step's items.  `per_item` Metropolis tiles make one Metropolis item.
 inline std::vector<QItem> build_queue(const std::vector<QProblem> &pr, int32_t order,
                                       int per_item)
 {
@@ -88,13 +119,13 @@ inline std::vector<QItem> build_queue(const std::vector<QProblem> &pr, int32_t o
     };
     auto phase_m = [&](const std::vector<int> &ps) {
         for (int p : ps)
-            for (int64_t b = 0; b < pr[p].tiles64; b += per_item)
+            for (int64_t b = 0; b < pr[p].mtiles; b += per_item)
                 q.push_back(QItem{IT_GMM_STEP, p, (int32_t)b,
-                                  (int32_t)std::min<int64_t>(per_item, pr[p].tiles64 - b)});
+                                  (int32_t)std::min<int64_t>(per_item, pr[p].mtiles - b)});
     };
     auto phase_mon = [&](const std::vector<int> &ps) {
         for (int p : ps)
-            q.push_back(QItem{IT_MONITOR, p, 0, (int32_t)pr[p].tiles64});
+            q.push_back(QItem{IT_MONITOR, p, 0, (int32_t)pr[p].mtiles});
     };
     if (order == ORDER_PHASES) {
         std::vector<int> all(np);

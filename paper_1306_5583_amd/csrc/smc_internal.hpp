@@ -116,6 +116,7 @@ struct Prob {
     double *mon;
     int32_t *counters;
     const double *sched;  // batched GMM: [T+1][4] = alpha_t and the three block scales
+    int32_t lsl;          // batched GMM: 2^lsl lanes of a Metropolis tile share a particle
 };
 
 struct Ctx {

@@ -362,7 +362,7 @@ __device__ __forceinline__ void normalise_block(const Prob &P, int32_t step)
     __shared__ double red[2 * (NT / WAVE)];
     __shared__ double wl[fin_lds<NT>()];
     const TilePartial *__restrict__ part = P.partials;
-    const int64_t ntiles = P.ntiles, n = P.n;
+    const int64_t ntiles = P.ntiles;
     double *__restrict__ prefix = P.prefix;
     double *__restrict__ scalars = P.scalars;
     const int tid = threadIdx.x;

@@ -95,6 +95,25 @@ def _full(shapes):
 
 @pytest.mark.parametrize("order", [0, 1])
 @pytest.mark.parametrize("per_item", [1, 2])
+@pytest.mark.parametrize("shapes,lanes", [
+    ([("gmm", 700, 4, 3000)], [8]),              # 47 points a lane at 16
+    ([("gmm", 65, 2, 511), ("pf", 3000, 0, 0)], [1]),
+    ([("gmm", 65, 2, 512), ("gmm", 1, 8, 20000)], [2, 64]),
+    ([("gmm", 1 << 16, 6, 5000), ("gmm", 1000, 2, 900)], [1, 1])])
+def test_small_batches_split_their_metropolis_tiles(L, order, per_item, shapes, lanes):
+    # tiles of 64 / lanes particles: covered once, and the monitor waits for
+    # as many as there are
+    items = L.smc_batch_plan_queue(_problems(L, shapes), order, per_item)
+    gm = [p for p, s in enumerate(shapes) if s[0] == "gmm"]
+    for p, ln in zip(gm, lanes):
+        tiles = math.ceil(shapes[p][1] / (64 // ln))
+        got = [(t, c) for k, q, t, c in items if k == IT_GMM_STEP and q == p]
+        assert sorted(t + j for t, c in got for j in range(c)) == list(range(tiles))
+        assert [c for k, q, _, c in items if k == IT_MONITOR and q == p] == [tiles]
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("per_item", [1, 2])
 @pytest.mark.parametrize("which", ["small", "benchmark"])
 def test_queue_covers_every_tile_once_in_dependency_order(L, order, per_item, which):
     shapes = _shapes_small() if which == "small" else _shapes_batched_benchmark()
