@@ -97,14 +97,19 @@ __device__ __forceinline__ float u24(uint32_t w)
 
 // Box-Muller: two standard normals from the four words of one call,
 // r = sqrt(-2 log u1), angle 2 pi u2 (sin/cos of pi * (2 u2), exact argument).
-__device__ __forceinline__ double2 normal2(uint4 w)
+// (log_u1: the logarithm of the first uniform)
+__device__ __forceinline__ double2 normal2(uint4 w, double log_u1)
 {
-    const double u1 = u53(w.x, w.y);
     const double u2 = u53(w.z, w.w);
-    const double r = sqrt_nonneg_d(-2.0 * log_pos_d(u1));
+    const double r = sqrt_nonneg_d(-2.0 * log_u1);
     double s, c;
     sincospi_d<true>(u2 + u2, &s, &c);  // argument in (0, 2]
     return make_double2(r * c, r * s);
+}
+
+__device__ __forceinline__ double2 normal2(uint4 w)
+{
+    return normal2(w, log_pos_d(u53(w.x, w.y)));
 }
 
 // Single-precision Box-Muller: four normals from one call.

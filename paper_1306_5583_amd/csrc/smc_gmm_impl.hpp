@@ -777,10 +777,10 @@ struct Proposal {
     double logw0[K];
     double fwd;
 
+    // `z`: the particle's normals of the sweep, coordinate q at z[q * zn]
     __device__ __forceinline__ void build(const double *__restrict__ src, int64_t n, int64_t si,
-                                          uint32_t ii, Key key, uint32_t t, uint32_t p, int block,
-                                          int sweep, double alpha, double scale,
-                                          const GmmPrior &pr)
+                                          const double *z, int zn, int block, double alpha,
+                                          double scale, const GmmPrior &pr)
     {
         const int off = block * K;
         const int dim = block == 2 ? K - 1 : K;
@@ -788,7 +788,6 @@ struct Proposal {
         for (int q = 0; q < D; ++q)
             phi[q] = src[(int64_t)q * n + si];
         log_weights<K>(phi, logw0);
-        const uint32_t tag = TAG_MH_MU + (uint32_t)block;
         const double h2 = scale * scale;
         fwd = 0.0;
 #pragma unroll
@@ -797,26 +796,18 @@ struct Proposal {
 #pragma unroll
         for (int q = 0; q < D; ++q) {
             const int mm = q - off;
-            if (mm >= 0 && mm < dim && (mm & 1) == 0) {
-                const double2 z =
-                    normal2(draw(key, ii, t, tag, (uint32_t)(64 * sweep + mm / 2), p));
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (q + h < D && mm + h < dim) {
-                        const double xi = h == 0 ? z.x : z.y;
-                        double dr = 0.0;
-                        if (MALA) {
-                            double g = log_prior_grad<K>(phi, logw0, pr, q + h);
-                            if (alpha != 0.0)
-                                g += alpha * src[(int64_t)(D + 2 + q + h) * n + si];
-                            dr = 0.5 * h2 * g;
-                        }
-                        const double v = phi[q + h] + dr + scale * xi;
-                        prop[q + h] = v;
-                        const double a = v - phi[q + h] - dr;
-                        fwd += a * a;
-                    }
+            if (mm >= 0 && mm < dim) {
+                double dr = 0.0;
+                if (MALA) {
+                    double g = log_prior_grad<K>(phi, logw0, pr, q);
+                    if (alpha != 0.0)
+                        g += alpha * src[(int64_t)(D + 2 + q) * n + si];
+                    dr = 0.5 * h2 * g;
                 }
+                const double v = phi[q] + dr + scale * z[q * zn];
+                prop[q] = v;
+                const double a = v - phi[q] - dr;
+                fwd += a * a;
             }
         }
     }
@@ -824,15 +815,14 @@ struct Proposal {
 
 // Values of the epilogue that do not depend on the likelihood, computed
 // before the data loop by the last wave and kept in LDS (one column per
-// lane) until wave 0 takes the decision: the proposal's log prior, the log of
-// the accept uniform, the proposed block coordinates and, for MALA, the
-// forward proposal term, the prior gradient at the proposal (block
+// lane) until wave 0 takes the decision: the proposal's log prior, the
+// proposed block coordinates and, for MALA, the forward proposal term, the prior gradient at the proposal (block
 // coordinates) and the proposed mixture weights omega'_j (the z-gradient
 // subtracts n omega'_j).
 template <int K, bool MALA>
 struct BlockStash {
-    static constexpr int LPP = 0, LOGU = 1, FWD = 2, PROP = 3, GP = 3 + K, ZC = 3 + 2 * K;
-    static constexpr int ROWS = MALA ? 3 + 3 * K - 1 : 3 + K;
+    static constexpr int LPP = 0, FWD = 1, PROP = 2, GP = 2 + K, ZC = 2 + 2 * K;
+    static constexpr int ROWS = MALA ? 2 + 3 * K - 1 : 2 + K;
 };
 
 // LDS of one Metropolis block: the wave-combine buffer and the stash.
@@ -840,15 +830,58 @@ constexpr int GMM_RED_DOUBLES = GMM_RED_GROUP * GMM_MAXW * WAVE;
 template <int K, bool MALA>
 constexpr int gmm_stash_doubles() { return BlockStash<K, MALA>::ROWS * WAVE; }
 
-// `red` (GMM_RED_DOUBLES), `stash` (gmm_stash_doubles<K, MALA>()) and, for
+// The random numbers of one sweep of a tile's particles: the D normals of the
+// proposals and the logarithms of the blocks' accept uniforms.  None depends
+// on the state, so they are drawn before the blocks, spread over the
+// particle's lanes and the workgroup's waves -- pair or uniform r by lane r
+// mod (W << lsl) -- where every lane of a particle used to draw every pair,
+// one after the other, in each block's chain (about 250 dependent
+// instructions each).  1000 particles of 1000 points, K = 4: 58 -> 51 us a
+// step with its other launches; 16384: 124 -> 121 us.  Row q of `zs`: coordinate q; row D + b: log U of block
+// b; one column a particle (WAVE >> lsl of them).
+template <int K>
+constexpr int gmm_draw_doubles() { return (3 * K - 1 + 3) * WAVE; }
+
+template <int K, bool SLICED>
+__device__ __forceinline__ void sweep_draws(const Prob &P, int W, int lsl, int64_t tile,
+                                            uint32_t t, int sweep, double *zs)
+{
+    constexpr int D = 3 * K - 1, NB = K == 1 ? 2 : 3;
+    constexpr int PK = (K + 1) / 2, PAIRS = 2 * PK + K / 2;  // K / 2 pairs for the K - 1 logits
+    if (!SLICED)
+        lsl = 0;
+    const int lane = lane_id(), col = lane >> lsl, cols = WAVE >> lsl;
+    const int64_t i = tile * cols + col;
+    const uint32_t ii = (uint32_t)(i < P.n ? i : 0);
+    for (int r = (wave_id() << lsl) + (lane & ((1 << lsl) - 1)); r < PAIRS + NB; r += W << lsl) {
+        const bool pair = r < PAIRS;
+        const int b = pair ? min(r / PK, 2) : r - PAIRS;
+        const int m = r - b * PK;
+        const uint4 w =
+            draw(P.key, ii, t, pair ? TAG_MH_MU + (uint32_t)b : TAG_MH_ACCEPT,
+                 (uint32_t)(pair ? 64 * sweep + m : 4 * sweep + b), P.problem_id);
+        const double l = log_pos_d(u53(w.x, w.y));
+        if (pair) {
+            const double2 z = normal2(w, l);
+            const int q = b * K + 2 * m;
+            zs[q * cols + col] = z.x;
+            if (2 * m + 1 < (b == 2 ? K - 1 : K))
+                zs[(q + 1) * cols + col] = z.y;
+        } else {
+            zs[(D + b) * cols + col] = l;
+        }
+    }
+}
+
+// `draws` (the sweep's numbers), `red` (GMM_RED_DOUBLES), `stash` (gmm_stash_doubles<K, MALA>()) and, for
 // the LDS hand-off modes `io`, `hand` (gmm_hand_doubles(K, MALA)) are the
 // caller's LDS.  With GMM_IO_GLOBAL the block reads `src` and writes `dst`
 // (every row when `full`, else the accepted rows in place).
 template <int K, bool MALA, bool SLICED>
 __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__restrict__ src,
                                                double *__restrict__ dst, int full, int W, int lsl,
-                                               int64_t tile, uint32_t t, int block, int sweep,
-                                               double alpha, double scale, int32_t step,
+                                               int64_t tile, int block, double alpha,
+                                               double scale, int32_t step, const double *draws,
                                                double *red, double *stash, int io = GMM_IO_GLOBAL,
                                                double *hand = nullptr)
 {
@@ -860,8 +893,6 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
     const int32_t *__restrict__ anc = P.anc;
     const int64_t n = P.n, nd = P.n_data;
     const double *__restrict__ y = P.data;
-    const Key key = P.key;
-    const uint32_t p = P.problem_id;
     const GmmPrior pr = P.prior;
     double *__restrict__ hist = P.hist;
     const int64_t hist_len = P.hist_len;
@@ -879,21 +910,20 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
     double *__restrict__ ws = out_lds ? hand : dst;
     const int64_t wi = out_lds ? lane : i;
     const int64_t wn = out_lds ? WAVE : n;
-    const uint32_t ii = (uint32_t)(valid ? i : 0);
+    const int zn = SLICED ? WAVE >> lsl : WAVE;
+    const double *zs = draws + (SLICED ? lane >> lsl : lane);
     const int off = block * K;
     const int dim = block == 2 ? K - 1 : K;
     const double h2 = scale * scale;
     MixLik<K, MALA> L;
     {
         Proposal<K, MALA> Q;
-        Q.build(rs, sn, si, ii, key, t, p, block, sweep, alpha, scale, pr);
+        Q.build(rs, sn, si, zs, zn, block, alpha, scale, pr);
         double logw[K];
         log_weights<K>(Q.prop, logw);
         L.setup(Q.prop, logw);
         if (__builtin_amdgcn_readfirstlane(wave_id()) == W - 1) {
             stash[S::LPP * WAVE + lane] = log_prior<K>(Q.prop, logw, pr);
-            const uint4 wa = draw(key, ii, t, TAG_MH_ACCEPT, (uint32_t)(4 * sweep + block), p);
-            stash[S::LOGU * WAVE + lane] = log_d(u53(wa.x, wa.y));
 #pragma unroll
             for (int q = 0; q < D; ++q) {
                 const int mm = q - off;
@@ -952,7 +982,7 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
         }
         logr += (stash[S::FWD * WAVE + lane] - bwd) / (2.0 * h2);
     }
-    const bool acc = valid && lm.lead && stash[S::LOGU * WAVE + lane] <= logr;
+    const bool acc = valid && lm.lead && zs[(D + block) * zn] <= logr;
     if (lm.lead && (valid || out_lds)) {
         if (out_all) {
 #pragma unroll
@@ -1010,18 +1040,22 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : 2) void gmm_s
     __shared__ double red[GMM_RED_DOUBLES];
     __shared__ double stash[gmm_stash_doubles<K, MALA>()];
     __shared__ double hand[gmm_hand_doubles(K, MALA)];
+    __shared__ double zs[gmm_draw_doubles<K>()];
     const int nb = K == 1 ? 2 : 3;
-    for (int sw = 0; sw < sweeps; ++sw)
+    for (int sw = 0; sw < sweeps; ++sw) {
+        if (sw > 0)
+            __syncthreads();
+        sweep_draws<K, SLICED>(P, W, lsl, blockIdx.x, t, sw, zs);
         for (int b = 0; b < nb; ++b) {
             const bool first = sw == 0 && b == 0;
             const bool last = sw == sweeps - 1 && b == nb - 1;
-            if (!first)
-                __syncthreads();
+            __syncthreads();
             gmm_block_tile<K, MALA, SLICED>(
-                P, src, dst, first ? full : 0, W, lsl, blockIdx.x, t, b, sw, alpha,
-                b == 0 ? s0 : (b == 1 ? s1 : s2), step, red, stash,
+                P, src, dst, first ? full : 0, W, lsl, blockIdx.x, b, alpha,
+                b == 0 ? s0 : (b == 1 ? s1 : s2), step, zs, red, stash,
                 first ? GMM_IO_FIRST : (last ? GMM_IO_LAST : GMM_IO_LDS), hand);
         }
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -37,6 +37,7 @@ namespace smc {
 
 constexpr uint64_t WAIT_TICKS = 200000000ull;  // 2 s of the 100 MHz constant clock
 constexpr int GMM_STASH_MAX = gmm_stash_doubles<BATCH_MAX_K, true>();
+constexpr int GMM_ITEM_DOUBLES = GMM_RED_DOUBLES + GMM_STASH_MAX + gmm_draw_doubles<BATCH_MAX_K>();
 
 __device__ __forceinline__ uint32_t load_relaxed(const uint32_t *p)
 {
@@ -88,7 +89,7 @@ __device__ bool wait_at_least(const uint32_t *ctr, uint32_t target, uint32_t *ab
 
 template <int K, bool MALA, bool SLICED>
 __device__ __attribute__((noinline)) void gmm_item(const Prob &P, int64_t tile0, int count, int32_t t,
-                                         double *red, double *stash)
+                                         double *draws, double *red, double *stash)
 {
     const double *sch = P.sched + 4 * (int64_t)t;
     const double a = fmin(fmax(sch[0], 0.0), 1.0);
@@ -96,31 +97,35 @@ __device__ __attribute__((noinline)) void gmm_item(const Prob &P, int64_t tile0,
     const double *prev = (const double *)P.state[(t - 1) & 1];
     const int nb = K == 1 ? 2 : 3;
     for (int q = 0; q < count; ++q) {
-        for (int sw = 0; sw < P.sweeps; ++sw)
+        for (int sw = 0; sw < P.sweeps; ++sw) {
+            __syncthreads();  // the LDS of the previous sweep or tile
+            sweep_draws<K, SLICED>(P, NWAVES, P.lsl, tile0 + q, (uint32_t)t, sw, draws);
             for (int b = 0; b < nb; ++b) {
                 const bool first = sw == 0 && b == 0;
                 __syncthreads();  // LDS and the rows the previous block wrote
                 gmm_block_tile<K, MALA, SLICED>(P, first ? prev : cur, cur, first ? 1 : 0, NWAVES,
-                                               SLICED ? P.lsl : 0, tile0 + q, (uint32_t)t, b, sw, a, sch[1 + b],
-                                               t, red, stash);
+                                                SLICED ? P.lsl : 0, tile0 + q, b, a, sch[1 + b],
+                                                t, draws, red, stash);
             }
+        }
     }
 }
 
 __device__ __forceinline__ void gmm_item_dispatch(const Prob &P, int64_t tile0, int count,
-                                                  int32_t t, double *red, double *stash)
+                                                  int32_t t, double *draws, double *red,
+                                                  double *stash)
 {
     const bool mala = P.move_kind == SMC_MOVE_MALA, sliced = P.lsl > 0;
 #define SMC_GMM_ITEM(k)                                                                           \
     case k:                                                                                       \
         if (mala && sliced)                                                                       \
-            gmm_item<k, true, true>(P, tile0, count, t, red, stash);                              \
+            gmm_item<k, true, true>(P, tile0, count, t, draws, red, stash);                              \
         else if (mala)                                                                            \
-            gmm_item<k, true, false>(P, tile0, count, t, red, stash);                             \
+            gmm_item<k, true, false>(P, tile0, count, t, draws, red, stash);                             \
         else if (sliced)                                                                          \
-            gmm_item<k, false, true>(P, tile0, count, t, red, stash);                             \
+            gmm_item<k, false, true>(P, tile0, count, t, draws, red, stash);                             \
         else                                                                                      \
-            gmm_item<k, false, false>(P, tile0, count, t, red, stash);                            \
+            gmm_item<k, false, false>(P, tile0, count, t, draws, red, stash);                            \
         break;
     switch (P.K) {
         SMC_GMM_ITEM(1)
@@ -205,13 +210,12 @@ __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restri
     __shared__ uint32_t sh_ticket;
     __shared__ int sh_go;
     // one LDS arena for the two largest users, which never run at the same
-    // time: a Metropolis item (wave-combine buffer + stash) and a stratified
+    // time: a Metropolis item (wave-combine buffer, stash and draws) and a stratified
     // resampling tile (cumulative weights + slot uniforms)
-    constexpr int ARENA = GMM_RED_DOUBLES + GMM_STASH_MAX > TILE + RS_UCAP
-                              ? GMM_RED_DOUBLES + GMM_STASH_MAX
-                              : TILE + RS_UCAP;
+    constexpr int ARENA = GMM_ITEM_DOUBLES > TILE + RS_UCAP ? GMM_ITEM_DOUBLES : TILE + RS_UCAP;
     __shared__ double arena[ARENA];
     double *gred = arena, *gstash = arena + GMM_RED_DOUBLES;
+    double *gdraws = gstash + GMM_STASH_MAX;
     const int tid = threadIdx.x;
     // thread 0's record of the last dependency it saw satisfied in this
     // launch (the step does not change within a launch)
@@ -312,7 +316,7 @@ __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restri
             release = P.kind == SMC_MODEL_GMM_TEMPERED ? DEP_R : -1;
             break;
         case IT_GMM_STEP:
-            gmm_item_dispatch(P, it.tile, it.count, t, gred, gstash);
+            gmm_item_dispatch(P, it.tile, it.count, t, gdraws, gred, gstash);
             release = DEP_M;
             units = (uint32_t)it.count;
             break;
