@@ -253,6 +253,14 @@ smc_status smc_resample(smc_ctx *ctx, int32_t step, int32_t force);
  * events (smc_profile_start). */
 smc_status smc_step(smc_ctx *ctx, int32_t step, const smc_move_args *args, int32_t force);
 
+/* The weighting of an iteration in one call: the same as smc_reweight(step,
+ * args), smc_ess(step, NULL) and smc_resample(step, force) in sequence, with
+ * the same results bit for bit (step < 0 is refused before anything is done).
+ * A mixture sampler with systematic resampling takes one launch up to 1024
+ * particles (one tile) and two up to 262144 (weights; normalisation and
+ * resampling); otherwise it makes the three calls. */
+smc_status smc_temper(smc_ctx *ctx, int32_t step, const smc_reweight_args *args, int32_t force);
+
 /* Importance-sampling estimate (Section 2.1 estimator 3; Section 4.1
  * monitors) of every state row under the current normalised weights,
  * written to history row `step` (CV: columns SMC_H_MON..; GMM: column

@@ -642,6 +642,48 @@ smc_status smc_step(smc_ctx *ctx, int32_t step, const smc_move_args *args, int32
     return hip_status(c, e, "smc_step");
 }
 
+smc_status smc_temper(smc_ctx *ctx, int32_t step, const smc_reweight_args *args, int32_t force)
+{
+    if (!ctx || !args)
+        return SMC_ERR_INVALID_ARG;
+    Ctx &c = ctx->c;
+    if (!c.initialised)
+        return fail(c, SMC_ERR_BAD_STATE, "smc_reweight before smc_init");
+    if (step < 0)
+        return fail(c, SMC_ERR_INVALID_ARG, "step must be >= 0");
+    const bool fused = c.cfg.model != SMC_MODEL_CV_TRACK &&
+                       c.cfg.scheme == SMC_RS_SYSTEMATIC && c.ntiles <= NR_MAX_TILES;
+    if (!fused || c.ntiles > 1) {
+        smc_status s = smc_reweight(ctx, step, args);
+        if (s == SMC_OK && fused) {
+            const hipError_t e = launch_normalise_resample(c, step, force);
+            if (e == hipSuccess)
+                c.normalised = c.armed_lw = c.armed_gather = true;
+            return hip_status(c, e, "smc_temper");
+        }
+        if (s == SMC_OK)
+            s = smc_ess(ctx, step, nullptr);
+        if (s == SMC_OK)
+            s = smc_resample(ctx, step, force);
+        return s;
+    }
+    if (!isfinite(args->dalpha))
+        return fail(c, SMC_ERR_INVALID_ARG, "dalpha must be finite");
+    hipError_t e = hipSuccess;
+    if (c.armed_gather) {
+        // the cached log-likelihood must be read at the resampled state
+        e = launch_gather(c);
+        if (e != hipSuccess)
+            return hip_status(c, e, "smc_temper");
+        c.cur ^= 1;
+        c.armed_gather = false;
+    }
+    e = launch_gmm_temper_tile(c, step, args->dalpha, c.armed_lw, force);
+    if (e == hipSuccess)
+        c.partials_valid = c.normalised = c.armed_lw = c.armed_gather = true;
+    return hip_status(c, e, "smc_temper");
+}
+
 smc_status smc_monitor(smc_ctx *ctx, int32_t step, double *out_dev)
 {
     if (!ctx)

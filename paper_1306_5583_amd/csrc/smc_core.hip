@@ -628,48 +628,118 @@ __global__ __launch_bounds__(TPB) void mon_partial_kernel(
     }
 }
 
-// The same partials per 64-particle tile: one wave per workgroup, one
-// particle per lane, no barriers.  Many more workgroups for the same work,
-// which is what a population too small to fill the chip with 1024-particle
-// tiles needs.
-template <typename T>
-__global__ __launch_bounds__(WAVE) void mon_partial64_kernel(
-    const T *__restrict__ x, int rows, int64_t n, const double *__restrict__ lw,
-    const int32_t *__restrict__ anc, const double *__restrict__ scalars, int gather_check,
-    int reset_check, double *__restrict__ mon, int64_t ntiles)
+// Sums of eight rows over the wave's lanes, row g complete in lane 8g + 7, by
+// way of `buf` (MON_BUF doubles of the wave's own LDS): lane 8g + q adds
+// columns 8q .. 8q + 7 of row g, then the row's eight lanes are added, pairs
+// of neighbours at every level as wave_sum pairs them (same bits).  About 50
+// instructions where eight wave_sums take 200.
+constexpr int MON_COLS = WAVE + 2;
+constexpr int MON_BUF = MON_GROUP * MON_COLS;
+__device__ __forceinline__ double wave_rows_sum(const double (&v)[MON_GROUP], double *buf)
 {
-    const bool resampled = scalars[SMC_S_RESAMPLED] != 0.0;
-    const bool gather = gather_check && resampled;
-    const bool reset = reset_check && resampled;
-    const double M = scalars[SMC_S_M];
-    const int64_t i = (int64_t)blockIdx.x * WAVE + lane_id();
+    static_assert(MON_GROUP * 8 == WAVE, "eight lanes a row, eight columns a lane");
+    const int lane = lane_id();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int g = 0; g < MON_GROUP; ++g)
+        buf[g * MON_COLS + lane] = v[g];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const double *b = buf + (lane >> 3) * MON_COLS + 8 * (lane & 7);
+    double a = ((b[0] + b[1]) + (b[2] + b[3])) + ((b[4] + b[5]) + (b[6] + b[7]));
+    a += dpp::mov<dpp::ROW_SHR1>(a, 0.0);
+    a += dpp::mov<dpp::ROW_SHR2>(a, 0.0);
+    a += dpp::mov<dpp::ROW_SHR4>(a, 0.0);
+    return a;
+}
+
+// Column sums of one 64-particle tile in one wave, one particle a lane:
+// store(c, sum) by one lane for each column c = 0 (sum w) and 1 + r (sum
+// w x_r).  MON_LOADS rows are in flight at once.
+constexpr int MON_LOADS = 16;
+template <typename T, typename F>
+__device__ __forceinline__ void mon_tile64(const T *__restrict__ x, int rows, int64_t n,
+                                           const double *__restrict__ lw,
+                                           const int32_t *__restrict__ anc, bool gather,
+                                           bool reset, double M, int64_t tile, double *buf,
+                                           F store)
+{
+    const int64_t i = tile * WAVE + lane_id();
     double w = 0.0;
     int64_t src = 0;
     if (i < n) {
         src = gather ? (int64_t)anc[i] : i;
         w = reset ? 1.0 : exp_nonpos_d(lw[i] - M);
     }
-    for (int c0 = 0; c0 <= rows; c0 += MON_GROUP) {
-        double v[MON_GROUP];
+    for (int c0 = 0; c0 <= rows; c0 += MON_LOADS) {
+        double v[MON_LOADS];
 #pragma unroll
-        for (int g = 0; g < MON_GROUP; ++g) {
+        for (int g = 0; g < MON_LOADS; ++g) {
             const int c = c0 + g;
             v[g] = 0.0;
-            if (c == 0)
-                v[g] = w;
-            else if (c <= rows && w != 0.0)
-                v[g] = w * (double)x[(int64_t)(c - 1) * n + src];
+            if (c > 0 && c <= rows && i < n)
+                v[g] = (double)x[(int64_t)(c - 1) * n + src];
         }
 #pragma unroll
-        for (int g = 0; g < MON_GROUP; ++g)
-            v[g] = wave_sum(v[g]);
-        if (lane_id() == 0) {
+        for (int h = 0; h < MON_LOADS; h += MON_GROUP) {
+            if (c0 + h > rows)
+                break;
+            double u[MON_GROUP];
 #pragma unroll
-            for (int g = 0; g < MON_GROUP; ++g)
-                if (c0 + g <= rows)
-                    mon[(int64_t)(c0 + g) * ntiles + blockIdx.x] = v[g];
+            for (int g = 0; g < MON_GROUP; ++g)  // no weight adds nothing, whatever the state
+                u[g] = c0 + h + g == 0 ? w : (w != 0.0 ? w * v[h + g] : 0.0);
+            const double a = wave_rows_sum(u, buf);
+            const int c = c0 + h + (lane_id() >> 3);
+            if ((lane_id() & 7) == 7 && c <= rows)
+                store(c, a);
         }
     }
+}
+
+// The same partials per 64-particle tile: one wave per workgroup, no
+// barriers.  Many more workgroups for the same work, which is what a
+// population too small to fill the chip with 1024-particle tiles needs.
+template <typename T>
+__global__ __launch_bounds__(WAVE) void mon_partial64_kernel(
+    const T *__restrict__ x, int rows, int64_t n, const double *__restrict__ lw,
+    const int32_t *__restrict__ anc, const double *__restrict__ scalars, int gather_check,
+    int reset_check, double *__restrict__ mon, int64_t ntiles)
+{
+    __shared__ double buf[MON_BUF];
+    const bool resampled = scalars[SMC_S_RESAMPLED] != 0.0;
+    mon_tile64(x, rows, n, lw, anc, gather_check && resampled, reset_check && resampled,
+               scalars[SMC_S_M], blockIdx.x, buf,
+               [&](int c, double a) { mon[(int64_t)c * ntiles + blockIdx.x] = a; });
+}
+
+// Populations of one tile, in one launch: a 64-particle tile a wave, then the
+// sums over the tiles, row r in wave r mod FIN_NW, tile by lane as
+// mon_combine adds them (same bits).
+template <typename T>
+__global__ __launch_bounds__(TILE) void mon_one_kernel(
+    const T *__restrict__ x, int rows, int64_t n, const double *__restrict__ lw,
+    const int32_t *__restrict__ anc, const double *__restrict__ scalars, int gather_check,
+    int reset_check, MonDest md, double *__restrict__ hist, int64_t hist_len)
+{
+    constexpr int NW = TILE / WAVE;
+    __shared__ double buf[NW * MON_BUF];
+    __shared__ double part[MON_STRIDE * NW];
+    __shared__ double col[MON_STRIDE];
+    const bool resampled = scalars[SMC_S_RESAMPLED] != 0.0;
+    const int nt = (int)ceil_div(n, WAVE), lane = lane_id(), wave = wave_id();
+    if (wave < nt)
+        mon_tile64(x, rows, n, lw, anc, gather_check && resampled, reset_check && resampled,
+                   scalars[SMC_S_M], wave, buf + wave * MON_BUF,
+                   [&](int c, double a) { part[c * NW + wave] = a; });
+    __syncthreads();
+    for (int r = wave; r <= rows; r += NW) {
+        const double a = wave_sum(lane < nt ? part[r * NW + lane] : 0.0);
+        if (lane == 0)
+            col[r] = a;
+    }
+    __syncthreads();
+    mon_finish(md, col, hist, hist_len);
 }
 
 __global__ __launch_bounds__(FIN_TPB) void mon_final_kernel(const double *__restrict__ mon,
@@ -685,6 +755,20 @@ __global__ __launch_bounds__(FIN_TPB) void mon_final_kernel(const double *__rest
 hipError_t launch_monitor(Ctx &c, int32_t step, double *out_dev, int rows, bool gather_pending,
                           bool reset_pending)
 {
+    if (c.ntiles == 1) {
+        const MonDest md = mon_dest(c, step, rows, out_dev);
+#define SMC_MON_ONE(T)                                                                           \
+    hipLaunchKernelGGL(mon_one_kernel<T>, dim3(1), dim3(TILE), 0, c.stream,                      \
+                       (const T *)c.state_ptr(), rows, c.n, c.buf.log_weight, c.buf.ancestors,   \
+                       c.buf.scalars, (int)gather_pending, (int)reset_pending, md,               \
+                       c.buf.history, c.buf.history_len)
+        if (c.elem_bytes == 4)
+            SMC_MON_ONE(float);
+        else
+            SMC_MON_ONE(double);
+#undef SMC_MON_ONE
+        return hipGetLastError();
+    }
     // 64-particle tiles up to MON64_MAX_TILES of them, 1024-particle tiles beyond
     const int64_t t64 = ceil_div(c.n, WAVE);
     const bool small = t64 <= MON64_MAX_TILES;

@@ -57,6 +57,20 @@ __global__ __launch_bounds__(TPB) void gmm_reweight_kernel(Prob P, const double 
     gmm_reweight_tile(P, llrow, blockIdx.x, reset_check, dalpha);
 }
 
+// The weighting of an iteration for a population of one tile: weights, then
+// normalisation and systematic resampling, one workgroup after its own
+// barrier where three launches would wait for one another (1000 particles:
+// 14 -> 8 us).
+__global__ __launch_bounds__(TPB) void gmm_temper_tile_kernel(Prob P,
+                                                              const double *__restrict__ llrow,
+                                                              int reset_check, double dalpha,
+                                                              int32_t step, int32_t force)
+{
+    gmm_reweight_tile(P, llrow, 0, reset_check, dalpha);
+    __syncthreads();
+    normalise_resample_tile(P, step, 0, force);
+}
+
 // ---------------------------------------------------------------------------
 // Launch helpers
 // ---------------------------------------------------------------------------
@@ -156,6 +170,16 @@ hipError_t launch_gmm_reweight(Ctx &c, double dalpha, bool reset_check)
     const double *llrow = (const double *)c.state_ptr() + (int64_t)D * c.n;
     hipLaunchKernelGGL(gmm_reweight_kernel, dim3((unsigned)c.ntiles), dim3(TPB), 0, c.stream,
                        make_prob(c), llrow, (int)reset_check, dalpha);
+    return hipGetLastError();
+}
+
+hipError_t launch_gmm_temper_tile(Ctx &c, int32_t step, double dalpha, bool reset_check,
+                                  int32_t force)
+{
+    const int D = 3 * c.cfg.K - 1;
+    const double *llrow = (const double *)c.state_ptr() + (int64_t)D * c.n;
+    hipLaunchKernelGGL(gmm_temper_tile_kernel, dim3(1), dim3(TPB), 0, c.stream, make_prob(c),
+                       llrow, (int)reset_check, dalpha, step, force);
     return hipGetLastError();
 }
 

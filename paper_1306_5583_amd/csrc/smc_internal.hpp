@@ -220,6 +220,8 @@ hipError_t launch_pf_reweight(Ctx &c, int32_t obs_index, bool reset_check);
 // --- GMM launchers (smc_gmm.hip) ---
 hipError_t launch_gmm_init(Ctx &c);
 hipError_t launch_gmm_reweight(Ctx &c, double dalpha, bool reset_check);
+hipError_t launch_gmm_temper_tile(Ctx &c, int32_t step, double dalpha, bool reset_check,
+                                  int32_t force);
 hipError_t launch_gmm_move(Ctx &c, int32_t step, const smc_move_args &a, bool gather_check);
 hipError_t launch_gmm_loglik_grad(const double *mu, const double *eta, const double *z,
                                   int64_t n, int32_t K, const double *y, int64_t n_data,

@@ -100,6 +100,35 @@ struct MonDest {
     double alpha;     // tempering exponent of the monitored particles
 };
 
+// The estimates from the column sums col[0 .. rows] (LDS, after a barrier).
+__device__ __forceinline__ void mon_finish(const MonDest &d, const double *col,
+                                           double *__restrict__ hist, int64_t hist_len)
+{
+    if ((int)threadIdx.x < d.rows) {
+        const int r = threadIdx.x;
+        const double est = col[1 + r] / col[0];
+        if (d.out)
+            d.out[r] = est;
+        if (hist && d.step >= 0 && d.step < hist_len && r >= d.rows - d.hist_ncols)
+            hist[(int64_t)d.step * SMC_HIST_COLS + d.hist_col + (r - (d.rows - d.hist_ncols))] =
+                est;
+        // path sampling (Section 5.2): the last row is U = sum W l at alpha;
+        // one trapezoid from the previously monitored (alpha, U)
+        if (d.scalars && r == d.rows - 1) {
+            double *sc = d.scalars;
+            const double a0 = sc[SMC_S_PS_ALPHA];
+            double ps = sc[SMC_S_PS_LOGZ];
+            if (a0 >= 0.0)
+                ps += 0.5 * (d.alpha - a0) * (est + sc[SMC_S_PS_U]);
+            sc[SMC_S_PS_LOGZ] = ps;
+            sc[SMC_S_PS_U] = est;
+            sc[SMC_S_PS_ALPHA] = d.alpha;
+            if (hist && d.step >= 0 && d.step < hist_len)
+                hist[(int64_t)d.step * SMC_HIST_COLS + SMC_H_PS] = ps;
+        }
+    }
+}
+
 // Sums the tile partials of every monitored row with the whole workgroup:
 // thread t adds tiles t, t + NTHR, t + 2 NTHR, ... in order (MON_IT of them
 // loaded at once, two rows at a time), each wave adds its lanes, and thread r
@@ -126,7 +155,7 @@ __device__ void mon_combine(const double *__restrict__ mon, int64_t ntiles, cons
 #pragma unroll
             for (int g = 0; g < RG; ++g)
                 if (r0 + g <= d.rows) {
-                    const double v = wave_sum(x[g]);
+                    const double v = w * WAVE < ntiles ? wave_sum(x[g]) : 0.0;
                     if (lane_id() == 0)
                         red[(r0 + g) * NW + w] = v;
                 }
@@ -168,29 +197,7 @@ __device__ void mon_combine(const double *__restrict__ mon, int64_t ntiles, cons
         col[tid] = a;
     }
     __syncthreads();
-    if ((int)threadIdx.x < d.rows) {
-        const int r = threadIdx.x;
-        const double est = col[1 + r] / col[0];
-        if (d.out)
-            d.out[r] = est;
-        if (hist && d.step >= 0 && d.step < hist_len && r >= d.rows - d.hist_ncols)
-            hist[(int64_t)d.step * SMC_HIST_COLS + d.hist_col + (r - (d.rows - d.hist_ncols))] =
-                est;
-        // path sampling (Section 5.2): the last row is U = sum W l at alpha;
-        // one trapezoid from the previously monitored (alpha, U)
-        if (d.scalars && r == d.rows - 1) {
-            double *sc = d.scalars;
-            const double a0 = sc[SMC_S_PS_ALPHA];
-            double ps = sc[SMC_S_PS_LOGZ];
-            if (a0 >= 0.0)
-                ps += 0.5 * (d.alpha - a0) * (est + sc[SMC_S_PS_U]);
-            sc[SMC_S_PS_LOGZ] = ps;
-            sc[SMC_S_PS_U] = est;
-            sc[SMC_S_PS_ALPHA] = d.alpha;
-            if (hist && d.step >= 0 && d.step < hist_len)
-                hist[(int64_t)d.step * SMC_HIST_COLS + SMC_H_PS] = ps;
-        }
-    }
+    mon_finish(d, col, hist, hist_len);
 }
 
 constexpr int FIN_MON_ROWS = 4;  // rows a move can carry (the tracking state)

@@ -274,9 +274,7 @@ class GmmSampler(_Base):
         if scales is None:
             scales = rw_scales(a) if self.move == "rw" else mala_scales(a)
         self._rargs.dalpha = dalpha
-        L.smc_reweight(self.ctx, t, self._rargs)
-        L.smc_ess(self.ctx, t)
-        L.smc_resample(self.ctx, t)
+        L.smc_temper(self.ctx, t, self._rargs)
         m = self._margs
         m.alpha = a
         for b in range(3):

@@ -398,6 +398,72 @@ def test_lockstep_small_populations(lib, orc, n, K, nd, move):
     _lockstep_gmm(lib, orc, n, K, nd, 4, move, sweeps=2)
 
 
+@pytest.mark.parametrize("n", [1, 63, 1000, 1024, 1025, 9000, 262144, 262145])
+@pytest.mark.parametrize("scheme,threshold", [("systematic", 0.5), ("systematic", 1.0),
+                                              ("systematic", 0.0), ("stratified", 0.5)])
+def test_temper_matches_three_calls(lib, n, scheme, threshold):
+    # smc_temper at the edges of its forms (one tile in one launch, up to 256
+    # tiles in two) against smc_reweight, smc_ess and smc_resample, bit for bit
+    pkg, L = lib
+    y = synth.gmm_data(20, [-1.0, 2.0], 1.0, [1, 1], 3)
+    a, b = (pkg.GmmSampler(n, y, 2, 4, seed=9, scheme=scheme, threshold=threshold)
+            for _ in range(2))
+    alphas = [0.0, 0.1, 0.3, 0.6, 1.0]
+    a.run(alphas, monitor=False)
+    b.init(monitor=False)
+    for t in range(1, 5):
+        b._rargs.dalpha = alphas[t] - alphas[t - 1]
+        L.smc_reweight(b.ctx, t, b._rargs)
+        L.smc_ess(b.ctx, t)
+        L.smc_resample(b.ctx, t)
+        m = b._margs
+        m.alpha = alphas[t]
+        for k, v in enumerate(pkg.sampler.rw_scales(alphas[t])):
+            m.scale[k] = v
+        L.smc_move(b.ctx, t, m)
+    assert np.array_equal(a.history_host(), b.history_host())
+    assert a.scalars_host() == b.scalars_host()
+    assert torch.equal(a.state(), b.state())
+    assert torch.equal(a.log_weight, b.log_weight)
+    assert torch.equal(a.ancestors, b.ancestors)
+    # a resample still pending at the next weighting
+    for s in (a, b):
+        s._rargs.dalpha = 0.25
+    L.smc_temper(a.ctx, 4, a._rargs, True)
+    L.smc_temper(a.ctx, 4, a._rargs)
+    for force in (True, False):
+        L.smc_reweight(b.ctx, 4, b._rargs)
+        L.smc_ess(b.ctx, 4)
+        L.smc_resample(b.ctx, 4, force)
+    assert a.scalars_host() == b.scalars_host()
+    assert torch.equal(a.ancestors, b.ancestors)
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 1000, 1024, 1025])
+@pytest.mark.parametrize("K", [1, 3, 6])
+def test_monitor_small_populations(lib, n, K):
+    # at the edge of the one-launch form: weighted means of every row, before
+    # and after a resample, against float64 sums of n products
+    pkg, L = lib
+    s = pkg.GmmSampler(n, synth.gmm_data(30, [-1.0, 2.0], 1.0, [1, 1], 3), K, 2, seed=5)
+    s.init()
+    s._rargs.dalpha = 0.05
+    for force in (False, True):
+        L.smc_reweight(s.ctx, 1, s._rargs)
+        L.smc_ess(s.ctx, 1)
+        if force:
+            L.smc_resample(s.ctx, 1, True)
+        L.smc_monitor(s.ctx, 1, s.monitor_out.data_ptr())
+        x = s.state()[:s.D + 1].cpu().numpy()
+        lw = s.log_weight.cpu().numpy()
+        w = np.exp(lw - lw.max())
+        if force:
+            x, w = x[:, s.ancestors.cpu().numpy()], np.ones(n)
+        w = w / w.sum()
+        assert_close_l1(s.monitor_out.cpu().numpy(), x @ w, np.abs(x) @ w + 1e-3, 1e-12,
+                        "monitor n=%d" % n)
+
+
 def test_autograd_function_gradcheck(lib, orc):
     pkg, L = lib
     K, n, nd = 3, 8, 40
