@@ -12,26 +12,27 @@ namespace smc {
 // ---------------------------------------------------------------------------
 // Scalar block reset (initialisation): L = log N, log Z = 0.
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void reset_scalars(double *scalars, int32_t *counters, int64_t n)
+{
+    const int t = threadIdx.x;
+    if (t < SMC_SCALARS_LEN)
+        scalars[t] = t == SMC_S_L || t == SMC_S_L2 ? log((double)n)
+                     : t == SMC_S_ESS              ? (double)n
+                     : t == SMC_S_PS_ALPHA         ? -1.0
+                                                   : 0.0;
+    if (t < 16)
+        counters[t] = 0;
+}
+
 // Scalars and counters to their t = 0 values; the history rows (whose
 // acceptance columns are accumulated) to zero.
 __global__ void reset_scalars_kernel(double *scalars, int32_t *counters, int64_t n, double *hist,
                                      int64_t hist_len)
 {
-    const int t = threadIdx.x;
-    if (t < SMC_SCALARS_LEN)
-        scalars[t] = 0.0;
-    if (t < 16)
-        counters[t] = 0;
+    reset_scalars(scalars, counters, n);
     if (hist)
-        for (int64_t k = t; k < hist_len * SMC_HIST_COLS; k += blockDim.x)
+        for (int64_t k = threadIdx.x; k < hist_len * SMC_HIST_COLS; k += blockDim.x)
             hist[k] = 0.0;
-    __syncthreads();
-    if (t == 0) {
-        scalars[SMC_S_L] = log((double)n);
-        scalars[SMC_S_L2] = log((double)n);
-        scalars[SMC_S_ESS] = (double)n;
-        scalars[SMC_S_PS_ALPHA] = -1.0;
-    }
 }
 
 hipError_t launch_reset_scalars(Ctx &c)
@@ -87,21 +88,10 @@ hipError_t launch_finalize_batch(const Prob *probs, int32_t nprob, const int32_t
 __global__ void reset_scalars_batch_kernel(const Prob *__restrict__ probs)
 {
     const Prob &P = probs[blockIdx.x];
-    const int t = threadIdx.x;
-    if (t < SMC_SCALARS_LEN)
-        P.scalars[t] = 0.0;
-    if (t < 16)
-        P.counters[t] = 0;
+    reset_scalars(P.scalars, P.counters, P.n);
     if (P.hist)
-        for (int64_t k = t; k < P.hist_len * SMC_HIST_COLS; k += blockDim.x)
+        for (int64_t k = threadIdx.x; k < P.hist_len * SMC_HIST_COLS; k += blockDim.x)
             P.hist[k] = 0.0;
-    __syncthreads();
-    if (t == 0) {
-        P.scalars[SMC_S_L] = log((double)P.n);
-        P.scalars[SMC_S_L2] = log((double)P.n);
-        P.scalars[SMC_S_ESS] = (double)P.n;
-        P.scalars[SMC_S_PS_ALPHA] = -1.0;
-    }
 }
 
 __global__ void set_step_kernel(int32_t *step, int32_t value, int32_t add)
@@ -340,7 +330,7 @@ __global__ __launch_bounds__(TPB) void normalise_resample_kernel(Prob P, int32_t
                                                                  int32_t force, MonDest md)
 {
     if ((int64_t)blockIdx.x < P.ntiles)
-        normalise_resample_tile(P, step, blockIdx.x, force);
+        normalise_resample_tile(P, step, (uint32_t)step, blockIdx.x, force);
     else
         monitor_block<TPB>(P, md);
 }
@@ -520,54 +510,92 @@ hipError_t launch_resample_batch(const Prob *probs, const int2 *map, int64_t til
 
 // ---------------------------------------------------------------------------
 // Resampling of a caller's log-weights in one call: per-tile partials of
-// lw, the normalisation, the resampling of the configured scheme, and a
-// five-value summary.
+// lw (and the scalars' reset), the normalisation, the resampling of the
+// configured scheme, and a five-value summary.  Every stage is a few
+// microseconds of latency and a call on a small population little else, so
+// systematic resampling takes two launches up to NR_MAX_TILES tiles and one
+// for a single tile (1000 weights: five launches of 12.3 us -> one of 6).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(TPB) void lw_partials_kernel(const double *__restrict__ lw,
-                                                          int64_t n,
-                                                          TilePartial *__restrict__ part)
+__device__ __forceinline__ void lw_partials_tile(const Prob &P, int64_t tile)
 {
     __shared__ double red[NWAVES];
-    const int64_t base = (int64_t)blockIdx.x * TILE;
+    const double *__restrict__ lw = P.lw;
+    const int64_t n = P.n, base = tile * TILE;
+    if (tile == 0)
+        reset_scalars(P.scalars, P.counters, n);
     double l[ITEMS];
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int64_t i = base + k * TPB + threadIdx.x;
         l[k] = i < n ? lw[i] : -INFINITY;
     }
-    tile_partial(l, part + blockIdx.x, red);
+    tile_partial(l, P.partials + tile, red);
 }
 
-// summary = {L, L2, ESS, resampled (0/1), device error bits}
-__global__ void resample_summary_kernel(const double *__restrict__ scalars,
-                                        const int32_t *__restrict__ counters,
-                                        double *__restrict__ summary)
+__global__ __launch_bounds__(TPB) void lw_partials_kernel(Prob P)
 {
-    if (threadIdx.x == 0) {
-        summary[0] = scalars[SMC_S_RESAMPLED] != 0.0 ? scalars[SMC_S_LPRE] : scalars[SMC_S_L];
-        summary[1] = scalars[SMC_S_L2];
-        summary[2] = scalars[SMC_S_ESS];
-        summary[3] = scalars[SMC_S_RESAMPLED];
-        summary[4] = (double)counters[CNT_ERR];
+    lw_partials_tile(P, blockIdx.x);
+}
+
+// summary = {L, L2, ESS, resampled (0/1), device error bits}, by the lane that
+// wrote the scalars or after them
+__device__ __forceinline__ void write_summary(const double *scalars, int32_t *counters,
+                                              double *summary)
+{
+    summary[0] = scalars[SMC_S_RESAMPLED] != 0.0 ? scalars[SMC_S_LPRE] : scalars[SMC_S_L];
+    summary[1] = scalars[SMC_S_L2];
+    summary[2] = scalars[SMC_S_ESS];
+    summary[3] = scalars[SMC_S_RESAMPLED];
+    // the error word is set by atomics
+    summary[4] = (double)__hip_atomic_load(&counters[CNT_ERR], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <bool ONE>
+__global__ __launch_bounds__(TPB) void resample_weights_kernel(Prob P, int32_t step,
+                                                               int32_t force, double *summary)
+{
+    if (ONE) {
+        lw_partials_tile(P, 0);
+        __syncthreads();
     }
+    normalise_resample_tile(P, -1, step, blockIdx.x, force);
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        write_summary(P.scalars, P.counters, summary);
+}
+
+__global__ void resample_summary_kernel(const double *scalars, int32_t *counters, double *summary)
+{
+    if (threadIdx.x == 0)
+        write_summary(scalars, counters, summary);
 }
 
 hipError_t launch_resample_weights(Ctx &c, int32_t step, int32_t force, double *summary)
 {
-    hipError_t e = launch_reset_scalars(c);
+    const Prob P = make_prob(c);
+    const dim3 grid((unsigned)c.ntiles);
+    const bool fused = c.cfg.scheme == SMC_RS_SYSTEMATIC && c.ntiles <= NR_MAX_TILES;
+    if (fused && c.ntiles == 1) {
+        hipLaunchKernelGGL(resample_weights_kernel<true>, grid, dim3(TPB), 0, c.stream, P, step,
+                           force, summary);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(lw_partials_kernel, grid, dim3(TPB), 0, c.stream, P);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(lw_partials_kernel, dim3((unsigned)c.ntiles), dim3(TPB), 0, c.stream,
-                       (const double *)c.buf.log_weight, c.n, c.partials());
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
+    if (fused) {
+        hipLaunchKernelGGL(resample_weights_kernel<false>, grid, dim3(TPB), 0, c.stream, P, step,
+                           force, summary);
+        return hipGetLastError();
+    }
     c.mon_pending_step = -1;
     if ((e = launch_finalize(c, -1)) != hipSuccess)
         return e;
     if ((e = launch_resample(c, step, force)) != hipSuccess)
         return e;
     hipLaunchKernelGGL(resample_summary_kernel, dim3(1), dim3(64), 0, c.stream, c.buf.scalars,
-                       (const int32_t *)c.counters(), summary);
+                       c.counters(), summary);
     return hipGetLastError();
 }
 

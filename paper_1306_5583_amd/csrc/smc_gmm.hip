@@ -60,7 +60,7 @@ __global__ __launch_bounds__(TPB) void gmm_reweight_kernel(Prob P, const double 
 // The weighting of an iteration for a population of one tile: weights, then
 // normalisation and systematic resampling, one workgroup after its own
 // barrier where three launches would wait for one another (1000 particles:
-// 14 -> 8 us).
+// 10.3 us and two launch gaps -> 6.3 us).
 __global__ __launch_bounds__(TPB) void gmm_temper_tile_kernel(Prob P,
                                                               const double *__restrict__ llrow,
                                                               int reset_check, double dalpha,
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(TPB) void gmm_temper_tile_kernel(Prob P,
 {
     gmm_reweight_tile(P, llrow, 0, reset_check, dalpha);
     __syncthreads();
-    normalise_resample_tile(P, step, 0, force);
+    normalise_resample_tile(P, step, (uint32_t)step, 0, force);
 }
 
 // ---------------------------------------------------------------------------

@@ -869,8 +869,8 @@ __device__ __forceinline__ void resample_sys_tile(const Prob &P, int64_t b, uint
 // What it saves is a dependent launch of one workgroup: at 70001 particles
 // the two took 4.2 + 4.8 us and the gap between them.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void normalise_resample_tile(const Prob &P, int32_t step, int64_t b,
-                                                        int32_t force)
+__device__ __forceinline__ void normalise_resample_tile(const Prob &P, int32_t row, uint32_t step,
+                                                        int64_t b, int32_t force)
 {
     __shared__ double red[NWAVES], red2[NWAVES];
     __shared__ double wl[TPB];
@@ -929,7 +929,7 @@ __device__ __forceinline__ void normalise_resample_tile(const Prob &P, int32_t s
         if (tid == 0) {
             nsh = r;
             if (b == 0)
-                write_normalisation(P, step, r, M, S1, Lprev, logz_prev);
+                write_normalisation(P, row, r, M, S1, Lprev, logz_prev);
             P.prefix[b] = tw.Pb;
             if (b + 1 == ntiles)
                 P.prefix[ntiles] = S1;
@@ -938,7 +938,7 @@ __device__ __forceinline__ void normalise_resample_tile(const Prob &P, int32_t s
     __syncthreads();
     tw.flag = (double)nsh.flag;
     tw.L = nsh.L;
-    resample_sys_fill(P, b, (uint32_t)step, force, tw, l);
+    resample_sys_fill(P, b, step, force, tw, l);
 }
 
 // The almost-constant-velocity transition of particle i at step t.

@@ -90,6 +90,29 @@ def test_all_zero_weights_report_an_error(L):
     assert np.array_equal(anc, keep)
 
 
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 5000, 262144, 262145])
+@pytest.mark.parametrize("case", ["plain", "zeros", "all zero", "nan", "inf", "kept"])
+def test_launch_forms_agree(L, orc, n, case):
+    # systematic resampling in one launch (one tile), two (up to 256 tiles) and
+    # by the general path: the summary is that of the stratified scheme, which
+    # always takes the general path, bit for bit; the ancestors the oracle's
+    lw = _weights(n, n, zeros=0.3 if case == "zeros" and n > 1 else 0.0)
+    if case == "all zero":
+        lw[:] = -np.inf
+    if case in ("nan", "inf"):
+        lw[n // 2] = np.nan if case == "nan" else np.inf
+    force = 0 if case == "kept" else 1
+    keep = np.full(n, 7)
+    anc, sm = _run(L, lw, "systematic", threshold=0.0, force=force, anc_init=keep)
+    _, ref = _run(L, lw, "stratified", threshold=0.0, force=force, anc_init=keep)
+    assert np.array_equal(sm, ref, equal_nan=True)
+    if sm[3] == 0.0:
+        assert np.array_equal(anc, keep)
+    elif case in ("plain", "zeros"):
+        anc_o, S_o, u_o = orc.resample("systematic", 17, 5, lw)
+        assert_ancestors(anc, anc_o, S_o, u_o)
+
+
 def test_invalid_arguments(L):
     from paper_1306_5583_amd import SmcError
     lw = torch.zeros(100, dtype=torch.float64, device="cuda")
