@@ -171,8 +171,7 @@ __global__ __launch_bounds__(TPB) void pf_step_tile_strat_kernel(Prob P, uint32_
     }
     __syncthreads();
     __shared__ double sS[TILE];
-    __shared__ double sU[RS_UCAP];
-    resample_tile<SMC_RS_STRATIFIED>(P, 0, t, force, nullptr, sS, sU);
+    resample_tile<SMC_RS_STRATIFIED>(P, 0, t, force, MultiSums{}, sS);
 }
 
 // Systematic resampling: a workgroup of TILE lanes.  One compute unit runs
@@ -378,11 +377,10 @@ __global__ __launch_bounds__(TPB) void resample_sys_kernel(Prob P, uint32_t t, i
 
 template <int SCHEME>
 __global__ __launch_bounds__(TPB) void resample_merge_kernel(Prob P, uint32_t t, int32_t force,
-                                                             const double *__restrict__ G)
+                                                             MultiSums G)
 {
     __shared__ double sS[TILE];
-    __shared__ double sU[RS_UCAP];
-    resample_tile<SCHEME>(P, blockIdx.x, t, force, G, sS, sU);
+    resample_tile<SCHEME>(P, blockIdx.x, t, force, G, sS);
 }
 
 // Batched resampling (systematic or stratified) over the tiles of many problems.
@@ -391,11 +389,10 @@ __global__ __launch_bounds__(TPB) void resample_batch_kernel(const Prob *__restr
                                                              const int32_t *__restrict__ step)
 {
     __shared__ double sS[TILE];
-    __shared__ double sU[RS_UCAP];
     const int2 pm = map[blockIdx.x];
     const Prob &P = probs[pm.x];
     if (P.scheme == SMC_RS_STRATIFIED)
-        resample_tile<SMC_RS_STRATIFIED>(P, pm.y, (uint32_t)*step, 0, nullptr, sS, sU);
+        resample_tile<SMC_RS_STRATIFIED>(P, pm.y, (uint32_t)*step, 0, MultiSums{}, sS);
     else
         resample_sys_tile(P, pm.y, (uint32_t)*step, 0);
 }
@@ -408,25 +405,59 @@ __device__ __forceinline__ double mn_exp(Key key, int64_t k, uint32_t t, uint32_
     return -log(u53(w.x, w.y));
 }
 
-__global__ __launch_bounds__(TPB) void mn_tile_sum_kernel(const double *__restrict__ scalars,
-                                                          int32_t force, int64_t count, Key key,
-                                                          uint32_t t, uint32_t p,
-                                                          double *__restrict__ gtile)
+// The exponentials of one tile, drawn once: their sum and, in `local`, their
+// inclusive sums from the tile's start, which the resampling offsets as it
+// reads them (a second pass that drew them again to write the sums over all
+// tiles took 9.4 us of a million particles' 62 us step).
+__global__ __launch_bounds__(TPB) void mn_exp_kernel(const double *__restrict__ scalars,
+                                                     int32_t force, int64_t count, Key key,
+                                                     uint32_t t, uint32_t p,
+                                                     double *__restrict__ gtile,
+                                                     double *__restrict__ local)
 {
-    __shared__ double red[NWAVES];
+    __shared__ double red[ITEMS + 1][NWAVES];
     if (!(force != 0 || scalars[SMC_S_FLAG] != 0.0))
         return;
     const int64_t base = (int64_t)blockIdx.x * TILE;
-    double s = 0.0;
+    double e[ITEMS], s = 0.0;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int64_t i = base + k * TPB + threadIdx.x;
-        if (i < count)
-            s += mn_exp(key, i, t, p);
+        e[k] = i < count ? mn_exp(key, i, t, p) : 0.0;
+        s += e[k];
     }
-    s = block_sum<NWAVES>(s, red);
-    if (threadIdx.x == 0)
+    // every wave's sums in one round: red[k] the scans', red[ITEMS] the total's
+    double v[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        v[k] = wave_incl_scan(e[k]);
+        if (lane_id() == WAVE - 1)
+            red[k][wave_id()] = v[k];
+    }
+    s = wave_sum(s);
+    if (lane_id() == 0)
+        red[ITEMS][wave_id()] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s = red[ITEMS][0];
+        for (int w = 1; w < NWAVES; ++w)
+            s += red[ITEMS][w];
         gtile[blockIdx.x] = s;
+    }
+    double carry = 0.0;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int64_t i = base + k * TPB + threadIdx.x;
+        double before = 0.0, all = 0.0;
+#pragma unroll
+        for (int w = 0; w < NWAVES; ++w) {
+            before += w < wave_id() ? red[k][w] : 0.0;
+            all += red[k][w];
+        }
+        if (i < count)
+            local[i] = carry + (before + v[k]);
+        carry += all;
+    }
 }
 
 __global__ __launch_bounds__(FIN_TPB) void mn_prefix_kernel(const double *__restrict__ scalars,
@@ -439,32 +470,6 @@ __global__ __launch_bounds__(FIN_TPB) void mn_prefix_kernel(const double *__rest
     if (!(force != 0 || scalars[SMC_S_FLAG] != 0.0))
         return;
     tile_offsets(gtiles, [&](int64_t b) { return gtile[b]; }, gprefix, red);
-}
-
-__global__ __launch_bounds__(TPB) void mn_write_kernel(const double *__restrict__ scalars,
-                                                       int32_t force, int64_t count, Key key,
-                                                       uint32_t t, uint32_t p,
-                                                       const double *__restrict__ gprefix,
-                                                       double *__restrict__ G)
-{
-    __shared__ double red[NWAVES];
-    if (!(force != 0 || scalars[SMC_S_FLAG] != 0.0))
-        return;
-    const int64_t b = blockIdx.x;
-    const int64_t base = b * TILE;
-    const int len = (int)min((int64_t)TILE, count - base);
-    const double P0 = gprefix[b], P1 = gprefix[b + 1];
-    double carry = 0.0;
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-        const int64_t i = base + k * TPB + threadIdx.x;
-        const double e = i < count ? mn_exp(key, i, t, p) : 0.0;
-        double tot;
-        const double incl = block_incl_scan<NWAVES>(e, red, &tot);
-        if (i < count)
-            G[i] = (k * TPB + (int)threadIdx.x == len - 1) ? P1 : fmin(P0 + (carry + incl), P1);
-        carry += tot;
-    }
 }
 
 hipError_t launch_resample(Ctx &c, int32_t step, int32_t force)
@@ -480,19 +485,16 @@ hipError_t launch_resample(Ctx &c, int32_t step, int32_t force)
         break;
     case SMC_RS_STRATIFIED:
         hipLaunchKernelGGL(resample_merge_kernel<SMC_RS_STRATIFIED>, grid, dim3(TPB), 0, c.stream,
-                           P, (uint32_t)step, force, (const double *)nullptr);
+                           P, (uint32_t)step, force, MultiSums{});
         break;
     default: {
         const int64_t count = c.n + 1;
-        hipLaunchKernelGGL(mn_tile_sum_kernel, dim3((unsigned)c.gtiles), dim3(TPB), 0, c.stream,
-                           c.buf.scalars, force, count, key, (uint32_t)step, p, c.gtile());
+        hipLaunchKernelGGL(mn_exp_kernel, dim3((unsigned)c.gtiles), dim3(TPB), 0, c.stream,
+                           c.buf.scalars, force, count, key, (uint32_t)step, p, c.gtile(), c.g());
         hipLaunchKernelGGL(mn_prefix_kernel, dim3(1), dim3(FIN_TPB), 0, c.stream, c.buf.scalars,
                            force, c.gtile(), c.gtiles, c.gprefix());
-        hipLaunchKernelGGL(mn_write_kernel, dim3((unsigned)c.gtiles), dim3(TPB), 0, c.stream,
-                           c.buf.scalars, force, count, key, (uint32_t)step, p, c.gprefix(),
-                           c.g());
         hipLaunchKernelGGL(resample_merge_kernel<SMC_RS_MULTINOMIAL>, grid, dim3(TPB), 0,
-                           c.stream, P, (uint32_t)step, force, (const double *)c.g());
+                           c.stream, P, (uint32_t)step, force, MultiSums{c.g(), c.gprefix()});
     }
     }
     return hipGetLastError();

@@ -210,9 +210,10 @@ __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restri
     __shared__ uint32_t sh_ticket;
     __shared__ int sh_go;
     // one LDS arena for the two largest users, which never run at the same
-    // time: a Metropolis item (wave-combine buffer, stash and draws) and a stratified
-    // resampling tile (cumulative weights + slot uniforms)
-    constexpr int ARENA = GMM_ITEM_DOUBLES > TILE + RS_UCAP ? GMM_ITEM_DOUBLES : TILE + RS_UCAP;
+    // time: a Metropolis item (wave-combine buffer, stash and draws) and a
+    // stratified resampling tile (cumulative weights)
+    constexpr int ARENA = GMM_ITEM_DOUBLES;
+    static_assert(ARENA >= TILE, "a tile's cumulative weights fit in the arena");
     __shared__ double arena[ARENA];
     double *gred = arena, *gstash = arena + GMM_RED_DOUBLES;
     double *gdraws = gstash + GMM_STASH_MAX;
@@ -309,8 +310,7 @@ __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restri
         }
         case IT_RESAMPLE:
             if (P.scheme == SMC_RS_STRATIFIED)
-                resample_tile<SMC_RS_STRATIFIED>(P, it.tile, (uint32_t)t, 0, nullptr, arena,
-                                                 arena + TILE);
+                resample_tile<SMC_RS_STRATIFIED>(P, it.tile, (uint32_t)t, 0, MultiSums{}, arena);
             else
                 resample_sys_tile(P, it.tile, (uint32_t)t, 0);
             release = P.kind == SMC_MODEL_GMM_TEMPERED ? DEP_R : -1;

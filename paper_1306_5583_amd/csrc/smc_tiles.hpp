@@ -450,11 +450,23 @@ struct StratPred {  // u_i = (i + U_i) / N, U_i from counter (i, t, RESAMPLE, 0)
     }
 };
 
+// Cumulative sums G_0 .. G_N of N + 1 exponentials: within each tile from its
+// start (`local`), and the tiles' offsets (prefix[tiles] = G_N).
+struct MultiSums {
+    const double *local, *prefix;
+};
+
 struct MultiPred {  // u_i = G_i / G_N
-    const double *G;
+    MultiSums G;
     double gn, stot;
-    int64_t n;
-    __device__ double operator()(int64_t i) const { return (G[i] / gn) * stot; }
+    __device__ double at(double g) const { return (g / gn) * stot; }
+    // the last of a tile ends on the next offset; none passes it
+    __device__ double operator()(int64_t i) const
+    {
+        const int64_t b = i / TILE;
+        const double P1 = G.prefix[b + 1];
+        return at(i % TILE == TILE - 1 ? P1 : fmin(G.prefix[b] + G.local[i], P1));
+    }
 };
 
 // Smallest i in [0, n] with pred(i) >= x (n when none), starting from an
@@ -505,6 +517,38 @@ __device__ int64_t count_below_search(const P &pred, double x, int64_t n)
     if (bal == 0ull)
         return hi;
     return lo + (__ffsll((long long)bal) - 1);
+}
+
+// Smallest slot i with u_i S >= x (n when none), by one wave: the tile by a
+// search over the offsets, the slot by looking at all of the tile's at once
+// (a search over the slots themselves is a chain of four dependent loads).
+__device__ inline int64_t count_below_sums(const MultiPred &pred, double x, int64_t n)
+{
+    const auto tile_end = [&](int64_t b) { return pred.at(pred.G.prefix[b + 1]); };
+    const int64_t base = count_below_search(tile_end, x, n / TILE) * TILE;
+    const double P0 = pred.G.prefix[base / TILE], P1 = pred.G.prefix[base / TILE + 1];
+    constexpr int PER = TILE / WAVE;
+    double g[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t i = base + k * WAVE + lane_id();
+        g[k] = i < n ? pred.G.local[i] : 0.0;
+    }
+    // u S < x iff G < x G_N / S but for rounding: only a sum that near to it
+    // is put through the division
+    const double gx = x / pred.stot * pred.gn;
+    const double gl = gx * (1.0 - 1e-14), gh = gx * (1.0 + 1e-14);
+    int below = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int j = k * WAVE + lane_id();
+        const double s = j == TILE - 1 ? P1 : fmin(P0 + g[k], P1);
+        bool lt = s < gl;
+        if (!lt && !(s > gh))
+            lt = pred.at(s) < x;
+        below += (int)__popcll(__ballot(base + j < n && lt));
+    }
+    return base + below;
 }
 
 // Cumulative weights of one tile in the blocked arrangement: lane t owns the
@@ -585,21 +629,13 @@ __device__ __forceinline__ TileCdf tile_cdf(const double (&l)[ITEMS], double mb,
     return r;
 }
 
-// Sorted ancestors of one tile by a merge of two sorted sequences: the
-// tile's cumulative weights S_j and the ordered uniforms u_i of the slots it
-// owns, [c(Pb), c(Pb1)) with c(x) = #{i : u_i S < x} (to N for the tile
-// holding the last positive weight).  Slot i goes to the first j with
-// S_j > u_i S.  Each lane takes an equal share of the merged sequence,
-// finds its start by a merge-path search, then walks it: the work is
-// balanced however unevenly the slots fall on the particles.  Slot uniforms
-// are staged in LDS when the tile owns at most RS_UCAP slots.
-constexpr int RS_UCAP = 2048;
-
-// sS (TILE doubles) and sU (RS_UCAP doubles) are the caller's LDS.
+// Sorted ancestors of one tile (stratified and multinomial): the slots it owns
+// are [c(Pb), c(Pb1)) with c(x) = #{i : u_i S < x} (to N for the tile holding
+// the last positive weight), and slot i goes to the first j with S_j > u_i S.
+// sS (TILE doubles) is the caller's LDS.
 template <int SCHEME>
 __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t t, int32_t force,
-                                              const double *__restrict__ G, double *sS,
-                                              double *sU)
+                                              MultiSums G, double *sS)
 {
     const double *__restrict__ lw = P.lw;
     const TilePartial *__restrict__ part = P.partials;
@@ -639,6 +675,12 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
     const double sc = mb > -INFINITY ? exp_nonpos_d(mb - M) : 0.0;
     double l[ITEMS];
     tile_load_lw(lw, base, len, l);
+    const MultiPred multi{G, SCHEME == SMC_RS_MULTINOMIAL ? G.prefix[n / TILE + 1] : 1.0, stot};
+    if (SCHEME == SMC_RS_MULTINOMIAL && wave_id() < 2) {
+        const int64_t cnt = count_below_sums(multi, wave_id() == 0 ? Pb : Pb1, n);
+        if (lane_id() == 0)
+            rng_lohi[wave_id()] = cnt;
+    }
     const TileCdf cdf = tile_cdf(l, mb, sc, Pb, Pb1, red, wave_last, wave_pos);
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k)
@@ -646,7 +688,6 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
 
     const SysPred sys{U, stot, n};
     const StratPred strat{key, t, p, stot, n};
-    const MultiPred multi{G, SCHEME == SMC_RS_MULTINOMIAL ? G[n] : 1.0, stot, n};
     auto pred = [&](int64_t i) -> double {
         if (SCHEME == SMC_RS_SYSTEMATIC)
             return sys(i);
@@ -655,13 +696,7 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
         return multi(i);
     };
     const double nd = (double)n;
-    if (SCHEME == SMC_RS_MULTINOMIAL) {
-        if (wave_id() < 2) {
-            const int64_t cnt = count_below_search(multi, wave_id() == 0 ? Pb : Pb1, n);
-            if (lane_id() == 0)
-                rng_lohi[wave_id()] = cnt;
-        }
-    } else if (tid < 2) {
+    if (SCHEME != SMC_RS_MULTINOMIAL && tid < 2) {
         const double x = tid == 0 ? Pb : Pb1;
         rng_lohi[tid] = SCHEME == SMC_RS_SYSTEMATIC
                             ? count_below_walk(sys, x, n, ceil(x / stot * nd - U))
@@ -673,37 +708,29 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
     const int64_t hi = has_last ? n : max((int64_t)rng_lohi[1], lo);
     const int64_t ns = hi - lo;
     const int jstar = cdf.lastpos < 0 ? 0 : cdf.lastpos;
-    const bool staged = ns <= RS_UCAP;
-    if (staged)
-        for (int64_t q = tid; q < ns; q += TPB)
-            sU[q] = pred(lo + q);
-    __syncthreads();
-    auto u_at = [&](int64_t q) -> double { return staged ? sU[q] : pred(lo + q); };
-
-    const int64_t total = (int64_t)len + ns;
-    const int64_t ipt = ceil_div(total, TPB);
-    const int64_t d0 = min((int64_t)tid * ipt, total);
-    const int64_t d1 = min(d0 + ipt, total);
-    // merge-path split of the first d0 items: owners consumed = first j with
-    // S_j not preceding slot d0-1-j  (an owner precedes a slot iff S_j <= u)
-    int64_t jl = max((int64_t)0, d0 - ns), jh = min(d0, (int64_t)len);
-    while (jl < jh) {
-        const int64_t mid = (jl + jh) >> 1;
-        if (sS[mid] <= u_at(d0 - 1 - mid))
-            jl = mid + 1;
-        else
-            jh = mid;
-    }
-    int64_t j = jl, i = d0 - jl;
-    double uj = i < ns ? u_at(i) : 0.0;
-    for (int64_t s = d0; s < d1; ++s) {
-        if (j < len && (i >= ns || sS[j] <= uj)) {
-            ++j;
-        } else {
-            anc[lo + i] = (int32_t)(base + (j < len ? j : jstar));
-            ++i;
-            if (i < ns)
-                uj = u_at(i);
+    // a_i = min{ j : S_j > u_i S }: each slot's owner by a binary search of the
+    // tile's S, four slots of a lane at a time.  A million particles: 16 us of
+    // dependent loads and steps; as a merge of slots and owners, each lane
+    // walking its share of both after a search for its start, 18.
+    constexpr int SLOTS = 4;
+    for (int64_t q0 = tid; q0 < ns; q0 += SLOTS * TPB) {
+        double u[SLOTS];
+        int j[SLOTS];
+#pragma unroll
+        for (int k = 0; k < SLOTS; ++k) {
+            u[k] = pred(min(lo + q0 + k * TPB, hi - 1));
+            j[k] = 0;
+        }
+#pragma unroll
+        for (int h = TILE / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int k = 0; k < SLOTS; ++k)
+                j[k] += sS[j[k] + h - 1] <= u[k] ? h : 0;
+#pragma unroll
+        for (int k = 0; k < SLOTS; ++k) {
+            j[k] += sS[j[k]] <= u[k] ? 1 : 0;
+            if (q0 + k * TPB < ns)
+                anc[lo + q0 + k * TPB] = (int32_t)(base + (j[k] < len ? j[k] : jstar));
         }
     }
     if (b == 0 && tid == 0) {
@@ -724,6 +751,8 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
 // range marks the range's first slot with its index and an inclusive
 // max-scan spreads it over the range, which keeps the stores coalesced and
 // the work even however the slots fall on the particles.
+constexpr int RS_UCAP = 2048;
+
 struct TileWeights {
     double flag, M, stot;  // decision, global maximum, total
     double Pb, Pb1, mb;    // the tile's cumulative offsets and maximum
