@@ -91,7 +91,8 @@ int gmm_waves(int64_t n, int64_t nd)
 // by the waves sharing the SIMD to three quarters) plus its points, which the
 // SIMD's waves share at about 85 % of issue; compute units take workgroups in
 // whole turns.  The model puts the line where the measurements have it
-// (random-walk step, K = 4, 1000 points; setup 60, us):
+// (random-walk step, K = 4, 1000 points; setup 60, us; the figures before
+// sweep_draws took three to eight us off each):
 //   particles   8 waves x 64   best sliced            model
 //   64          119            23 (4 waves x 1)       64 lanes a particle
 //   1000        118            33 (4 waves x 4)       the same
