@@ -113,14 +113,16 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 // and split into exponent (summed as an integer) and mantissa (multiplied;
 // one logarithm per FLUSH points).  A group of points with an s not above
 // S_MIN in some lane -- a point some thirty-five standard deviations from
-// every component, or a NaN -- is left out of that lane's sums; at the end of
-// its segment to_safe() takes it again and moves the wave to the safe form,
-// which factors the largest term out of each point, for the rest of the chunk
-// (a vector far from the data is out of range at most points; the first
-// segment is one group, so such a wave changes over at once).  A wave with a
-// parameter that is not finite takes the whole chunk in the safe form, and a
-// sum that comes out NaN is taken again with zero for the terms that are not
-// finite.
+// every component, or a NaN -- is left out of that lane's sums, ends the
+// segment, and repair() takes it again with the largest term factored out.
+// After a second such group within FLUSH points, or when the first group of
+// the chunk is one (a vector far from the data is out of range at most
+// points), the wave takes the rest of its chunk in the safe form, which
+// factors the largest term out of every point.  A wave with a parameter that
+// is not finite takes the whole chunk in the safe form, and a sum that comes
+// out NaN is taken again with zero for the terms that are not finite.
+// One distant observation in every wave's part of the data, gradient at 2^16
+// vectors of 1000 points: 342 -> 360 us at K = 6, 632 -> 642 at K = 12.
 //
 // Tournament form (K <= 8 without the gradient, K = 2 with it): the largest
 // a_j = c_j log2(e) - u_j^2 is carried through K - 1 maxima, the loser of each
@@ -154,10 +156,10 @@ struct MixLik {
     // group until its reciprocal is known)
     static constexpr int GROUP = K > 8 || (GRAD && K > 6) ? 1 : (GRAD || K > 4 ? 2 : 4);
     static constexpr bool TOURN = K > 1 && (GRAD ? K == 2 : K <= TOURN_MAX_K);
-    // the gradient of K > 3 goes back to the chunk's start instead of
-    // to_safe(), whose registers would spill (four or more components all out
-    // of range are rare)
-    static constexpr bool RESTART = GRAD && K > 3;
+    // the gradient of K = 16 in the safe form throughout: the product form's
+    // registers would spill in its loop (2^14 vectors, 10^4 points: 3250 us a
+    // call against 2450)
+    static constexpr bool SAFE_ONLY = GRAD && K > 15;
     // points per segment, one logarithm each (safe form: factors <= 16).  Segments of 32 points cost 3 %.
     static constexpr int FLUSH = 128;
     // s <= K 2^SHIFT <= 2^494; s > 2^-500 has a power above 2^-504, so every
@@ -174,13 +176,12 @@ struct MixLik {
     double ll;  // after chunk(): sum of log p(y_k) over the chunk
     double m2, lsum, prod;
     int ex;
-    bool bad;  // a group of the current segment waits for to_safe()
     double gmu[GRAD ? K : 1], geta[GRAD ? K : 1], gr[GRAD ? K : 1];
 
     __device__ __forceinline__ void setup(const double (&phi)[3 * K - 1 > 0 ? 3 * K - 1 : 1],
                                           const double (&logw)[K])
     {
-        bool ok = K > 1;
+        bool ok = K > 1 && !SAFE_ONLY;
         double cmax = -INFINITY;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -207,7 +208,6 @@ struct MixLik {
         ll = m2 = lsum = 0.0;
         prod = 1.0;
         ex = 0;
-        bad = false;
         if (GRAD) {
 #pragma unroll
             for (int j = 0; j < K; ++j)
@@ -264,9 +264,8 @@ struct MixLik {
     // The terms and densities of N points (GROUP, or 1 for the remainder of a
     // chunk) in the fast form; whether every density is in range (false for
     // NaN).  No step of it can be contracted differently from one use to the
-    // next, so the answer is the same in group() and to_safe(), which takes
-    // the terms one at a time (LEAN: few registers).
-    template <int N, bool LEAN>
+    // next, so in_range() gives the same answer.
+    template <int N>
     __device__ __forceinline__ bool densities(const double (&y)[N], double (&u)[N][K],
                                               double (&e)[N][K], double (&s)[N])
     {
@@ -278,12 +277,83 @@ struct MixLik {
                 u[i][j] = fma(g[j], y[i], -gm[j]);
                 e[i][j] = exp2_neg<SHIFT>(fma(u[i][j], u[i][j], c[j]));
                 s[i] = j == 0 ? e[i][0] : s[i] + e[i][j];
-                if (LEAN)
-                    __builtin_amdgcn_sched_barrier(0);
             }
             good = good & (s[i] > S_MIN);
         }
         return good;
+    }
+
+    // Whether a point's density is in range: the sum of densities(), the terms
+    // one at a time (few registers).
+    __device__ __forceinline__ bool in_range(double y)
+    {
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const double u = fma(g[j], y, -gm[j]);
+            const double e = exp2_neg<SHIFT>(fma(u, u, c[j]));
+            s = j == 0 ? e : s + e;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return s > S_MIN;
+    }
+
+    // point<false>() with the constants of the fast form and the same bits, the
+    // terms computed again for each of their uses and one at a time, so that
+    // the loop around it keeps its registers.
+    __device__ __forceinline__ void far_point(double y)
+    {
+        int o = off;
+        asm volatile("" : "+v"(o));  // O - d_j stays here instead of K registers
+        double m = 0.0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const double u = fma(g[j], y, -gm[j]);
+            const double a = fma(-u, u, (double)o - c[j]);
+            m = j == 0 ? a : fmax(m, a);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("" : "+v"(y), "+v"(o));  // computed again
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const double u = fma(g[j], y, -gm[j]);
+            const double e = exp2_neg(m - fma(-u, u, (double)o - c[j]));
+            s = j == 0 ? e : s + e;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        m2 += m;
+        prod *= s;
+        if (GRAD) {
+            const double inv = recip(s);
+            asm volatile("" : "+v"(y), "+v"(o));
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const double u = fma(g[j], y, -gm[j]);
+                const double r = exp2_neg(m - fma(-u, u, (double)o - c[j])) * inv;
+                const double ru = r * u;
+                gmu[j] += ru;
+                geta[j] = fma(ru, u, geta[j]);
+                gr[j] += r;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+
+    // The group of N points at p that group() left out of some lanes' sums.
+    template <int N>
+    __device__ __forceinline__ void repair(const double *__restrict__ p)
+    {
+        bool good = true;
+#pragma nounroll
+        for (int i = 0; i < N; ++i)
+            good = good & in_range(p[i]);
+        if (!good) {
+            m2 -= ((N + 1) / 2) * OUT + N * (off - SHIFT);
+#pragma nounroll
+            for (int i = 0; i < N; ++i)
+                far_point(p[i]);
+        }
     }
 
     // One point in the tournament form (finite parameters; a_j = -inf, from a
@@ -329,24 +399,24 @@ struct MixLik {
         }
     }
 
+    // Whether this lane has the group in its sums (false: for repair()).
     template <int N>
-    __device__ __forceinline__ void group(const double (&y)[N])
+    __device__ __forceinline__ bool group(const double (&y)[N])
     {
         if constexpr (TOURN) {
 #pragma unroll
             for (int i = 0; i < N; ++i)
                 tournament(y[i]);
-            return;
+            return true;
         }
         double u[N][K], e[N][K], s[N];
-        const bool good = densities<N, false>(y, u, e, s);
-        bad = bad | !good;
+        const bool good = densities<N>(y, u, e, s);
 #pragma unroll
         for (int i = 0; i < N; i += 2) {
             const bool two = i + 1 < N;
             // no branch, so that the loads of the next group stay ahead: a
             // group out of range counts as a density OUT_S (taken back by
-            // to_safe()), which leaves nothing of it in the gradient's sums
+            // repair()), which leaves nothing of it in the gradient's sums
             const double p = two ? s[i] * s[two ? i + 1 : i] : s[i];
             const double q = good ? p : OUT_S;
             prod *= __builtin_amdgcn_frexp_mant(q);
@@ -369,6 +439,7 @@ struct MixLik {
                 }
             }
         }
+        return good;
     }
 
     __device__ __forceinline__ void flush()
@@ -386,36 +457,6 @@ struct MixLik {
         for (int j = 0; j < K; ++j)
             c[j] = (double)off - c[j];
         fast = false;
-    }
-
-    // From the fast to the safe form, with the groups of N points at k, k +
-    // step, .. below kend that group() left out of a lane's sums.
-    template <int N>
-    __device__ __forceinline__ void to_safe(const double *__restrict__ y, int64_t k, int64_t kend,
-                                            int step)
-    {
-        flush();
-        if (bad) {
-            double cl[K];
-#pragma unroll
-            for (int j = 0; j < K; ++j)
-                cl[j] = (double)off - c[j];
-#pragma nounroll
-            for (; k < kend; k += step) {
-                double a[N], u[N][K], e[N][K], s[N];
-#pragma unroll
-                for (int i = 0; i < N; ++i)
-                    a[i] = y[k + i];
-                if (!densities<N, true>(a, u, e, s)) {
-                    m2 -= ((N + 1) / 2) * OUT + N * (off - SHIFT);
-#pragma nounroll
-                    for (int i = 0; i < N; ++i)
-                        point<false>(y[k + i], cl);
-                }
-            }
-        }
-        flush();
-        safe_constants();
     }
 
     __device__ __forceinline__ void finish()
@@ -453,60 +494,60 @@ struct MixLik {
                 }
             }
         } else {
-            const int step = GROUP * one;
-            const double *__restrict__ yg = y + slice * GROUP;  // this lane's groups
-            int len = TOURN ? FLUSH / GROUP : 1;
-            while (fast && k + step <= k1) {
-                const int64_t kseg = k;
-                const int groups = (int)min((int64_t)len, (k1 - k) / step);
-                const double *__restrict__ p = yg + k;
-                double a[GROUP];
-#pragma unroll
-                for (int i = 0; i < GROUP; ++i)
-                    a[i] = p[i];
-                for (int r = 1; r < groups; ++r) {
-                    double b[GROUP];
-                    p += step;
+            if constexpr (!SAFE_ONLY) {
+                const int step = GROUP * one;
+                const double *__restrict__ yg = y + slice * GROUP;  // this lane's groups
+                // a group out of range that ends up to here changes the form
+                int64_t quiet = k + step;
+                while (fast && k + step <= k1) {
+                    const int groups = (int)min((int64_t)(FLUSH / GROUP), (k1 - k) / step);
+                    const double *__restrict__ p = yg + k;
+                    double a[GROUP];
 #pragma unroll
                     for (int i = 0; i < GROUP; ++i)
-                        b[i] = p[i];
-                    group<GROUP>(a);
+                        a[i] = p[i];
+                    bool far = false;  // uniform across the wave
+                    int r = 1;
+                    for (; r < groups; ++r) {
+                        double b[GROUP];
+                        p += step;
 #pragma unroll
-                    for (int i = 0; i < GROUP; ++i)
-                        a[i] = b[i];
-                }
-                group<GROUP>(a);
-                k += (int64_t)groups * step;
-                // three components are out of range more often: a short
-                // second segment
-                len = K <= 3 && len == 1 ? 16 / GROUP : FLUSH / GROUP;
-                if (!TOURN && __any(bad)) {
-                    if constexpr (RESTART) {
-                        reset();
-                        safe_constants();
-                        k = k0;
-                    } else {
-                        to_safe<GROUP>(yg, kseg, k, step);
+                        for (int i = 0; i < GROUP; ++i)
+                            b[i] = p[i];
+                        const bool good = group<GROUP>(a);
+                        far = !TOURN && __any(!good);
+                        if (far)
+                            break;
+#pragma unroll
+                        for (int i = 0; i < GROUP; ++i)
+                            a[i] = b[i];
                     }
-                } else {
+                    if (!far) {
+                        const bool good = group<GROUP>(a);
+                        far = !TOURN && __any(!good);
+                    }
+                    k += (int64_t)r * step;  // the segment, or up to the group out of range
                     flush();
-                }
-            }
-            if ((SLICED || GROUP > 1) && fast && k < k1) {
-                for (int64_t q = k + slice; q < k1; q += one) {
-                    const double a[1] = {y[q]};
-                    group<1>(a);
-                }
-                if (!TOURN && __any(bad)) {
-                    if constexpr (RESTART) {
-                        reset();
-                        safe_constants();
-                        k = k0;
-                    } else {
-                        to_safe<1>(y + slice, k, k1 - slice, one);
-                        k = k1;
+                    if (far) {
+                        repair<GROUP>(yg + k - step);
+                        flush();
+                        if (k <= quiet)
+                            safe_constants();
+                        quiet = k + (int64_t)FLUSH * one;
                     }
-                } else {
+                }
+                if ((SLICED || GROUP > 1) && fast && k < k1) {
+                    bool good = true;
+                    for (int64_t q = k + slice; q < k1; q += one) {
+                        const double a[1] = {y[q]};
+                        good = good & group<1>(a);
+                    }
+                    if (!TOURN && __any(!good)) {
+                        flush();
+#pragma nounroll
+                        for (int64_t q = k + slice; q < k1; q += one)
+                            repair<1>(y + q);
+                    }
                     k = k1;
                 }
             }
@@ -518,9 +559,17 @@ struct MixLik {
             }
             // the safe form
             if constexpr (SLICED) {
+                // one point ahead, while a register pair is left for it (the
+                // gradient of K = 16: 2450 -> 4380 us with it)
+                constexpr bool AHEAD = !SAFE_ONLY;
                 int m = 0;
-                for (k += slice; k < k1; k += one) {
-                    point<false>(y[k], c);
+                k += slice;
+                double next = AHEAD && k < k1 ? y[k] : 0.0;
+                for (; k < k1; k += one) {
+                    const double now = AHEAD ? next : y[k];
+                    if (AHEAD)
+                        next = k + one < k1 ? y[k + one] : 0.0;
+                    point<false>(now, c);
                     if (++m == FLUSH) {
                         flush();
                         m = 0;
@@ -532,7 +581,6 @@ struct MixLik {
                 const int64_t kend = min(k + FLUSH, k1);
                 if (K <= 8 && k + 2 <= kend) {  // two points at a time
                     double y0 = y[k], y1 = y[k + 1];
-#pragma unroll 2
                     for (; k + 4 <= kend; k += 2) {
                         const double n0 = y[k + 2], n1 = y[k + 3];
                         point<false>(y0, c);
@@ -550,7 +598,10 @@ struct MixLik {
             }
         }
         finish();
-        if (K > 1 && ll != ll) {  // a term that is not finite: once more, clamped
+        // a term that is not finite: once more, clamped
+        if (K > 1 && !TOURN && fast && __any(ll != ll))
+            safe_constants();
+        if (K > 1 && ll != ll) {
             reset();
 #pragma nounroll
             for (k = k0 + slice; k < k1; k += one) {

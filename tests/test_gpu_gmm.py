@@ -366,6 +366,42 @@ def test_loglik_out_of_range_points(lib, orc, K, nd, grad):
             assert_close_l1(g[:, i], gr, mass, 1e-12, "grad %d" % i)
 
 
+@pytest.mark.parametrize("K,grad", [(3, True), (4, True), (6, True), (9, False), (12, True)])
+def test_distant_points_cost_their_groups(lib, K, grad):
+    # one observation some forty standard deviations from everything in each
+    # wave's part of the data: it may cost its own group again (a few per cent
+    # here), not the part it is in (1.4 to 1.8 times the call)
+    pkg, L = lib
+    n, nd = 1 << 16, 1000
+    rng = np.random.default_rng(K)
+    mu = np.linspace(-5, 5, K)[:, None] + 0.5 * rng.normal(size=(K, n))
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+    mu_d, eta_d = dev(mu), dev(0.4 + 0.3 * rng.normal(size=(K, n)))
+    z_d = dev(0.3 * rng.normal(size=(K - 1, n)))
+    y = 3.0 * rng.normal(size=nd)
+    far = y.copy()
+    far[nd // 9::nd // 8] = 60.0
+    ys = [dev(y), dev(far)]
+    ll = torch.empty(n, dtype=torch.float64, device="cuda")
+    g = torch.empty((3 * K - 1, n), dtype=torch.float64, device="cuda")
+    ms = [[], []]
+    for r in range(12):
+        for q in range(2):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                L.smc_gmm_loglik_grad(mu_d.data_ptr(), eta_d.data_ptr(), z_d.data_ptr(), n, K,
+                                      ys[q].data_ptr(), nd, ll.data_ptr(),
+                                      g.data_ptr() if grad else 0,
+                                      torch.cuda.current_stream().cuda_stream)
+            b.record()
+            b.synchronize()
+            if r >= 2:
+                ms[q].append(a.elapsed_time(b))
+    t = [float(np.median(v)) for v in ms]
+    assert t[1] < 1.25 * t[0], t
+
+
 @pytest.mark.parametrize("n", [1, 3, 65, 700])
 @pytest.mark.parametrize("K,nd", [(1, 5), (2, 1), (3, 37), (4, 257), (6, 1000), (9, 515)])
 def test_loglik_small_populations(lib, orc, K, nd, n):
