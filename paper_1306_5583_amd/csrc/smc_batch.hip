@@ -400,7 +400,7 @@ smc_status smc_batch_create(const smc_batch_problem *probs, int32_t nprob, void 
         KGroup g = grp[pl.keys[k]];
         g.map64 = reinterpret_cast<int2 *>(b->table + pl.map64[k]);
         g.tiles64 = pl.tiles64[k];
-        g.split = gmm_split(g.sum_n, g.max_nd, GMM_SETUP_INIT);
+        g.split = gmm_split(g.sum_n, g.max_nd, g.K, GMM_SETUP_INIT);
         const auto &v = m64[pl.keys[k]];
         e = hipMemcpy(g.map64, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice);
         b->groups.push_back(g);

@@ -102,14 +102,18 @@ int gmm_waves(int64_t n, int64_t nd)
 //   20000       220            166 (4 waves x 16)     the same
 //   40000       328            290 (4 waves x 32)     the same
 // and K = 6 with the gradient, 1000 vectors, 10^4 points: 633 -> 57 us.
+// A single component takes three to five instructions a point, and a point
+// of a lane's own costs it a load besides: it counts 2.5 times (value of 10^4
+// points, us: 4096 vectors 22 sliced against 25, 8192 39 / 25, 16384 77 / 25).
 // Above 2^17 particles the turns are many and the split no longer matters.
-GmmSplit gmm_split(int64_t n, int64_t nd, double setup)
+GmmSplit gmm_split(int64_t n, int64_t nd, int K, double setup)
 {
     constexpr int CUS = 256, SIMDS = 4;
     const auto cost = [&](const GmmSplit &sp) {
         const int64_t turns = ceil_div(ceil_div(n, WAVE >> sp.lsl), CUS);
         const double w = std::max(1.0, (double)turns * sp.W / SIMDS);  // waves of a SIMD
-        const double points = (double)nd / ((double)sp.W * (1 << sp.lsl));
+        const double points = (double)nd / ((double)sp.W * (1 << sp.lsl)) *
+                              (K == 1 && sp.lsl > 0 ? 2.5 : 1.0);
         return setup * (1.0 + 0.25 * (w - 1.0)) + points * (0.15 + 0.85 * w);
     };
     GmmSplit best{gmm_waves(n, nd), 0};
@@ -150,7 +154,7 @@ GmmSplit gmm_split(int64_t n, int64_t nd, double setup)
 
 hipError_t launch_gmm_init(Ctx &c)
 {
-    const GmmSplit sp = gmm_split(c.n, c.cfg.n_data, GMM_SETUP_INIT);
+    const GmmSplit sp = gmm_split(c.n, c.cfg.n_data, c.cfg.K, GMM_SETUP_INIT);
 #define CALL_INIT(k) GmmK<k>::init(c, sp)
     hipError_t e;
     {
@@ -187,7 +191,7 @@ hipError_t launch_gmm_temper_tile(Ctx &c, int32_t step, double dalpha, bool rese
 hipError_t launch_gmm_move(Ctx &c, int32_t step, const smc_move_args &a, bool gather_check)
 {
     // every block of every sweep in one launch (gmm_step_kernel)
-    const GmmSplit sp = gmm_split(c.n, c.cfg.n_data, GMM_SETUP_STEP);
+    const GmmSplit sp = gmm_split(c.n, c.cfg.n_data, c.cfg.K, GMM_SETUP_STEP);
     const int sweeps = a.sweeps > 0 ? a.sweeps : (c.cfg.sweeps > 0 ? c.cfg.sweeps : 1);
     const double scale[3] = {a.scale[0], a.scale[1], a.scale[2]};
 #define CALL_STEP(k) GmmK<k>::step(c, sp, step, sweeps, a.alpha, scale, gather_check)

@@ -471,6 +471,18 @@ struct MixLik {
         }
     }
 
+    // One point of a single component.
+    __device__ __forceinline__ void single(double y)
+    {
+        const double u = fma(g[0], y, -gm[0]);
+        m2 += fma(-u, u, c[0]);
+        if (GRAD) {
+            gmu[0] += u;
+            geta[0] = fma(u, u, geta[0]);
+            gr[0] += 1.0;
+        }
+    }
+
     // The points [k0, k1) (uniform across the wave) of this lane's particle.
     // Unsliced, every lane takes all of them: wave-uniform loads, the next
     // group fetched one group ahead.  SLICED, the 2^lsl lanes of a particle
@@ -484,15 +496,34 @@ struct MixLik {
         const int one = SLICED ? 1 << lsl : 1;  // stride of single points
         int64_t k = k0;
         if constexpr (K == 1) {
-            for (k += slice; k < k1; k += one) {
-                const double u = fma(g[0], y[k], -gm[0]);
-                m2 += fma(-u, u, c[0]);
-                if (GRAD) {
-                    gmu[0] += u;
-                    geta[0] = fma(u, u, geta[0]);
-                    gr[0] += 1.0;
+            // three to five instructions a point: eight (sliced: four) to a wait
+            // for loads, the next ones on their way
+            constexpr int P = SLICED ? 4 : 8;
+            k += slice;
+            if (k + (int64_t)(P - 1) * one < k1) {
+                double a[P];
+#pragma unroll
+                for (int i = 0; i < P; ++i)
+                    a[i] = y[k + i * one];
+                for (; k + (int64_t)(2 * P - 1) * one < k1; k += P * one) {
+                    double b[P];
+#pragma unroll
+                    for (int i = 0; i < P; ++i)
+                        b[i] = y[k + (P + i) * one];
+#pragma unroll
+                    for (int i = 0; i < P; ++i)
+                        single(a[i]);
+#pragma unroll
+                    for (int i = 0; i < P; ++i)
+                        a[i] = b[i];
                 }
+#pragma unroll
+                for (int i = 0; i < P; ++i)
+                    single(a[i]);
+                k += P * one;
             }
+            for (; k < k1; k += one)
+                single(y[k]);
         } else {
             if constexpr (!SAFE_ONLY) {
                 const int step = GROUP * one;
@@ -1237,7 +1268,7 @@ hipError_t GmmK<K>::loglik(const double *mu, const double *eta, const double *z,
                                   const double *y, int64_t nd, double *ll, double *grad,
                                   hipStream_t s)
 {
-    const GmmSplit sp = gmm_split(n, nd, GMM_SETUP_LOGLIK);
+    const GmmSplit sp = gmm_split(n, nd, K, GMM_SETUP_LOGLIK);
     const dim3 grid((unsigned)ceil_div(n, WAVE >> sp.lsl)), blk((unsigned)(sp.W * WAVE));
 #define SMC_LOGLIK(GRAD, SLICED)                                                                  \
     hipLaunchKernelGGL((gmm_loglik_kernel<K, GRAD, SLICED>), grid, blk, 0, s, mu, eta, z, n, y,   \

@@ -236,7 +236,7 @@ struct GmmSplit {
 // `setup`: a kernel's work besides the data, in data points (three proposals
 // and decisions; the prior draws; the constants of the likelihood alone).
 constexpr double GMM_SETUP_STEP = 60.0, GMM_SETUP_INIT = 30.0, GMM_SETUP_LOGLIK = 12.0;
-GmmSplit gmm_split(int64_t n, int64_t nd, double setup);
+GmmSplit gmm_split(int64_t n, int64_t nd, int K, double setup);
 
 // --- batched launchers (a table of Prob and (problem, tile) maps) ---
 hipError_t launch_pf_init_batch(const Prob *probs, const int2 *map, int64_t tiles, hipStream_t s);

@@ -402,6 +402,33 @@ def test_distant_points_cost_their_groups(lib, K, grad):
     assert t[1] < 1.25 * t[0], t
 
 
+@pytest.mark.parametrize("n,nds", [((1 << 17) + 65, (1, 7, 8, 9, 15, 16, 17, 31, 33, 133)),
+                                   (3, (1, 3, 255, 256, 257, 1000, 4097))])
+def test_loglik_one_component(lib, n, nds):
+    # the loop over a single component at the edges of its eight points (four
+    # where lanes share a particle): l = sum_k log N(y_k | mu, 1/lambda) and its
+    # derivatives in closed form, to 1e-12 of the summands' mass
+    from paper_1306_5583_amd.autograd import loglik_and_grad
+    rng = np.random.default_rng(n)
+    mu, eta = rng.normal(0, 2, (1, n)), rng.normal(0, 0.5, (1, n))
+    cols = np.unique(np.concatenate([np.arange(min(n, 70)), np.arange(n)[-70:]]))
+    m, e = mu[0, cols, None], eta[0, cols, None]
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+    for nd in nds:
+        y = rng.normal(0.0, 3.0, nd)
+        d, lam = y[None, :] - m, np.exp(e)
+        terms = 0.5 * e - 0.5 * lam * d * d - 0.5 * math.log(2 * math.pi)
+        ll, g = loglik_and_grad(dev(mu), dev(eta), dev(np.zeros((0, n))), dev(y))
+        ll0, _ = loglik_and_grad(dev(mu), dev(eta), dev(np.zeros((0, n))), dev(y),
+                                 with_grad=False)
+        mass = np.abs(terms).sum(1) + 2.0 * nd
+        for v in (ll, ll0):
+            assert_close_l1(v.cpu().numpy()[cols], terms.sum(1), mass, 1e-12, "ll nd=%d" % nd)
+        g = g.cpu().numpy()[:, cols]
+        assert_close_l1(g[0], (lam * d).sum(1), np.abs(lam * d).sum(1) + 1, 1e-12, "mu nd=%d" % nd)
+        assert_close_l1(g[1], (0.5 - 0.5 * lam * d * d).sum(1), mass, 1e-12, "eta nd=%d" % nd)
+
+
 @pytest.mark.parametrize("n", [1, 3, 65, 700])
 @pytest.mark.parametrize("K,nd", [(1, 5), (2, 1), (3, 37), (4, 257), (6, 1000), (9, 515)])
 def test_loglik_small_populations(lib, orc, K, nd, n):
