@@ -32,6 +32,8 @@ namespace smc {
 constexpr double kHalfLog2Pi = 0.91893853320467274178032973640562;
 constexpr int GMM_MAXW = 8;       // waves per particle tile
 constexpr int GMM_RED_GROUP = 4;  // accumulators combined per LDS round
+// doubles of the wave-combine buffer: wave 0 keeps its own sums in registers
+constexpr int gmm_red_doubles(int W) { return GMM_RED_GROUP * (W - 1) * WAVE; }
 // Where a Metropolis block reads and writes the particles' state: global
 // memory both ways (each block its own launch or queue item) or, when one
 // workgroup runs a step's blocks in sequence, global -> LDS for the first,
@@ -677,7 +679,7 @@ __device__ __forceinline__ void combine_slices(MixLik<K, GRAD> &L, int lsl)
 
 // Combines the accumulators of the W waves in wave order; wave 0 ends with
 // the totals (SLICED: in the last lane of each particle).  `red` holds
-// GMM_RED_GROUP * GMM_MAXW * 64 doubles.
+// gmm_red_doubles(W).
 template <int K, bool GRAD, bool SLICED>
 __device__ __forceinline__ void combine_waves(MixLik<K, GRAD> &L, int W, int lsl, double *red)
 {
@@ -691,7 +693,7 @@ __device__ __forceinline__ void combine_waves(MixLik<K, GRAD> &L, int W, int lsl
 #pragma unroll
             for (int g = 0; g < GMM_RED_GROUP; ++g)
                 if (q0 + g < NACC)
-                    red[(g * GMM_MAXW + w) * WAVE + lane] = L.acc(q0 + g);
+                    red[(g * (W - 1) + w - 1) * WAVE + lane] = L.acc(q0 + g);
         }
         __syncthreads();
         if (w == 0) {
@@ -700,7 +702,7 @@ __device__ __forceinline__ void combine_waves(MixLik<K, GRAD> &L, int W, int lsl
                 if (q0 + g < NACC) {
                     double a = L.acc(q0 + g);
                     for (int v = 1; v < W; ++v)
-                        a += red[(g * GMM_MAXW + v) * WAVE + lane];
+                        a += red[(g * (W - 1) + v - 1) * WAVE + lane];
                     L.acc(q0 + g) = a;
                 }
         }
@@ -751,7 +753,7 @@ template <int K, bool GRAD, bool SLICED>
 __device__ __forceinline__ void gmm_init_tile(const Prob &P, int W, int64_t tile, int lsl)
 {
     constexpr int D = 3 * K - 1;
-    __shared__ double red[GMM_RED_GROUP * GMM_MAXW * WAVE];
+    __shared__ double red[gmm_red_doubles(GMM_MAXW)];
     double *__restrict__ st = (double *)P.state[0];
     double *__restrict__ lw = P.lw;
     const int64_t n = P.n, nd = P.n_data;
@@ -907,8 +909,6 @@ struct BlockStash {
     static constexpr int ROWS = MALA ? 2 + 3 * K - 1 : 2 + K;
 };
 
-// LDS of one Metropolis block: the wave-combine buffer and the stash.
-constexpr int GMM_RED_DOUBLES = GMM_RED_GROUP * GMM_MAXW * WAVE;
 template <int K, bool MALA>
 constexpr int gmm_stash_doubles() { return BlockStash<K, MALA>::ROWS * WAVE; }
 
@@ -955,7 +955,7 @@ __device__ __forceinline__ void sweep_draws(const Prob &P, int W, int lsl, int64
     }
 }
 
-// `draws` (the sweep's numbers), `red` (GMM_RED_DOUBLES), `stash` (gmm_stash_doubles<K, MALA>()) and, for
+// `draws` (the sweep's numbers), `red` (gmm_red_doubles(W)), `stash` (gmm_stash_doubles<K, MALA>()) and, for
 // the LDS hand-off modes `io`, `hand` (gmm_hand_doubles(K, MALA)) are the
 // caller's LDS.  With GMM_IO_GLOBAL the block reads `src` and writes `dst`
 // (every row when `full`, else the accepted rows in place).
@@ -1112,14 +1112,20 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
 // previous block's wave 0 left there (visible to the workgroup after the
 // barrier), and the last one writes the whole state to `dst`.
 // A random walk with K <= 4 fits two workgroups of eight waves on a compute
-// unit (128 registers).
+// unit (128 registers); MALA with K <= 2 three waves a SIMD (K = 2, 2^16
+// particles of 200 points: 95 us at the 171 registers it would take, 87 at
+// 168).  The wave-combine buffer is the launch's dynamic LDS,
+// as long as its waves need: with few data points a workgroup has one or two
+// waves, and LDS decides how many of them a compute unit holds (MALA, K = 4,
+// 2^16 particles of 50 points: 147 us at three workgroups a compute unit, the
+// buffer as long as for eight waves, 77 at five).
 template <int K, bool MALA, bool SLICED>
-__global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : 2) void gmm_step_kernel(
+__global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : (K <= 2 ? 3 : 2)) void gmm_step_kernel(
     Prob P, const double *__restrict__ src, double *__restrict__ dst, int full, int W, int lsl,
     uint32_t t,
     int sweeps, double alpha, double s0, double s1, double s2, int32_t step)
 {
-    __shared__ double red[GMM_RED_DOUBLES];
+    extern __shared__ double red[];
     __shared__ double stash[gmm_stash_doubles<K, MALA>()];
     __shared__ double hand[gmm_hand_doubles(K, MALA)];
     __shared__ double zs[gmm_draw_doubles<K>()];
@@ -1154,7 +1160,7 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 ? 4 : 2) void gmm_loglik_ker
     double *__restrict__ grad)
 {
     constexpr int D = 3 * K - 1;
-    __shared__ double red[GMM_RED_GROUP * GMM_MAXW * WAVE];
+    __shared__ double red[gmm_red_doubles(GMM_MAXW)];
     const LaneMap lm(blockIdx.x, SLICED ? lsl : 0);
     const int64_t i = lm.i;
     const bool valid = i < n;
@@ -1233,6 +1239,7 @@ hipError_t GmmK<K>::step(Ctx &c, GmmSplit sp, int32_t step, int sweeps, double a
     const double *src = (const double *)c.state_ptr();
     double *dst = gather_check ? (double *)c.other_ptr() : (double *)c.state_ptr();
     const Prob P = make_prob(c);
+    const unsigned lds = sizeof(double) * (unsigned)gmm_red_doubles(sp.W);
     hipEvent_t e0, e1;
     const bool timed = c.prof_take(&e0, &e1);
 #define SMC_STEP_ARGS                                                                             \
@@ -1241,10 +1248,10 @@ hipError_t GmmK<K>::step(Ctx &c, GmmSplit sp, int32_t step, int sweeps, double a
 #define SMC_STEP(MALA, SLICED)                                                                    \
     do {                                                                                          \
         if (timed)                                                                                \
-            hipExtLaunchKernelGGL((gmm_step_kernel<K, MALA, SLICED>), grid, blk, 0, c.stream, e0, \
-                                  e1, 0, SMC_STEP_ARGS);                                          \
+            hipExtLaunchKernelGGL((gmm_step_kernel<K, MALA, SLICED>), grid, blk, lds, c.stream,   \
+                                  e0, e1, 0, SMC_STEP_ARGS);                                      \
         else                                                                                      \
-            hipLaunchKernelGGL((gmm_step_kernel<K, MALA, SLICED>), grid, blk, 0, c.stream,        \
+            hipLaunchKernelGGL((gmm_step_kernel<K, MALA, SLICED>), grid, blk, lds, c.stream,      \
                                SMC_STEP_ARGS);                                                    \
     } while (0)
     if (c.cfg.move_kind == SMC_MOVE_MALA) {

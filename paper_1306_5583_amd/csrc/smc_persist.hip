@@ -37,7 +37,8 @@ namespace smc {
 
 constexpr uint64_t WAIT_TICKS = 200000000ull;  // 2 s of the 100 MHz constant clock
 constexpr int GMM_STASH_MAX = gmm_stash_doubles<BATCH_MAX_K, true>();
-constexpr int GMM_ITEM_DOUBLES = GMM_RED_DOUBLES + GMM_STASH_MAX + gmm_draw_doubles<BATCH_MAX_K>();
+constexpr int GMM_ITEM_RED = gmm_red_doubles(NWAVES);
+constexpr int GMM_ITEM_DOUBLES = GMM_ITEM_RED + GMM_STASH_MAX + gmm_draw_doubles<BATCH_MAX_K>();
 
 __device__ __forceinline__ uint32_t load_relaxed(const uint32_t *p)
 {
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restri
     constexpr int ARENA = GMM_ITEM_DOUBLES;
     static_assert(ARENA >= TILE, "a tile's cumulative weights fit in the arena");
     __shared__ double arena[ARENA];
-    double *gred = arena, *gstash = arena + GMM_RED_DOUBLES;
+    double *gred = arena, *gstash = arena + GMM_ITEM_RED;
     double *gdraws = gstash + GMM_STASH_MAX;
     const int tid = threadIdx.x;
     // thread 0's record of the last dependency it saw satisfied in this

@@ -454,6 +454,25 @@ def test_loglik_small_populations(lib, orc, K, nd, n):
         assert_close_l1(g[:, i], gr, mass, 1e-12, "grad %d" % i)
 
 
+def test_few_data_points_fill_the_chip(lib):
+    # with 50 data points a workgroup has one wave and a compute unit holds as
+    # many as its LDS allows: four of MALA's with K = 4 at least, so 1024 tiles
+    # run at once and take little longer than 625 (1.15 times here; where only
+    # three fit, 2.2)
+    pkg, L = lib
+    y = synth.gmm_data(50, [-3.0, 0.0, 3.0, 6.0], 2.0, [1, 1, 1, 1], 3)
+    ms = []
+    for n in (40000, 65536):
+        s = pkg.GmmSampler(n, y, 4, 12, seed=3, move="mala")
+        alphas = [(t / 12) ** 4 for t in range(13)]
+        s.run(alphas, monitor=False)
+        L.smc_profile_start(s.ctx, 12)
+        s.run(alphas, monitor=False)
+        torch.cuda.synchronize()
+        ms.append(float(np.median(L.smc_profile_read(s.ctx, 12))))
+    assert ms[1] < 1.6 * ms[0], ms
+
+
 @pytest.mark.parametrize("n,K,nd,move", [(5, 3, 300, "mala"), (61, 4, 1000, "rw"),
                                          (257, 2, 90, "mala"), (900, 5, 700, "mala"),
                                          (1300, 8, 500, "rw")])
