@@ -712,8 +712,76 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
     // tile's S, four slots of a lane at a time.  A million particles: 16 us of
     // dependent loads and steps; as a merge of slots and owners, each lane
     // walking its share of both after a search for its start, 18.
-    constexpr int SLOTS = 4;
-    for (int64_t q0 = tid; q0 < ns; q0 += SLOTS * TPB) {
+    constexpr int SLOTS = 4, MSLOTS = 8, CHUNK = MSLOTS * TPB;
+    // A tile that owns many times its share of the slots (weights concentrated
+    // on few particles) finds the owners at the ends of the chunks of slots
+    // first, a chunk a lane.  The waves fill those that lie in a single
+    // particle without drawing their uniforms, a chunk each; the others are
+    // searched between their two owners only.  A million particles, stratified,
+    // one with all the weight: 1905 us, most of it one workgroup's, -> 138 (as a
+    // merge 1420); a sixteenth of them with all of it 69 -> 60 (61).
+    constexpr int ROUND = TPB - 1;  // chunks to a round of ends
+    __shared__ int ends[TPB];
+    __shared__ unsigned long long mixed[NWAVES];  // chunks of more than one owner
+    const bool many = ns > 8192;
+    for (int64_t r0 = 0; many && r0 < ns; r0 += (int64_t)ROUND * CHUNK) {
+        const int64_t left = ns - r0, i0 = lo + r0;
+        __syncthreads();
+        {
+            const double v = pred(min(i0 + (int64_t)tid * CHUNK, hi - 1));
+            int j = 0;
+            for (int h = TILE / 2; h > 0; h >>= 1)
+                j += sS[j + h - 1] <= v ? h : 0;
+            ends[tid] = j + (sS[j] <= v ? 1 : 0);
+        }
+        __syncthreads();
+        const unsigned long long mine = __ballot(tid < ROUND && (int64_t)tid * CHUNK < left &&
+                                                 ends[tid] != ends[min(tid + 1, ROUND)]);
+        if (lane_id() == 0)
+            mixed[wave_id()] = mine;
+        for (int c = wave_id(); c < ROUND && (int64_t)c * CHUNK < left; c += NWAVES) {
+            const int jlo = ends[c];
+            const int m = (int)min((int64_t)CHUNK, left - (int64_t)c * CHUNK);
+            int32_t *__restrict__ dst = anc + i0 + (int64_t)c * CHUNK;
+            if (jlo == ends[c + 1]) {
+                const int32_t own = (int32_t)(base + (jlo < len ? jlo : jstar));
+#pragma unroll
+                for (int k = 0; k < CHUNK; k += WAVE)
+                    if (k + lane_id() < m)
+                        dst[k + lane_id()] = own;
+            }
+        }
+        __syncthreads();
+        for (int w = 0; w < NWAVES; ++w) {
+            unsigned long long todo = mixed[w];
+            while (todo) {
+                const int c = w * WAVE + __ffsll((long long)todo) - 1;
+                todo &= todo - 1;
+                const int jlo = ends[c], jhi = ends[c + 1];
+                const int m = (int)min((int64_t)CHUNK, left - (int64_t)c * CHUNK);
+                const int64_t ic = i0 + (int64_t)c * CHUNK;
+                double u[MSLOTS];
+                int j[MSLOTS];
+#pragma unroll
+                for (int k = 0; k < MSLOTS; ++k) {
+                    u[k] = pred(ic + min(tid + k * TPB, m - 1));
+                    j[k] = jlo;
+                }
+                for (int h = 1 << (31 - __clz(max(jhi - jlo, 1))); h > 0; h >>= 1)
+#pragma unroll
+                    for (int k = 0; k < MSLOTS; ++k) {
+                        const bool in = j[k] + h <= jhi;
+                        j[k] += in & (sS[in ? j[k] + h - 1 : 0] <= u[k]) ? h : 0;
+                    }
+#pragma unroll
+                for (int k = 0; k < MSLOTS; ++k)
+                    if (tid + k * TPB < m)
+                        anc[ic + tid + k * TPB] =
+                            (int32_t)(base + (j[k] < len ? j[k] : jstar));
+            }
+        }
+    }
+    for (int64_t q0 = tid; !many && q0 < ns; q0 += SLOTS * TPB) {
         double u[SLOTS];
         int j[SLOTS];
 #pragma unroll

@@ -113,6 +113,58 @@ def test_launch_forms_agree(L, orc, n, case):
         assert_ancestors(anc, anc_o, S_o, u_o)
 
 
+@pytest.mark.parametrize("scheme", ["stratified", "multinomial"])
+@pytest.mark.parametrize("n,case", [(300000, "one"), (4097, "one"), (5121, "last"),
+                                    (100003, "block"), (262144, "few"), (70001, "wide")])
+def test_concentrated_weights(L, orc, n, scheme, case):
+    # tiles that own many times their share of the slots: more than a round of
+    # chunk ends (255 chunks of 1024), one particle, a tile or a few particles
+    # with all the weight, log-weights far apart
+    rng = np.random.default_rng(n)
+    lw = rng.normal(0.0, 1.0, n)
+    if case == "wide":
+        lw *= 10.0
+    else:
+        heavy = {"one": [n // 2], "last": [n - 1], "block": np.arange(n // 3, n // 3 + 900),
+                 "few": rng.integers(0, n, 7)}[case]
+        lw -= 45.0
+        lw[heavy] += 45.0
+    anc, sm = _run(L, lw, scheme, threshold=0.0, force=1)
+    anc_o, S_o, u_o = orc.resample(scheme, 17, 5, lw)
+    assert sm[3] == 1.0
+    assert_ancestors(anc, anc_o, S_o, u_o)
+
+
+@pytest.mark.parametrize("scheme", ["stratified", "multinomial"])
+def test_concentrated_weights_cost_their_stores(L, scheme):
+    # one particle with all the weight of a million: one workgroup writes every
+    # slot, without drawing or searching for each (ten times the call with even
+    # weights at most; with them sixty to eighty times)
+    n, code = 1 << 20, L.SCHEMES[scheme]
+    nb = L.smc_resample_weights_workspace(n, code)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    anc = torch.zeros(n, dtype=torch.int32, device="cuda")
+    summary = torch.zeros(5, dtype=torch.float64, device="cuda")
+    even = torch.zeros(n, dtype=torch.float64, device="cuda")
+    one = even.clone()
+    one[n // 2] = 100.0
+    stream = torch.cuda.current_stream().cuda_stream
+    ms = [[], []]
+    for r in range(12):
+        for q, lw in enumerate((even, one)):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                L.smc_resample_weights(lw.data_ptr(), n, code, 0.0, 1, 1, 3, 0, anc.data_ptr(),
+                                       summary.data_ptr(), ws.data_ptr(), nb, stream)
+            b.record()
+            b.synchronize()
+            if r >= 2:
+                ms[q].append(a.elapsed_time(b))
+    t = [float(np.median(v)) for v in ms]
+    assert t[1] < 10.0 * t[0], t
+
+
 def test_invalid_arguments(L):
     from paper_1306_5583_amd import SmcError
     lw = torch.zeros(100, dtype=torch.float64, device="cuda")
