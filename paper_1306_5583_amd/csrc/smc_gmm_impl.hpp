@@ -590,32 +590,15 @@ struct MixLik {
                     m2 = __builtin_nan("");
                 k = k1;
             }
-            // the safe form
-            if constexpr (SLICED) {
-                // one point ahead, while a register pair is left for it (the
-                // gradient of K = 16: 2450 -> 4380 us with it)
-                constexpr bool AHEAD = !SAFE_ONLY;
-                int m = 0;
-                k += slice;
-                double next = AHEAD && k < k1 ? y[k] : 0.0;
-                for (; k < k1; k += one) {
-                    const double now = AHEAD ? next : y[k];
-                    if (AHEAD)
-                        next = k + one < k1 ? y[k + one] : 0.0;
-                    point<false>(now, c);
-                    if (++m == FLUSH) {
-                        flush();
-                        m = 0;
-                    }
-                }
-                flush();
-            }
+            // the safe form, two points at a time while registers allow and
+            // the next two fetched ahead of them
+            k += slice;
             while (k < k1) {
-                const int64_t kend = min(k + FLUSH, k1);
-                if (K <= 8 && k + 2 <= kend) {  // two points at a time
-                    double y0 = y[k], y1 = y[k + 1];
-                    for (; k + 4 <= kend; k += 2) {
-                        const double n0 = y[k + 2], n1 = y[k + 3];
+                const int64_t kend = min(k + (int64_t)FLUSH * one, k1);
+                if (K <= 8 && k + one < kend) {
+                    double y0 = y[k], y1 = y[k + one];
+                    for (; k + 3 * one < kend; k += 2 * one) {
+                        const double n0 = y[k + 2 * one], n1 = y[k + 3 * one];
                         point<false>(y0, c);
                         point<false>(y1, c);
                         y0 = n0;
@@ -623,9 +606,9 @@ struct MixLik {
                     }
                     point<false>(y0, c);
                     point<false>(y1, c);
-                    k += 2;
+                    k += 2 * one;
                 }
-                for (; k < kend; ++k)
+                for (; k < kend; k += one)
                     point<false>(y[k], c);
                 flush();
             }
