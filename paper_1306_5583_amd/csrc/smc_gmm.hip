@@ -75,62 +75,6 @@ __global__ __launch_bounds__(TPB) void gmm_temper_tile_kernel(Prob P,
 // Launch helpers
 // ---------------------------------------------------------------------------
 
-// Waves per 64-particle tile: enough waves overall to fill the GPU, at most
-// GMM_MAXW, and no more than the data can feed (>= 32 points per wave).
-int gmm_waves(int64_t n, int64_t nd)
-{
-    const int64_t tiles = ceil_div(n, WAVE);
-    int W = 1;
-    while (W < GMM_MAXW && tiles * W < 8192 && nd >= (int64_t)(2 * W) * 32)
-        W *= 2;
-    return W;
-}
-
-// The split with the least modelled time, in units of one data point's terms.
-// A lane's chain is `setup` (what a launch does besides its data, overlapped
-// by the waves sharing the SIMD to three quarters) plus its points, which the
-// SIMD's waves share at about 85 % of issue; compute units take workgroups in
-// whole turns.  The model puts the line where the measurements have it
-// (random-walk step, K = 4, 1000 points; setup 60, us; the figures before
-// sweep_draws took three to eight us off each):
-//   particles   8 waves x 64   best sliced            model
-//   64          119            23 (4 waves x 1)       64 lanes a particle
-//   1000        118            33 (4 waves x 4)       the same
-//   4000        118            55 (4 waves x 16)      the same
-//   12000       121            105 (4 waves x 16)     the same
-//   16384       125            128 (4 waves x 32)     unsliced
-//   20000       220            166 (4 waves x 16)     the same
-//   40000       328            290 (4 waves x 32)     the same
-// and K = 6 with the gradient, 1000 vectors, 10^4 points: 633 -> 57 us.
-// A single component takes three to five instructions a point, and a point
-// of a lane's own costs it a load besides: it counts 2.5 times (value of 10^4
-// points, us: 4096 vectors 22 sliced against 25, 8192 39 / 25, 16384 77 / 25).
-// Above 2^17 particles the turns are many and the split no longer matters.
-GmmSplit gmm_split(int64_t n, int64_t nd, int K, double setup)
-{
-    constexpr int CUS = 256, SIMDS = 4;
-    const auto cost = [&](const GmmSplit &sp) {
-        const int64_t turns = ceil_div(ceil_div(n, WAVE >> sp.lsl), CUS);
-        const double w = std::max(1.0, (double)turns * sp.W / SIMDS);  // waves of a SIMD
-        const double points = (double)nd / ((double)sp.W * (1 << sp.lsl)) *
-                              (K == 1 && sp.lsl > 0 ? 2.5 : 1.0);
-        return setup * (1.0 + 0.25 * (w - 1.0)) + points * (0.15 + 0.85 * w);
-    };
-    GmmSplit best{gmm_waves(n, nd), 0};
-    if (n > (1 << 17))
-        return best;
-    double t = 0.97 * cost(best);
-    for (int lsl = 0; lsl <= 6 && (int64_t)4 << lsl <= nd; ++lsl) {
-        const GmmSplit sp{4, lsl};
-        const double c = cost(sp);
-        if (c < t) {
-            t = c;
-            best = sp;
-        }
-    }
-    return best;
-}
-
 #define SMC_K_SWITCH(K_, CALL)                                                                   \
     switch (K_) {                                                                                \
     case 1: return CALL(1);                                                                      \

@@ -30,7 +30,6 @@
 namespace smc {
 
 constexpr double kHalfLog2Pi = 0.91893853320467274178032973640562;
-constexpr int GMM_MAXW = 8;       // waves per particle tile
 constexpr int GMM_RED_GROUP = 4;  // accumulators combined per LDS round
 // doubles of the wave-combine buffer: wave 0 keeps its own sums in registers
 constexpr int gmm_red_doubles(int W) { return GMM_RED_GROUP * (W - 1) * WAVE; }

@@ -12,6 +12,7 @@
 
 #include "../../include/smc.h"
 #include "smc_device.hpp"
+#include "smc_gmm_split.hpp"
 
 namespace smc {
 
@@ -226,17 +227,6 @@ hipError_t launch_gmm_move(Ctx &c, int32_t step, const smc_move_args &a, bool ga
 hipError_t launch_gmm_loglik_grad(const double *mu, const double *eta, const double *z,
                                   int64_t n, int32_t K, const double *y, int64_t n_data,
                                   double *loglik, double *grad, hipStream_t stream);
-int gmm_waves(int64_t n, int64_t nd);
-// How a mixture kernel spreads a particle's data: W waves of a workgroup and,
-// within a wave, 2^lsl neighbouring lanes (a wave then holds 64 >> lsl
-// particles).
-struct GmmSplit {
-    int W, lsl;
-};
-// `setup`: a kernel's work besides the data, in data points (three proposals
-// and decisions; the prior draws; the constants of the likelihood alone).
-constexpr double GMM_SETUP_STEP = 60.0, GMM_SETUP_INIT = 30.0, GMM_SETUP_LOGLIK = 12.0;
-GmmSplit gmm_split(int64_t n, int64_t nd, int K, double setup);
 
 // --- batched launchers (a table of Prob and (problem, tile) maps) ---
 hipError_t launch_pf_init_batch(const Prob *probs, const int2 *map, int64_t tiles, hipStream_t s);

@@ -98,3 +98,9 @@ def assert_gmm_run_matches(h, hist_o, alphas, L, what="run", path=True):
     assert_close_l1(h[:ts, L.SMC_H_PS], hist_o[:ts, 9], ps_mass + np.abs(hist_o[:ts, 9]),
                     1e-12, what + " path sampling")
     return ts
+
+
+# Shapes (vectors, data points) of the likelihood tests that mean to reach the
+# form with one lane a particle: a ragged population beyond 2^17, four waves
+# with 264 points each (the last 263): two segments of 128 and a remainder.
+UNSLICED = ((1 << 17) + 65, 1055)

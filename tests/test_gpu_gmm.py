@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 import synth
-from gpu_helpers import (assert_ancestors, assert_close_l1, assert_gmm_run_matches,
+from gpu_helpers import (UNSLICED, assert_ancestors, assert_close_l1, assert_gmm_run_matches,
                          decision_matches)
 
 pytestmark = pytest.mark.gpu
@@ -364,6 +364,64 @@ def test_loglik_out_of_range_points(lib, orc, K, nd, grad):
             lam = np.exp(eta[:, i, None])
             mass = 2.0 * nd + (lam * d * (1.0 + d)).max(0).sum()
             assert_close_l1(g[:, i], gr, mass, 1e-12, "grad %d" % i)
+
+
+def _loglik_longdouble(mu, eta, z, y):
+    # value and gradient of one vector in extended precision: where components
+    # meet at a point hundreds of standard deviations away (exponents of 65000
+    # and more), double precision leaves 1e-11 of the responsibilities open
+    mu, eta, z, y = (np.asarray(a, dtype=np.longdouble) for a in (mu, eta, z, y))
+    K = len(mu)
+    zz = np.append(z, np.longdouble(0))
+    logw = zz - zz.max() - np.log(np.exp(zz - zz.max()).sum())
+    lam, d = np.exp(eta)[:, None], y[None, :] - mu[:, None]
+    half_log_2pi = np.log(2 * np.arctan(np.longdouble(1)) * 4) / 2
+    e = (logw + eta / 2 - half_log_2pi)[:, None] - lam * d * d / 2
+    m = e.max(0)
+    w = np.exp(e - m)
+    s = w.sum(0)
+    r = w / s
+    g = np.concatenate([(r * lam * d).sum(1), (r * (1 - lam * d * d) / 2).sum(1),
+                        (r.sum(1) - len(y) * np.exp(logw))[:K - 1]])
+    return float((m + np.log(s)).sum()), g.astype(np.float64)
+
+
+@pytest.mark.parametrize("grad", [False, True])
+@pytest.mark.parametrize("K", [2, 3, 4, 6, 7, 8, 9, 12, 15, 16])
+def test_loglik_out_of_range_points_one_lane(lib, orc, K, grad):
+    # the form with a lane a particle (64 vectors to a wave), in some lanes of
+    # it only: one point out of range within a segment and at its end, two near
+    # each other, one at a wave's first point and one in its remainder; a wave
+    # of vectors far from every point, and one with weights out of range
+    pkg, L = lib
+    n, nd = UNSLICED
+    per = (nd + 3) // 4  # the waves' parts of the data
+    rng = np.random.default_rng(50 + K)
+    y = rng.normal(0.0, 2.0, nd)
+    y[[130, per + 40, per + 45, 2 * per, 3 * per + 127, nd - 1]] = 300.0
+    mu = rng.normal(0, 3, (K, n))
+    eta = rng.normal(0.4, 0.8, (K, n))
+    z = rng.normal(0, 0.5, (K - 1, n))
+    near = np.arange(n) % 5 == 0           # a wide component: every point in range
+    eta[0, near] = -12.0
+    z[0, 64:128:7] = 70.0                  # second wave: weights beyond e^+-41
+    z[K - 2, 65:128:9] = -300.0
+    mu[:, 128:192] += 1000.0               # third wave: every point out of range
+    dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), device="cuda")
+    from paper_1306_5583_amd.autograd import loglik_and_grad
+    ll, g = loglik_and_grad(dev(mu), dev(eta), dev(z), dev(y), with_grad=grad)
+    cols = np.concatenate([np.arange(0, 192, 4), np.arange(1, 192, 16), rng.integers(0, n, 24),
+                           np.arange(n - 66, n, 5)])
+    ll = ll.cpu().numpy()
+    g = g[:, torch.as_tensor(cols, device="cuda")].cpu().numpy() if grad else None
+    for q, i in enumerate(cols):
+        v, gr = _loglik_longdouble(mu[:, i], eta[:, i], z[:, i], y)
+        assert_close_l1(ll[i], v, abs(v) + 50, 1e-12, "ll %d" % i)
+        if grad:
+            # no summand of any derivative exceeds this at any point
+            d = np.abs(y[None, :] - mu[:, i, None])
+            mass = 2.0 * nd + (np.exp(eta[:, i, None]) * d * (1.0 + d)).max(0).sum()
+            assert_close_l1(g[:, q], gr, mass, 1e-12, "grad %d" % i)
 
 
 @pytest.mark.parametrize("K,grad", [(3, True), (4, True), (6, True), (9, False), (12, True)])
