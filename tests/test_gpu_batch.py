@@ -426,3 +426,78 @@ def test_model_comparison_over_k(lib):
         assert abs(logz[i] - s.log_z()) <= 1e-10 * scale, (K, logz[i], s.log_z())
         s.close()
     br.close()
+
+
+# Samplers whose 64-particle tiles a small batch splits, 2 to 64 lanes to a
+# particle (as many as leave a lane 64 points of a wave's part): n, K, n_data,
+# move, sweeps, scheme, lanes.
+SPLIT = [(300, 4, 2100, "rw", 2, "stratified", 8), (130, 2, 600, "mala", 1, "systematic", 2),
+         (65, 6, 1100, "mala", 2, "systematic", 4), (150, 3, 4500, "rw", 1, "systematic", 16),
+         (70, 1, 8200, "mala", 3, "stratified", 32), (21, 8, 16500, "rw", 1, "systematic", 64),
+         (97, 5, 3000, "mala", 1, "systematic", 8), (1030, 2, 520, "rw", 1, "systematic", 2)]
+
+
+def _split_specs(pkg, steps):
+    specs = [pkg.PfSpec(n=2500, y=synth.pf_trajectory(steps + 1, 4)[1], seed=5, problem_id=3)]
+    for i, (n, K, nd, move, sweeps, scheme, _) in enumerate(SPLIT):
+        y, _ = synth.gmm_data_spaced(nd, K, 60 + i)
+        specs.append(pkg.GmmSpec(n=n, y=y, K=K, alphas=synth.prior_tempering(steps, 4.0),
+                                 move=move, sweeps=sweeps, scheme=scheme, seed=900 + i,
+                                 problem_id=40 + i))
+    return specs
+
+
+def test_split_tiles_match_oracle(lib, orc):
+    pkg, L = lib
+    steps = 5
+    specs = _split_specs(pkg, steps)
+    br = pkg.BatchRunner(specs)
+    # the tiles are split as the cases say (the monitor waits for all of them)
+    tiles = {int(p): int(c) for k, p, _, c in br.queue() if k == 5}
+    for i, (n, _, _, _, _, _, lanes) in enumerate(SPLIT):
+        assert tiles[i + 1] == -(-n // (64 // lanes)), (i, tiles[i + 1])
+    br.set_schedule(0, 2, 2)  # two tiles to a Metropolis item
+    br.run(steps, graph=True)
+    br.check()
+    for i, (n, K, nd, move, sweeps, scheme, lanes) in enumerate(SPLIT, start=1):
+        _say("split", n, K, nd, move, sweeps, scheme, lanes)
+        sp = specs[i]
+        sched = pkg.batch.gmm_schedule(sp.alphas, None, move)
+        cfg = orc.gmm_cfg(n, sp.seed, K, problem=sp.problem_id, move=move, sweeps=sweeps,
+                          scheme=scheme)
+        _, hist_o, pop_o, _ = orc.gmm_run(cfg, sp.y, sched[:, 0], sched[:, 1:])
+        h = br.history_host(i)
+        ts = assert_gmm_run_matches(h[:steps + 1], hist_o, sched[:, 0], L, "problem %d" % i)
+        assert ts == steps + 1, (i, ts)
+        assert br.log_z_path(i) == h[steps, L.SMC_H_PS]
+        st = br.state(i).cpu().numpy()[:3 * K - 1]
+        assert_close_l1(st, pop_o, np.abs(pop_o) + 1.0, 1e-12, "problem %d population" % i)
+
+
+def test_split_tiles_schedules_give_the_same_bits(lib):
+    # every schedule, a second run, graph or eager, and a schedule that changes
+    # in the middle of a run
+    pkg, L = lib
+    steps = 4
+    want = None
+    for order, per_item, wgs in [(0, 1, 2), (0, 1, 2), (1, 2, 1), (0, 2, 1), (1, 1, 2), (0, 1, 1)]:
+        br = pkg.BatchRunner(_split_specs(pkg, steps))
+        br.set_schedule(order, per_item, wgs)
+        if wgs == 1 and per_item == 1:  # the last: another schedule from step 3 on
+            br.init()
+            br.step()
+            br.step()
+            br.set_schedule(1, 2, 2)
+            br.step()
+            br.capture()
+            br.replay()
+        else:
+            br.run(steps, graph=(order == 0))
+        br.check()
+        got = [(br.history_host(i).copy(), br.state(i).cpu().numpy().copy())
+               for i in range(len(SPLIT) + 1)]
+        br.close()
+        want = want or got
+        for i, ((h0, x0), (h1, x1)) in enumerate(zip(want, got)):
+            assert np.array_equal(h0, h1), (order, per_item, wgs, i)
+            assert np.array_equal(x0, x1), (order, per_item, wgs, i)
