@@ -406,6 +406,12 @@ struct TilePartial {
     double m, s1, s2, pad;
 };
 
+// A lane's four squares in the order every form of the partial adds them.
+__device__ __forceinline__ double sum_squares(double e0, double e1, double e2, double e3)
+{
+    return fma(e3, e3, fma(e2, e2, fma(e0, e0, e1 * e1)));
+}
+
 // Reduces the ITEMS log-weights held by each lane of a TPB workgroup to a
 // TilePartial (written by lane 0).  Out-of-range items must be -inf.
 __device__ __forceinline__ void tile_partial(const double (&lw)[ITEMS], TilePartial *out,
@@ -418,12 +424,14 @@ __device__ __forceinline__ void tile_partial(const double (&lw)[ITEMS], TilePart
     m = block_max<NWAVES>(m, red);
     double s1 = 0.0, s2 = 0.0;
     if (m > -INFINITY) {
+        static_assert(ITEMS == 4, "sum_squares takes a lane's weights");
+        double e[ITEMS];
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            const double e = exp_nonpos_d(lw[k] - m);
-            s1 += e;
-            s2 += e * e;
+            e[k] = exp_nonpos_d(lw[k] - m);
+            s1 += e[k];
         }
+        s2 = sum_squares(e[0], e[1], e[2], e[3]);
     }
     __shared__ double red2[2 * NWAVES];
     double v[2] = {s1, s2};

@@ -51,27 +51,29 @@ constexpr int64_t NR_MAX_TILES = TPB;
 // or Gaussian c - ((y-pos)/s)^2 / 2 when gaussian != 0.  The two independent
 // coordinates combine into one logarithm: log1p(a) + log1p(b) =
 // log((1 + a)(1 + b)).
+// A filter's numbers do not depend on the kernel that takes its step, bit for
+// bit, so here and in the other functions that several kernels inline nothing
+// is left to the compiler's contraction: the fused operations are written, the
+// others stay two.
 struct ObsModel {
     double c, half_nu1, inv_nu, inv_s;
     int gaussian;
-    // What the log-density takes off the constant c + c.
-    __device__ __forceinline__ double term(double px, double yx, double py, double yy) const
+    // The log-density is 2c - scale() * stat().
+    __device__ __forceinline__ double scale() const { return gaussian ? 0.5 : half_nu1; }
+    __device__ __forceinline__ double stat(double px, double yx, double py, double yy) const
     {
+#pragma clang fp contract(off)
         const double rx = (yx - px) * inv_s;
         const double ry = (yy - py) * inv_s;
         if (gaussian)
-            return 0.5 * (rx * rx + ry * ry);
-        const double q = fma(rx * rx, inv_nu, 1.0) * fma(ry * ry, inv_nu, 1.0);
-        return half_nu1 * log_pos_d(q);
+            return fma(ry, ry, rx * rx);
+        return log_pos_d(fma(rx * rx, inv_nu, 1.0) * fma(ry * ry, inv_nu, 1.0));
     }
     __device__ __forceinline__ double operator()(double px, double yx, double py, double yy) const
     {
-        const double rx = (yx - px) * inv_s;
-        const double ry = (yy - py) * inv_s;
-        if (gaussian)
-            return (c + c) - 0.5 * (rx * rx + ry * ry);
-        const double q = fma(rx * rx, inv_nu, 1.0) * fma(ry * ry, inv_nu, 1.0);
-        return (c + c) - half_nu1 * log_pos_d(q);
+#pragma clang fp contract(off)
+        const double off = scale() * stat(px, yx, py, yy);
+        return (c + c) - off;
     }
 };
 

@@ -54,7 +54,8 @@ __device__ __forceinline__ void pf_init_tile(const Prob &P, T *__restrict__ x, i
         x[n + i] = s1;
         x[2 * n + i] = s2;
         x[3 * n + i] = s3;
-        const double l = P.obs((double)s0, yx, (double)s1, yy);
+        const double l = fma(-P.obs.scale(), P.obs.stat((double)s0, yx, (double)s1, yy),
+                             P.obs.c + P.obs.c);
         lw[i] = l;
         lwv[k] = l;
     }

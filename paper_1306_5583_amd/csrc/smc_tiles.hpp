@@ -242,7 +242,7 @@ __device__ __forceinline__ void normalise_one_pass(const TilePartial *__restrict
     for (int k = 0; k < FIN_IT; ++k) {
         const double sc = q[k].m > -INFINITY ? exp_nonpos_d(q[k].m - M) : 0.0;
         wl[fin_slot(k * NT + tid)] = q[k].s1 * sc;
-        s2 += q[k].s2 * (sc * sc);
+        s2 = fma(q[k].s2, sc * sc, s2);
     }
     __syncthreads();
     double e[FIN_IT];
@@ -400,7 +400,7 @@ __device__ __forceinline__ void normalise_block(const Prob &P, int32_t step)
             [&](int64_t b) {
                 const TilePartial q = part[b];
                 const double sc = q.m > -INFINITY ? exp_nonpos_d(q.m - M) : 0.0;
-                s2 += q.s2 * (sc * sc);
+                s2 = fma(q.s2, sc * sc, s2);
                 return q.s1 * sc;
             },
             prefix, red);
@@ -1047,17 +1047,17 @@ __device__ __forceinline__ void cv_transition(Key key, uint32_t i, uint32_t t, u
     if constexpr (sizeof(T) == 8) {
         const double2 a = normal2(draw(key, i, t, TAG_PF_MOVE, 0, p));
         const double2 b = normal2(draw(key, i, t, TAG_PF_MOVE, 1, p));
-        *npx = (px + mv.dt * vx) + mv.sd_pos * a.x;
-        *npy = (py + mv.dt * vy) + mv.sd_pos * a.y;
-        *nvx = vx + mv.sd_vel * b.x;
-        *nvy = vy + mv.sd_vel * b.y;
+        *npx = fma(mv.sd_pos, a.x, fma(mv.dt, vx, px));
+        *npy = fma(mv.sd_pos, a.y, fma(mv.dt, vy, py));
+        *nvx = fma(mv.sd_vel, b.x, vx);
+        *nvy = fma(mv.sd_vel, b.y, vy);
     } else {
         const float4 z = normal4f(draw(key, i, t, TAG_PF_MOVE, 0, p));
         const float dt = (float)mv.dt, sp = (float)mv.sd_pos, sv = (float)mv.sd_vel;
-        *npx = (px + dt * vx) + sp * z.x;
-        *npy = (py + dt * vy) + sp * z.y;
-        *nvx = vx + sv * z.z;
-        *nvy = vy + sv * z.w;
+        *npx = fmaf(sp, z.x, fmaf(dt, vx, px));
+        *npy = fmaf(sp, z.y, fmaf(dt, vy, py));
+        *nvx = fmaf(sv, z.z, vx);
+        *nvy = fmaf(sv, z.w, vy);
     }
 }
 
@@ -1108,10 +1108,10 @@ __device__ __forceinline__ void pf_move_tile(const Prob &P, const T *__restrict_
             const double w = reset ? 1.0 : exp_nonpos_d(lw_in - M);
             if (w != 0.0) {
                 ms[0] += w;
-                ms[1] += w * (double)px;
-                ms[2] += w * (double)py;
-                ms[3] += w * (double)vx;
-                ms[4] += w * (double)vy;
+                ms[1] = fma(w, (double)px, ms[1]);
+                ms[2] = fma(w, (double)py, ms[2]);
+                ms[3] = fma(w, (double)vx, ms[3]);
+                ms[4] = fma(w, (double)vy, ms[4]);
             }
         }
         T npx, npy, nvx, nvy;
@@ -1189,11 +1189,7 @@ __device__ __forceinline__ double pf_move_wide(const Prob &P, const T *__restric
         xout[n + i] = npy;
         xout[2 * n + i] = nvx;
         xout[3 * n + i] = nvy;
-        // the product is rounded before the subtraction, as in the 256-lane
-        // form (whose two branches meet there)
-        double off = P.obs.term((double)npx, yx, (double)npy, yy);
-        asm("" : "+v"(off));
-        l = lw_in + ((P.obs.c + P.obs.c) - off);
+        l = lw_in + P.obs((double)npx, yx, (double)npy, yy);
         P.lw[i] = l;
     }
     if (MON) {
@@ -1220,9 +1216,8 @@ __device__ __forceinline__ double pf_move_wide(const Prob &P, const T *__restric
         double a = 0.0;
         if (r == 0) {
             a = ((L.e[tt] + L.e[TPB + tt]) + L.e[2 * TPB + tt]) + L.e[3 * TPB + tt];
-        } else if (r == 1) {  // (the first two squares fused as the compiler fuses them there)
-            const double e1 = L.e[TPB + tt], e2 = L.e[2 * TPB + tt], e3 = L.e[3 * TPB + tt];
-            a = fma(e3, e3, fma(e2, e2, fma(L.e[tt], L.e[tt], e1 * e1)));
+        } else if (r == 1) {
+            a = sum_squares(L.e[tt], L.e[TPB + tt], L.e[2 * TPB + tt], L.e[3 * TPB + tt]);
         } else {
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {

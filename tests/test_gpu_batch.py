@@ -501,3 +501,36 @@ def test_split_tiles_schedules_give_the_same_bits(lib):
         for i, ((h0, x0), (h1, x1)) in enumerate(zip(want, got)):
             assert np.array_equal(h0, h1), (order, per_item, wgs, i)
             assert np.array_equal(x0, x1), (order, per_item, wgs, i)
+
+
+@pytest.mark.parametrize("obs_nu", [math.inf, 10.0, 1.5])
+@pytest.mark.parametrize("fp32", [False, True])
+def test_batched_filters_equal_single_filters(lib, obs_nu, fp32):
+    # the batch moves four particles a lane, a single filter of up to 256 tiles
+    # one a lane (and a larger one four): Gaussian and Student-t observations,
+    # both states, bit for bit.  (smc_step against its three calls does not
+    # compare these two forms: both take the same one.)
+    pkg, L = lib
+    ns = [1, 700, 1024, 1025, 3001, 70001, 262144, 262145]
+    _, y = synth.pf_trajectory(5, 8)
+    specs = [pkg.PfSpec(n=n, y=y, seed=30 + i, problem_id=i, obs_nu=obs_nu, fp32_state=fp32)
+             for i, n in enumerate(ns)]
+    br = pkg.BatchRunner(specs)
+    br.run(len(y) - 1, graph=False)
+    br.check()
+    for i, n in enumerate(ns):
+        pf = pkg.ParticleFilter(n, y, seed=30 + i, problem_id=i, obs_nu=obs_nu, fp32_state=fp32)
+        pf.run()
+        h, hs = br.history_host(i), pf.history_host()
+        cols = [L.SMC_H_ESS, L.SMC_H_FLAG, L.SMC_H_DLOGZ, L.SMC_H_LOGZ, L.SMC_H_L]
+        assert np.array_equal(h[:, cols], hs[:, cols]), n
+        # the batch completes the monitor of a step with the next step's pass
+        # (beyond 256 tiles it adds their sums in 256 lanes, not in 512)
+        mon = slice(L.SMC_H_MON, L.SMC_H_MON + 4)
+        if n <= 262144:
+            assert np.array_equal(h[:-1, mon], hs[:len(h) - 1, mon]), n
+        assert np.array_equal(br.state(i).cpu().numpy(), pf.state().cpu().numpy()), n
+        assert np.array_equal(br.bufs[i].log_weight.cpu().numpy(), pf.log_weight.cpu().numpy()), n
+        assert np.array_equal(br.bufs[i].ancestors.cpu().numpy(), pf.ancestors.cpu().numpy()), n
+        pf.close()
+    br.close()
