@@ -458,8 +458,10 @@ smc_status smc_batch_destroy(smc_batch *b);
  * fastest.  With a non-NULL cache_path, a line "<arch> <shape buckets> |
  * order=o per_item=q wgs_per_cu=w step_ms=..." (shape buckets: per problem
  * type, mixture size and move kind, the rounded-up log2 of the particle and
- * data counts, with their multiplicities) is read instead of measuring when
- * present, and appended after measuring.  Synchronises the stream.  Leaves
+ * data counts, the sweeps and the log2 of the lanes that share a particle,
+ * with their multiplicities) is read instead of measuring when present, and
+ * appended after measuring; a line whose buckets lack the last two (written
+ * when every Metropolis tile had 64 particles) matches nothing.  Synchronises the stream.  Leaves
  * the state undefined and drops a captured graph: call smc_batch_init (and
  * capture again) afterwards. */
 smc_status smc_batch_autotune(smc_batch *b, int32_t repeats, const char *cache_path);

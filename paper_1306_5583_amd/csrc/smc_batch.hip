@@ -230,17 +230,20 @@ std::string cache_key(const smc_batch *b)
     hipDeviceProp_t prop;
     (void)hipGetDevice(&dev);
     (void)hipGetDeviceProperties(&prop, dev);
-    // shape bucket: per problem type and mixture size, the problem count and
-    // the rounded-up log2 of the particles and of the data points
+    // shape bucket: per problem type and mixture size, the problem count, the
+    // rounded-up log2 of the particles and of the data points, and what decides
+    // how long a Metropolis tile takes besides: the sweeps and the lanes that
+    // share a particle (which follow from the exact sizes of the whole batch)
     std::map<std::string, int> buckets;
-    for (const smc_batch_problem &q : b->probs) {
-        const smc_config &c = q.cfg;
+    for (size_t i = 0; i < b->probs.size(); ++i) {
+        const smc_config &c = b->probs[i].cfg;
         char k[96];
         if (c.model == SMC_MODEL_CV_TRACK)
             snprintf(k, sizeof(k), "pf%d", (int)ceil(log2((double)c.n)));
         else
-            snprintf(k, sizeof(k), "g%d%c%d.%d", c.K, c.move_kind == SMC_MOVE_MALA ? 'm' : 'r',
-                     (int)ceil(log2((double)c.n)), (int)ceil(log2((double)c.n_data)));
+            snprintf(k, sizeof(k), "g%d%c%d.%d.%d.%d", c.K,
+                     c.move_kind == SMC_MOVE_MALA ? 'm' : 'r', (int)ceil(log2((double)c.n)),
+                     (int)ceil(log2((double)c.n_data)), c.sweeps, b->qp[i].lsl);
         buckets[k] += 1;
     }
     std::string key = prop.gcnArchName;

@@ -207,6 +207,29 @@ def test_autotune_and_cache(lib, tmp_path):
     assert open(cache).read().strip().splitlines() == lines
 
 
+def test_autotune_cache_tells_tile_sizes_apart(lib, tmp_path):
+    # 1023 and 1024 data points round to the same bucket but split a particle
+    # over 2 and 4 lanes, and sweeps make a tile longer: each has its own line;
+    # a line of the form that knew neither is not taken
+    pkg, L = lib
+    cache = str(tmp_path / "tune.txt")
+
+    def tune(nd, sweeps=1):
+        y, _ = synth.gmm_data_spaced(nd, 4, 8)
+        br = pkg.BatchRunner([pkg.GmmSpec(n=100, y=y, K=4, move="rw", sweeps=sweeps,
+                                          alphas=synth.prior_tempering(4, 4.0))])
+        br.autotune(repeats=2, cache_path=cache)
+        br.close()
+        return open(cache).read().strip().splitlines()
+
+    assert [len(tune(1023)), len(tune(1024)), len(tune(1024, 2)), len(tune(1023))] == [1, 2, 3, 3]
+    key, rest = tune(1023)[0].split(" | ")
+    arch, bucket = key.split()
+    old = "%s %s | %s\n" % (arch, ".".join(bucket.split(".")[:2]) + "x1", rest)
+    open(cache, "w").write(old)
+    assert len(tune(1023)) == 2
+
+
 def test_every_schedule_gives_the_same_bits(lib):
     # queue orders, tiles per Metropolis item and workgroup counts: the
     # dependency waits make every schedule compute the same thing
