@@ -82,8 +82,11 @@ std::vector<QProblem> queue_problems(const smc_batch_problem *probs, int32_t np)
 {
     std::vector<QProblem> q;
     std::vector<int64_t> n, nd;
+    int64_t steps = INT32_MAX;  // that the observations and schedules given last for
     for (int32_t i = 0; i < np; ++i) {
         const smc_config &c = probs[i].cfg;
+        const int32_t rows = c.model == SMC_MODEL_GMM_TEMPERED ? probs[i].schedule_len : c.n_obs;
+        steps = std::min<int64_t>(steps, std::max(rows, 1) - 1);
         QProblem r;
         r.gmm = c.model == SMC_MODEL_GMM_TEMPERED;
         r.tiles = ceil_div(c.n, TILE);
@@ -95,7 +98,7 @@ std::vector<QProblem> queue_problems(const smc_batch_problem *probs, int32_t np)
         n.push_back(c.n);
         nd.push_back(c.n_data);
     }
-    split_tiles(q, n, nd);
+    split_tiles(q, n, nd, steps);
     return q;
 }
 

@@ -72,9 +72,13 @@ struct QProblem {
 // particles: 712 us a step with whole tiles, 431 split like this, 488 with
 // half the cost and 32 points for the line; four filters and two samplers
 // 1404 -> 313.
+// A step index is as far as the 32-bit tickets and counters reach, and more
+// items bring that nearer: a batch of so many steps that they could not index
+// the last with its tiles split keeps them whole.
 inline void split_tiles(std::vector<QProblem> &pr, const std::vector<int64_t> &n,
-                        const std::vector<int64_t> &n_data)
+                        const std::vector<int64_t> &n_data, int64_t steps)
 {
+    const std::vector<QProblem> whole_tiles = pr;
     constexpr double SLOTS = 512;  // two workgroups a compute unit
     constexpr int WAVES = 4, MIN_POINTS = 64;
     double total = 0.0;
@@ -92,6 +96,14 @@ inline void split_tiles(std::vector<QProblem> &pr, const std::vector<int64_t> &n
         const int64_t per = 64 >> p.lsl;
         p.mtiles = (n[i] + per - 1) / per;
     }
+    // a step's tickets: its items and no more workgroups than items
+    uint64_t items = 0, longest = 0;
+    for (const QProblem &p : pr) {
+        items += (uint64_t)(p.gmm ? 2 * p.tiles + 2 + p.mtiles : 2 * p.tiles + 1);
+        longest = std::max(longest, (uint64_t)p.mtiles);
+    }
+    if ((uint64_t)steps > 0xFFFFFFFFull / std::max(2 * items, longest))
+        pr = whole_tiles;
 }
 
 // One step's items.  `per_item` Metropolis tiles make one Metropolis item.

@@ -112,6 +112,19 @@ def test_small_batches_split_their_metropolis_tiles(L, order, per_item, shapes, 
         assert [c for k, q, _, c in items if k == IT_MONITOR and q == p] == [tiles]
 
 
+@pytest.mark.parametrize("steps,tiles", [(3, 500), (4000000, 500), (4400000, 16),
+                                         (100000000, 16)])
+def test_long_runs_keep_whole_tiles(L, steps, tiles):
+    # 1000 particles split into 500 Metropolis tiles reach 2^32 tickets after
+    # 4.26 million steps (of 504 items and as many workgroups); 16 whole tiles
+    # after 107 million, as when no tile was split
+    probs = _problems(L, [("gmm", 1000, 4, 20000)])
+    probs[0].schedule_len = steps + 1
+    items = L.smc_batch_plan_queue(probs, 0, 1)
+    assert sum(c for k, _, _, c in items if k == IT_GMM_STEP) == tiles
+    assert steps * 2 * len(items) < 1 << 32
+
+
 @pytest.mark.parametrize("order", [0, 1])
 @pytest.mark.parametrize("per_item", [1, 2])
 @pytest.mark.parametrize("which", ["small", "benchmark"])
