@@ -430,7 +430,7 @@ smc_status smc_batch_table_size(const smc_batch_problem *probs, int32_t nprob, s
  * items receives *count rows of
  * four int32 {kind (0 move, 1 reweight, 2 normalise, 3 resample, 4
  * Metropolis, 5 monitor), problem, tile, tiles in the item (monitor: the
- * problem's Metropolis items)}; with capacity 0 only
+ * problem's Metropolis tiles)}; with capacity 0 only
  * *count is written.  SMC_ERR_INVALID_ARG when capacity is non-zero and too
  * small. */
 smc_status smc_batch_plan_queue(const smc_batch_problem *probs, int32_t nprob, int32_t order,

@@ -516,7 +516,7 @@ hipError_t launch_resample_batch(const Prob *probs, const int2 *map, int64_t til
 // configured scheme, and a five-value summary.  Every stage is a few
 // microseconds of latency and a call on a small population little else, so
 // systematic resampling takes two launches up to NR_MAX_TILES tiles and one
-// for a single tile (1000 weights: five launches of 12.3 us -> one of 6).
+// for a single tile (1000 weights: five launches of 12.3 us -> one of 8).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void lw_partials_tile(const Prob &P, int64_t tile)
 {

@@ -343,26 +343,6 @@ __device__ __forceinline__ double wave_incl_scan(double v)
     return dpp::incl_scan(v, 0.0, OpAdd{});
 }
 
-// Inclusive prefix sum across the workgroup; *total receives the sum.
-template <int NW>
-__device__ __forceinline__ double block_incl_scan(double v, double *red, double *total)
-{
-    v = wave_incl_scan(v);
-    __syncthreads();
-    if (lane_id() == WAVE - 1)
-        red[wave_id()] = v;
-    __syncthreads();
-    double before = 0.0, all = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        if (w < wave_id())
-            before += red[w];
-        all += red[w];
-    }
-    *total = all;
-    return before + v;
-}
-
 // Exclusive prefix sum across the workgroup, defined as the inclusive value
 // of the previous lane so that consecutive lanes agree exactly; *total
 // receives the sum (sequential over the wave totals).

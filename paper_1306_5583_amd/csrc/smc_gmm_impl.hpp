@@ -1,7 +1,7 @@
-// smc_gmm_impl.hpp -- (templates over the number of components K) the tempered Bayesian Gaussian-mixture sampler of Section
-// 5.2 on gfx950: prior draws, the mixture log-likelihood (and its gradient),
-// the three Metropolis blocks (random walk or MALA), and the reweighting by
-// the tempering increment.
+// smc_gmm_impl.hpp -- (templates over the number of components K) the tempered
+// Bayesian Gaussian-mixture sampler of Section 5.2 on gfx950: prior draws, the
+// mixture log-likelihood (and its gradient), the three Metropolis blocks
+// (random walk or MALA), and the reweighting by the tempering increment.
 //
 // Per-particle parameters in unconstrained coordinates (rows of the state):
 //   mu_j (rows 0..K-1), eta_j = log lambda_j (K..2K-1),
@@ -161,7 +161,8 @@ struct MixLik {
     // registers would spill in its loop (2^14 vectors, 10^4 points: 3250 us a
     // call against 2450)
     static constexpr bool SAFE_ONLY = GRAD && K > 15;
-    // points per segment, one logarithm each (safe form: factors <= 16).  Segments of 32 points cost 3 %.
+    // points per segment, one logarithm each (safe form: factors <= 16);
+    // segments of 32 points cost 3 %
     static constexpr int FLUSH = 128;
     // s <= K 2^SHIFT <= 2^494; s > 2^-500 has a power above 2^-504, so every
     // s that counts, the product of two and its reciprocal are normal
@@ -832,8 +833,8 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_init_batch_kernel(
 // The proposal of particle i for one block: loads phi, draws the normals,
 // adds the drift (MALA).  Deterministic, so it is rebuilt after the data
 // loop instead of being kept in registers across it.  All array indices are
-// compile-time (the block's coordinates are selected by uniform branches),
-// so nothing is spilled to scratch.  fwd = sum over the block of
+// compile-time (the block's coordinates are selected by uniform branches), so
+// the arrays are registers, not scratch.  fwd = sum over the block of
 // (phi' - phi - drift)^2, the forward proposal term of MALA.
 template <int K, bool MALA>
 struct Proposal {
@@ -882,9 +883,9 @@ struct Proposal {
 // Values of the epilogue that do not depend on the likelihood, computed
 // before the data loop by the last wave and kept in LDS (one column per
 // lane) until wave 0 takes the decision: the proposal's log prior, the
-// proposed block coordinates and, for MALA, the forward proposal term, the prior gradient at the proposal (block
-// coordinates) and the proposed mixture weights omega'_j (the z-gradient
-// subtracts n omega'_j).
+// proposed block coordinates and, for MALA, the forward proposal term, the
+// prior gradient at the proposal (block coordinates) and the proposed mixture
+// weights omega'_j (the z-gradient subtracts n omega'_j).
 template <int K, bool MALA>
 struct BlockStash {
     static constexpr int LPP = 0, FWD = 1, PROP = 2, GP = 2 + K, ZC = 2 + 2 * K;
@@ -901,8 +902,10 @@ constexpr int gmm_stash_doubles() { return BlockStash<K, MALA>::ROWS * WAVE; }
 // mod (W << lsl) -- where every lane of a particle used to draw every pair,
 // one after the other, in each block's chain (about 250 dependent
 // instructions each).  1000 particles of 1000 points, K = 4: 58 -> 51 us a
-// step with its other launches; 16384: 124 -> 121 us.  Row q of `zs`: coordinate q; row D + b: log U of block
-// b; one column a particle (WAVE >> lsl of them).
+// step with its other launches; 16384: 124 -> 121 us.  (Below 64 data points a
+// workgroup is one wave and takes them one after the other: 40000 particles of
+// 20 points 33 -> 37 us.)  Row q of `zs`: coordinate q; row D + b: log U of
+// block b; one column a particle (WAVE >> lsl of them).
 template <int K>
 constexpr int gmm_draw_doubles() { return (3 * K - 1 + 3) * WAVE; }
 
@@ -937,9 +940,9 @@ __device__ __forceinline__ void sweep_draws(const Prob &P, int W, int lsl, int64
     }
 }
 
-// `draws` (the sweep's numbers), `red` (gmm_red_doubles(W)), `stash` (gmm_stash_doubles<K, MALA>()) and, for
-// the LDS hand-off modes `io`, `hand` (gmm_hand_doubles(K, MALA)) are the
-// caller's LDS.  With GMM_IO_GLOBAL the block reads `src` and writes `dst`
+// `draws` (the sweep's numbers), `red` (gmm_red_doubles(W)), `stash`
+// (gmm_stash_doubles<K, MALA>()) and, for the LDS hand-off modes `io`, `hand`
+// (gmm_hand_doubles(K, MALA)) are the caller's LDS.  With GMM_IO_GLOBAL the block reads `src` and writes `dst`
 // (every row when `full`, else the accepted rows in place).
 template <int K, bool MALA, bool SLICED>
 __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__restrict__ src,
@@ -1102,7 +1105,8 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
 // 2^16 particles of 50 points: 147 us at three workgroups a compute unit, the
 // buffer as long as for eight waves, 77 at five).
 template <int K, bool MALA, bool SLICED>
-__global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : (K <= 2 ? 3 : 2)) void gmm_step_kernel(
+__global__ __launch_bounds__(GMM_MAXW *WAVE,
+                             K <= 4 && !MALA ? 4 : (K <= 2 ? 3 : 2)) void gmm_step_kernel(
     Prob P, const double *__restrict__ src, double *__restrict__ dst, int full, int W, int lsl,
     uint32_t t,
     int sweeps, double alpha, double s0, double s1, double s2, int32_t step)
@@ -1132,9 +1136,9 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 && !MALA ? 4 : (K <= 2 ? 3 :
 // Log-likelihood (and gradient) for separate parameter arrays (the adjoint
 // entry point).
 // ---------------------------------------------------------------------------
-// Four waves per SIMD (128 registers) where that costs no spill: K = 4 with
-// the gradient would take 141, and 2^16 vectors of 1000 points 249 us against
-// 224).
+// Four waves per SIMD (128 registers) up to four components: K = 4 with the
+// gradient would take 141, and 2^16 vectors of 1000 points 249 us against 224
+// (where lanes share a particle it spills six registers).
 template <int K, bool GRAD, bool SLICED>
 __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 ? 4 : 2) void gmm_loglik_kernel(
     const double *__restrict__ mu, const double *__restrict__ eta, const double *__restrict__ z,

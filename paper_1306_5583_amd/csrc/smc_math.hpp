@@ -10,10 +10,10 @@
 //              Waite reduction with ln2 in two parts), e^r by its Taylor series
 //              to degree 13 (truncation below 5e-18), then scaled by 2^k.
 //  exp2_neg(a): 2^-a (or 2^(SCALE - a)) for a >= 0 (the terms of a
-//              log-sum-exp taken in base 2): a = n + f with n = floor(a) and f in [0, 1) exact, 2^-f by
-//              the degree-10 minimax polynomial with constant term 1 (Remez
-//              exchange, 2.3e-16 relative error; coefficients from
-//              gen_exp2_poly.py), scaled by 2^-n.
+//              log-sum-exp taken in base 2): a = n + f with n = floor(a) and
+//              f in [0, 1) exact, 2^-f by the degree-10 minimax polynomial with
+//              constant term 1 (Remez exchange, 2.3e-16 relative error;
+//              coefficients from gen_exp2_poly.py), scaled by 2^-n.
 //  sincospi_d: sin(pi x), cos(pi x) by exact reduction to r = x - n/2,
 //              |r| <= 1/4, and the Taylor series of sin(pi r), cos(pi r)
 //              to r^17 / r^16 (truncation below 1e-17 for |pi r| <= pi/4),
@@ -57,7 +57,10 @@ constexpr double kExp2C[11] = {
     -0x1.c6b08d6ce972dp-5,  0x1.3b2ab68e51132p-7,   -0x1.5d87ee7d3cf77p-10,
     0x1.43079ee0aac33p-13,  -0x1.ffa0707bb4816p-17, 0x1.611aa9e1420f2p-20,
     -0x1.a11af6e0d35bap-24, 0x1.5696f50dd8aa2p-28};
-constexpr double pow2(int n) { return n == 0 ? 1.0 : n > 0 ? 2.0 * pow2(n - 1) : 0.5 * pow2(n + 1); }
+constexpr double pow2(int n)
+{
+    return n == 0 ? 1.0 : n > 0 ? 2.0 * pow2(n - 1) : 0.5 * pow2(n + 1);
+}
 constexpr double kSinC[10] = {sin_c(0), sin_c(1), sin_c(2), sin_c(3), sin_c(4),
                               sin_c(5), sin_c(6), sin_c(7), sin_c(8), sin_c(9)};
 constexpr double kCosC[10] = {cos_c(0), cos_c(1), cos_c(2), cos_c(3), cos_c(4),

@@ -89,8 +89,9 @@ __device__ bool wait_at_least(const uint32_t *ctr, uint32_t target, uint32_t *ab
 }
 
 template <int K, bool MALA, bool SLICED>
-__device__ __attribute__((noinline)) void gmm_item(const Prob &P, int64_t tile0, int count, int32_t t,
-                                         double *draws, double *red, double *stash)
+__device__ __attribute__((noinline)) void gmm_item(const Prob &P, int64_t tile0, int count,
+                                                   int32_t t, double *draws, double *red,
+                                                   double *stash)
 {
     const double *sch = P.sched + 4 * (int64_t)t;
     const double a = fmin(fmax(sch[0], 0.0), 1.0);
@@ -120,13 +121,13 @@ __device__ __forceinline__ void gmm_item_dispatch(const Prob &P, int64_t tile0, 
 #define SMC_GMM_ITEM(k)                                                                           \
     case k:                                                                                       \
         if (mala && sliced)                                                                       \
-            gmm_item<k, true, true>(P, tile0, count, t, draws, red, stash);                              \
+            gmm_item<k, true, true>(P, tile0, count, t, draws, red, stash);                       \
         else if (mala)                                                                            \
-            gmm_item<k, true, false>(P, tile0, count, t, draws, red, stash);                             \
+            gmm_item<k, true, false>(P, tile0, count, t, draws, red, stash);                      \
         else if (sliced)                                                                          \
-            gmm_item<k, false, true>(P, tile0, count, t, draws, red, stash);                             \
+            gmm_item<k, false, true>(P, tile0, count, t, draws, red, stash);                      \
         else                                                                                      \
-            gmm_item<k, false, false>(P, tile0, count, t, draws, red, stash);                            \
+            gmm_item<k, false, false>(P, tile0, count, t, draws, red, stash);                     \
         break;
     switch (P.K) {
         SMC_GMM_ITEM(1)

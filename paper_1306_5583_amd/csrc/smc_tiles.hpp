@@ -1146,8 +1146,9 @@ __device__ __forceinline__ void pf_move_tile(const Prob &P, const T *__restrict_
 // other).  The sums are taken from LDS in the 256-lane form's order -- lane t
 // of four waves adds particles t, t + 256, .. and the waves' sums are added in
 // wave order -- one (row, wave) pair to a wave, so both forms give the same
-// bits.  70001 particles: 11.8 us a launch in the 256-lane form.  Returns the tile's maximum; L.sum holds s1, s2 and, with MON, the
-// monitor's five sums by wave, complete after the last barrier.
+// bits.  70001 particles: 11.8 us a launch in the 256-lane form, 8.4 here.
+// Returns the tile's maximum; L.sum holds s1, s2 and, with MON, the monitor's
+// five sums by wave, complete after the last barrier.
 constexpr int WIDE_WAVES = TILE / WAVE;
 
 template <bool MON>
