@@ -145,9 +145,12 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 // accumulated as sum r u (in gmu), sum r u^2 (in geta) and sum r (in gr)
 // and converted once in finish().
 // Largest K without the gradient that takes the tournament form: the two
-// forms cross there (value of 2^14 vectors at 2000 points, us: K = 2 33
-// against 50, K = 4 73 / 86, K = 6 120 / 123, K = 8 163 / 157, K = 12
-// 244 / 238; the tournament has no points out of range, so it keeps K = 8).
+// forms cross there (value of 2^14 vectors at 2000 points, us, tournament
+// against product: K = 2 33 / 50, K = 4 73 / 86, K = 5 105 / 112, K = 6
+// 117 / 122, K = 7 134 / 131, K = 8 150 / 150, K = 9 184 / 190, K = 10
+// 197 / 192, K = 12 241 / 228, K = 16 327 / 296; of 2^16 at 1000: K = 7
+// 275 / 273, K = 8 315 / 311, K = 9 359 / 346).  The tournament has no points
+// out of range, so it keeps K = 7 and 8.
 constexpr int TOURN_MAX_K = 8;
 
 template <int K, bool GRAD>
