@@ -310,7 +310,11 @@ const char *smc_last_error(const smc_ctx *ctx);
  *   l_i = sum_k log sum_j omega_j N(y_k | mu_j, 1/lambda_j)
  * mu, eta (= log lambda) [K][n], z [K-1][n] (logits against component K),
  * y [n_data]; loglik [n]; grad [3K-1][n] (rows dl/dmu, dl/deta, dl/dz) or
- * NULL.  All device pointers; enqueued on hip_stream. */
+ * NULL.  All device pointers; enqueued on hip_stream.  The order of a vector's
+ * sum follows from n and n_data, and whether the densities of a point are
+ * scaled by the largest of them from the vectors of the same wave as well, so
+ * its last bits may differ from one population to another; one call's results
+ * are always the same. */
 smc_status smc_gmm_loglik_grad(const double *mu, const double *eta, const double *z,
                                int64_t n, int32_t K, const double *y, int64_t n_data,
                                double *loglik, double *grad, void *hip_stream);
@@ -395,9 +399,11 @@ smc_status smc_profile_read(smc_ctx *ctx, float *ms, int32_t capacity, int32_t *
  * step progresses whatever the number of co-resident workgroups; waits are
  * bounded (a time-out raises SMC_DEVERR_TIMEOUT and the rest of the step is
  * skipped).  A step can be captured once into a HIP graph and replayed.
- * Every problem computes exactly what its own single-problem context would
- * (same per-tile functions, same Philox counters with its problem_id); the
- * batch only changes how the work is scheduled.  Supported: systematic and
+ * Every problem computes what its own single-problem context would (same
+ * per-tile functions, same Philox counters with its problem_id); the batch
+ * only changes how the work is scheduled.  A filter's numbers are the same
+ * bit for bit; a sampler's log-likelihoods are summed by another number of
+ * waves and lanes, so they agree to rounding.  Supported: systematic and
  * stratified resampling, FP64 or FP32 tracking state, mixture samplers with
  * up to BATCH_MAX_K = 8 components, any mix of move kinds and sweep counts.
  * ------------------------------------------------------------------------ */

@@ -591,7 +591,7 @@ smc_status smc_batch_set_schedule(smc_batch *b, int32_t order, int32_t per_item,
 }
 
 // Autotuner of the persistent step: times whole steps (from a fresh
-// initialisation) for every candidate schedule -- queue order, 64-particle
+// initialisation) for every candidate schedule -- queue order, Metropolis
 // tiles per Metropolis item, step workgroups per compute unit -- and keeps
 // the fastest; results are cached per device and batch shape bucket.
 smc_status smc_batch_autotune(smc_batch *b, int32_t repeats, const char *cache_path)
