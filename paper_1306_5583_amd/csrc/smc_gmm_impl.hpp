@@ -153,17 +153,18 @@ __device__ __forceinline__ double log_prior_grad(const double (&phi)[3 * K - 1 >
 // out of range, so it keeps K = 7 and 8.
 constexpr int TOURN_MAX_K = 8;
 
-template <int K, bool GRAD>
+// SAFE_ONLY: the safe form throughout, for a gradient whose product form's
+// registers would spill in its loop: K = 16 (2^14 vectors, 10^4 points: 3250 us
+// a call against 2450) and, with the step's own registers, K = 15 (MALA step of
+// 20000 particles, 400 points, 1870 us against 1020; the likelihood alone 1870
+// in the product form, 1930 in the safe one).
+template <int K, bool GRAD, bool SAFE_ONLY = GRAD && (K > 15)>
 struct MixLik {
     // points per group: independent chains for the two waves a SIMD holds,
     // as far as the registers allow (the gradient keeps every term of the
     // group until its reciprocal is known)
     static constexpr int GROUP = K > 8 || (GRAD && K > 6) ? 1 : (GRAD || K > 4 ? 2 : 4);
     static constexpr bool TOURN = K > 1 && (GRAD ? K == 2 : K <= TOURN_MAX_K);
-    // the gradient of K = 16 in the safe form throughout: the product form's
-    // registers would spill in its loop (2^14 vectors, 10^4 points: 3250 us a
-    // call against 2450)
-    static constexpr bool SAFE_ONLY = GRAD && K > 15;
     // points per segment, one logarithm each (safe form: factors <= 16);
     // segments of 32 points cost 3 %
     static constexpr int FLUSH = 128;
@@ -646,12 +647,12 @@ struct MixLik {
 
 // Sums over the 2^lsl neighbouring lanes of a particle, complete in the last
 // of them (the steps of the wave scan, as many as the slices need).
-template <int K, bool GRAD>
-__device__ __forceinline__ void combine_slices(MixLik<K, GRAD> &L, int lsl)
+template <typename Lik>
+__device__ __forceinline__ void combine_slices(Lik &L, int lsl)
 {
 #define SMC_SLICE_STEP(STEP, ...)                                                                 \
     if (lsl > STEP) {                                                                             \
-        _Pragma("unroll") for (int q = 0; q < MixLik<K, GRAD>::NACC; ++q)                         \
+        _Pragma("unroll") for (int q = 0; q < Lik::NACC; ++q)                                     \
             L.acc(q) += dpp::mov<__VA_ARGS__>(L.acc(q), 0.0);                                     \
     }
     SMC_SLICE_STEP(0, dpp::ROW_SHR1)
@@ -666,12 +667,12 @@ __device__ __forceinline__ void combine_slices(MixLik<K, GRAD> &L, int lsl)
 // Combines the accumulators of the W waves in wave order; wave 0 ends with
 // the totals (SLICED: in the last lane of each particle).  `red` holds
 // gmm_red_doubles(W).
-template <int K, bool GRAD, bool SLICED>
-__device__ __forceinline__ void combine_waves(MixLik<K, GRAD> &L, int W, int lsl, double *red)
+template <bool SLICED, typename Lik>
+__device__ __forceinline__ void combine_waves(Lik &L, int W, int lsl, double *red)
 {
-    constexpr int NACC = MixLik<K, GRAD>::NACC;
+    constexpr int NACC = Lik::NACC;
     if (SLICED)
-        combine_slices<K, GRAD>(L, lsl);
+        combine_slices(L, lsl);
     const int w = wave_id(), lane = lane_id();
     for (int q0 = 0; q0 < NACC; q0 += GMM_RED_GROUP) {
         __syncthreads();
@@ -783,7 +784,7 @@ __device__ __forceinline__ void gmm_init_tile(const Prob &P, int W, int64_t tile
     int64_t k0, k1;
     data_chunk(nd, W, &k0, &k1);
     L.template chunk<SLICED>(y, k0, k1, lsl);
-    combine_waves<K, GRAD, SLICED>(L, W, lsl, red);
+    combine_waves<SLICED>(L, W, lsl, red);
     if (wave_id() == 0 && valid && lm.lead) {
 #pragma unroll
         for (int q = 0; q < D; ++q)
@@ -985,7 +986,7 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
     const int off = block * K;
     const int dim = block == 2 ? K - 1 : K;
     const double h2 = scale * scale;
-    MixLik<K, MALA> L;
+    MixLik<K, MALA, MALA && (K > 14)> L;
     {
         Proposal<K, MALA> Q;
         Q.build(rs, sn, si, zs, zn, block, alpha, scale, pr);
@@ -1019,7 +1020,7 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
         ll0 = rs[(int64_t)D * sn + si];
         lp0 = rs[(int64_t)(D + 1) * sn + si];
     }
-    combine_waves<K, MALA, SLICED>(L, W, lsl, red);
+    combine_waves<SLICED>(L, W, lsl, red);
     if (wave_id() != 0)
         return;
     double phi[D > 0 ? D : 1];
@@ -1169,7 +1170,7 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE, K <= 4 ? 4 : 2) void gmm_loglik_ker
     int64_t k0, k1;
     data_chunk(nd, W, &k0, &k1);
     L.template chunk<SLICED>(y, k0, k1, lsl);
-    combine_waves<K, GRAD, SLICED>(L, W, lsl, red);
+    combine_waves<SLICED>(L, W, lsl, red);
     if (wave_id() == 0 && valid && lm.lead) {
         ll[i] = L.ll;
         if (GRAD) {

@@ -531,6 +531,26 @@ def test_few_data_points_fill_the_chip(lib):
     assert ms[1] < 1.6 * ms[0], ms
 
 
+@pytest.mark.parametrize("n,nd,Ks,most", [(20000, 400, (15, 14), 1.8)])
+def test_langevin_step_against_its_neighbours(lib, n, nd, Ks, most):
+    # a step of K components against its neighbour's: K = 15 where lanes share
+    # a particle, 1.4 times K = 14 in the safe form (2.5 in the product form,
+    # which spills in its loop)
+    pkg, L = lib
+    ms = []
+    for K in Ks:
+        y, _ = synth.gmm_data_spaced(nd, K, 3)
+        s = pkg.GmmSampler(n, y, K, 6, seed=3, move="mala")
+        alphas = [(t / 6) ** 4 for t in range(7)]
+        s.run(alphas, monitor=False)
+        L.smc_profile_start(s.ctx, 6)
+        s.run(alphas, monitor=False)
+        torch.cuda.synchronize()
+        ms.append(float(np.median(L.smc_profile_read(s.ctx, 6))))
+    print(Ks, ms, flush=True)
+    assert ms[0] < most * ms[1], ms
+
+
 @pytest.mark.parametrize("n,K,nd,move", [(5, 3, 300, "mala"), (61, 4, 1000, "rw"),
                                          (257, 2, 90, "mala"), (900, 5, 700, "mala"),
                                          (1300, 8, 500, "rw")])
