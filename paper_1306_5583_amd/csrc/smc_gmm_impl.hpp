@@ -848,7 +848,7 @@ struct Proposal {
     double logw0[K];
     double fwd;
 
-    // `z`: the particle's normals of the sweep, coordinate q at z[q * zn]
+    // `z`: the particle's normals, coordinate q at z[q * zn]
     __device__ __forceinline__ void build(const double *__restrict__ src, int64_t n, int64_t si,
                                           const double *z, int zn, int block, double alpha,
                                           double scale, const GmmPrior &pr)
@@ -899,6 +899,27 @@ struct BlockStash {
 template <int K, bool MALA>
 constexpr int gmm_stash_doubles() { return BlockStash<K, MALA>::ROWS * WAVE; }
 
+// One pair of normals (coordinates 2m, 2m + 1 of the block) or the logarithm of
+// the accept uniform of block b, particle ii.  `z`: the block's first
+// coordinate, `u`: its log U, in the particle's column of rows of `cols`.
+template <int K>
+__device__ __forceinline__ void draw_item(const Prob &P, uint32_t ii, uint32_t t, int sweep,
+                                          bool pair, int b, int m, double *z, double *u, int cols)
+{
+    const uint4 w =
+        draw(P.key, ii, t, pair ? TAG_MH_MU + (uint32_t)b : TAG_MH_ACCEPT,
+             (uint32_t)(pair ? 64 * sweep + m : 4 * sweep + b), P.problem_id);
+    const double l = log_pos_d(u53(w.x, w.y));
+    if (pair) {
+        const double2 v = normal2(w, l);
+        z[2 * m * cols] = v.x;
+        if (2 * m + 1 < (b == 2 ? K - 1 : K))
+            z[(2 * m + 1) * cols] = v.y;
+    } else {
+        *u = l;
+    }
+}
+
 // The random numbers of one sweep of a tile's particles: the D normals of the
 // proposals and the logarithms of the blocks' accept uniforms.  None depends
 // on the state, so they are drawn before the blocks, spread over the
@@ -906,10 +927,9 @@ constexpr int gmm_stash_doubles() { return BlockStash<K, MALA>::ROWS * WAVE; }
 // mod (W << lsl) -- where every lane of a particle used to draw every pair,
 // one after the other, in each block's chain (about 250 dependent
 // instructions each).  1000 particles of 1000 points, K = 4: 58 -> 51 us a
-// step with its other launches; 16384: 124 -> 121 us.  (Below 64 data points a
-// workgroup is one wave and takes them one after the other: 40000 particles of
-// 20 points 33 -> 37 us.)  Row q of `zs`: coordinate q; row D + b: log U of
-// block b; one column a particle (WAVE >> lsl of them).
+// step with its other launches; 16384: 124 -> 121 us.  Row q of `zs`:
+// coordinate q; row D + b: log U of block b; one column a particle (WAVE >>
+// lsl of them).
 template <int K>
 constexpr int gmm_draw_doubles() { return (3 * K - 1 + 3) * WAVE; }
 
@@ -927,33 +947,36 @@ __device__ __forceinline__ void sweep_draws(const Prob &P, int W, int lsl, int64
     for (int r = (wave_id() << lsl) + (lane & ((1 << lsl) - 1)); r < PAIRS + NB; r += W << lsl) {
         const bool pair = r < PAIRS;
         const int b = pair ? min(r / PK, 2) : r - PAIRS;
-        const int m = r - b * PK;
-        const uint4 w =
-            draw(P.key, ii, t, pair ? TAG_MH_MU + (uint32_t)b : TAG_MH_ACCEPT,
-                 (uint32_t)(pair ? 64 * sweep + m : 4 * sweep + b), P.problem_id);
-        const double l = log_pos_d(u53(w.x, w.y));
-        if (pair) {
-            const double2 z = normal2(w, l);
-            const int q = b * K + 2 * m;
-            zs[q * cols + col] = z.x;
-            if (2 * m + 1 < (b == 2 ? K - 1 : K))
-                zs[(q + 1) * cols + col] = z.y;
-        } else {
-            zs[(D + b) * cols + col] = l;
-        }
+        draw_item<K>(P, ii, t, sweep, pair, b, r - b * PK, zs + b * K * cols + col,
+                     zs + (D + b) * cols + col, cols);
     }
 }
 
-// `draws` (the sweep's numbers), `red` (gmm_red_doubles(W)), `stash`
-// (gmm_stash_doubles<K, MALA>()) and, for the LDS hand-off modes `io`, `hand`
-// (gmm_hand_doubles(K, MALA)) are the caller's LDS.  With GMM_IO_GLOBAL the block reads `src` and writes `dst`
-// (every row when `full`, else the accepted rows in place).
+// The same of one block, one lane a particle: the normals to `z`, log U to `u`.
+template <int K>
+__device__ __forceinline__ void block_draws(const Prob &P, int W, int64_t tile, uint32_t t,
+                                            int sweep, int b, double *z, double *u)
+{
+    const int lane = lane_id();
+    const int64_t i = tile * WAVE + lane;
+    const uint32_t ii = (uint32_t)(i < P.n ? i : 0);
+    const int pairs = b == 2 ? K / 2 : (K + 1) / 2;
+    for (int r = wave_id(); r < pairs + 1; r += W)
+        draw_item<K>(P, ii, t, sweep, r < pairs, b, r, z + lane, u + lane, WAVE);
+}
+
+// `draws` (coordinate q in row q + z0) and `logu` (the block's numbers), `red`
+// (gmm_red_doubles(W)), `stash` (gmm_stash_doubles<K, MALA>()) and, for the LDS hand-off modes `io`, `hand`
+// (gmm_hand_doubles(K, MALA)) are the caller's LDS.  With GMM_IO_GLOBAL the
+// block reads `src` and writes `dst` (every row when `full`, else the accepted
+// rows in place).
 template <int K, bool MALA, bool SLICED>
 __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__restrict__ src,
                                                double *__restrict__ dst, int full, int W, int lsl,
                                                int64_t tile, int block, double alpha,
                                                double scale, int32_t step, const double *draws,
-                                               double *red, double *stash, int io = GMM_IO_GLOBAL,
+                                               int z0, const double *logu, double *red,
+                                               double *stash, int io = GMM_IO_GLOBAL,
                                                double *hand = nullptr)
 {
     constexpr int D = 3 * K - 1;
@@ -982,7 +1005,8 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
     const int64_t wi = out_lds ? lane : i;
     const int64_t wn = out_lds ? WAVE : n;
     const int zn = SLICED ? WAVE >> lsl : WAVE;
-    const double *zs = draws + (SLICED ? lane >> lsl : lane);
+    const int zcol = SLICED ? lane >> lsl : lane;
+    const double *zs = draws + z0 * zn + zcol;
     const int off = block * K;
     const int dim = block == 2 ? K - 1 : K;
     const double h2 = scale * scale;
@@ -1053,7 +1077,7 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
         }
         logr += (stash[S::FWD * WAVE + lane] - bwd) / (2.0 * h2);
     }
-    const bool acc = valid && lm.lead && zs[(D + block) * zn] <= logr;
+    const bool acc = valid && lm.lead && logu[zcol] <= logr;
     if (lm.lead && (valid || out_lds)) {
         if (out_all) {
 #pragma unroll
@@ -1094,43 +1118,80 @@ __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__re
                   (double)__popcll(bal));
 }
 
+// The wave-combine buffer and the draws are the step kernel's dynamic LDS, as
+// long as its waves need: with few data points a workgroup has one to four
+// waves, and LDS decides how many of them a compute unit holds (MALA, K = 4,
+// 2^16 particles of 50 points: 147 us at three workgroups a compute unit, the
+// buffer as long as for eight waves, 77 at five).  For the same reason a single
+// wave draws for one block at a time, into the rows that the proposal then
+// takes (its lanes read only their own column), and two or four waves do it,
+// into rows of their own, for as many components as the shorter buffer gains
+// them a workgroup.  us a step, with the whole sweep's draws / by block (before
+// the draws were spread): random walk, K = 11, 2^16 particles of 50 points 280 /
+// 135 (137); MALA, K = 8, 288 / 145 (233); MALA, K = 14, 200000 of 200 points
+// 3250 / 2230 (2950).  Where it gains nothing, its barriers cost 1 to 5 %.
+constexpr bool gmm_draws_by_block(int K, int W, int lsl)
+{
+    return lsl == 0 && (W == 1 || (W < GMM_MAXW && K > 3 * W));
+}
+
+template <int K>
+unsigned gmm_step_lds(int W, int lsl)
+{
+    const int draws = !gmm_draws_by_block(K, W, lsl) ? gmm_draw_doubles<K>() >> lsl
+                      : W > 1                        ? K * WAVE
+                                                     : 0;
+    return sizeof(double) * (unsigned)(gmm_red_doubles(W) + draws);
+}
+
+// Waves a SIMD holds of gmm_step_kernel.  A random walk with K <= 4 fits two
+// workgroups of eight waves on a compute unit (128 registers); MALA with K <= 2
+// three waves (K = 2, 2^16 particles of 200 points: 95 us at the 171 registers
+// it would take, 87 at 168).
+constexpr int gmm_step_waves(int K, bool MALA) { return K <= 4 && !MALA ? 4 : (K <= 2 ? 3 : 2); }
+
 // All Metropolis blocks of a step (every sweep) in one launch: the tile's
 // workgroup runs the blocks one after the other.  The first block reads
 // `src` (through the ancestors when the step resampled and `full` is set)
 // and leaves the tile's state in LDS; each later block reads the state the
 // previous block's wave 0 left there (visible to the workgroup after the
 // barrier), and the last one writes the whole state to `dst`.
-// A random walk with K <= 4 fits two workgroups of eight waves on a compute
-// unit (128 registers); MALA with K <= 2 three waves a SIMD (K = 2, 2^16
-// particles of 200 points: 95 us at the 171 registers it would take, 87 at
-// 168).  The wave-combine buffer is the launch's dynamic LDS,
-// as long as its waves need: with few data points a workgroup has one or two
-// waves, and LDS decides how many of them a compute unit holds (MALA, K = 4,
-// 2^16 particles of 50 points: 147 us at three workgroups a compute unit, the
-// buffer as long as for eight waves, 77 at five).
 template <int K, bool MALA, bool SLICED>
 __global__ __launch_bounds__(GMM_MAXW *WAVE,
-                             K <= 4 && !MALA ? 4 : (K <= 2 ? 3 : 2)) void gmm_step_kernel(
+                             gmm_step_waves(K, MALA)) void gmm_step_kernel(
     Prob P, const double *__restrict__ src, double *__restrict__ dst, int full, int W, int lsl,
-    uint32_t t,
-    int sweeps, double alpha, double s0, double s1, double s2, int32_t step)
+    uint32_t t, int sweeps, double alpha, double s0, double s1, double s2, int32_t step)
 {
+    using S = BlockStash<K, MALA>;
     extern __shared__ double red[];
-    __shared__ double stash[gmm_stash_doubles<K, MALA>()];
+    __shared__ double stash[gmm_stash_doubles<K, MALA>() + WAVE];  // and a block's log U
     __shared__ double hand[gmm_hand_doubles(K, MALA)];
-    __shared__ double zs[gmm_draw_doubles<K>()];
-    const int nb = K == 1 ? 2 : 3;
+    constexpr int D = 3 * K - 1, nb = K == 1 ? 2 : 3;
+    const bool by_block = !SLICED && gmm_draws_by_block(K, W, 0);
+    const int cols = SLICED ? WAVE >> lsl : WAVE;
+    double *zs = red + gmm_red_doubles(W);
     for (int sw = 0; sw < sweeps; ++sw) {
-        if (sw > 0)
-            __syncthreads();
-        sweep_draws<K, SLICED>(P, W, lsl, blockIdx.x, t, sw, zs);
+        if (!by_block) {
+            if (sw > 0)
+                __syncthreads();
+            sweep_draws<K, SLICED>(P, W, lsl, blockIdx.x, t, sw, zs);
+        }
         for (int b = 0; b < nb; ++b) {
             const bool first = sw == 0 && b == 0;
             const bool last = sw == sweeps - 1 && b == nb - 1;
+            double *z = zs, *logu = zs + (D + b) * cols;
             __syncthreads();
+            if (by_block) {
+                if (W == 1)
+                    z = stash + S::PROP * WAVE;
+                logu = stash + S::ROWS * WAVE;
+                block_draws<K>(P, W, blockIdx.x, t, sw, b, z, logu);
+                __syncthreads();
+            }
             gmm_block_tile<K, MALA, SLICED>(
                 P, src, dst, first ? full : 0, W, lsl, blockIdx.x, b, alpha,
-                b == 0 ? s0 : (b == 1 ? s1 : s2), step, zs, red, stash,
+                b == 0 ? s0 : (b == 1 ? s1 : s2), step, z, by_block ? -b * K : 0, logu, red,
+                stash,
                 first ? GMM_IO_FIRST : (last ? GMM_IO_LAST : GMM_IO_LDS), hand);
         }
     }
@@ -1229,7 +1290,7 @@ hipError_t GmmK<K>::step(Ctx &c, GmmSplit sp, int32_t step, int sweeps, double a
     const double *src = (const double *)c.state_ptr();
     double *dst = gather_check ? (double *)c.other_ptr() : (double *)c.state_ptr();
     const Prob P = make_prob(c);
-    const unsigned lds = sizeof(double) * (unsigned)gmm_red_doubles(sp.W);
+    const unsigned lds = gmm_step_lds<K>(sp.W, sp.lsl);
     hipEvent_t e0, e1;
     const bool timed = c.prof_take(&e0, &e1);
 #define SMC_STEP_ARGS                                                                             \

@@ -98,6 +98,7 @@ __device__ __attribute__((noinline)) void gmm_item(const Prob &P, int64_t tile0,
     double *cur = (double *)P.state[t & 1];
     const double *prev = (const double *)P.state[(t - 1) & 1];
     const int nb = K == 1 ? 2 : 3;
+    const int cols = WAVE >> (SLICED ? P.lsl : 0);  // of a row of draws
     for (int q = 0; q < count; ++q) {
         for (int sw = 0; sw < P.sweeps; ++sw) {
             __syncthreads();  // the LDS of the previous sweep or tile
@@ -107,7 +108,8 @@ __device__ __attribute__((noinline)) void gmm_item(const Prob &P, int64_t tile0,
                 __syncthreads();  // LDS and the rows the previous block wrote
                 gmm_block_tile<K, MALA, SLICED>(P, first ? prev : cur, cur, first ? 1 : 0, NWAVES,
                                                 SLICED ? P.lsl : 0, tile0 + q, b, a, sch[1 + b],
-                                                t, draws, red, stash);
+                                                t, draws, 0, draws + (3 * K - 1 + b) * cols, red,
+                                                stash);
             }
         }
     }

@@ -104,3 +104,11 @@ def assert_gmm_run_matches(h, hist_o, alphas, L, what="run", path=True):
 # form with one lane a particle: a ragged population beyond 2^17, four waves
 # with 264 points each (the last 263): two segments of 128 and a remainder.
 UNSLICED = ((1 << 17) + 65, 1055)
+
+# (particles, data points, K, waves) of samplers whose workgroups draw for one
+# Metropolis block at a time, one lane a particle: one wave, and two and four
+# where the components are many enough; and one beside each line that draws for
+# the whole sweep.
+DRAW_SHAPES = [(70, 3, 1, 1), (70, 3, 8, 1), (40000, 20, 16, 1),
+               ((1 << 17) + 65, 64, 6, 2), ((1 << 17) + 65, 64, 7, 2), ((1 << 17) + 65, 127, 16, 2),
+               ((1 << 17) + 65, 128, 12, 4), ((1 << 17) + 65, 133, 13, 4)]

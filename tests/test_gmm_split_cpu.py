@@ -9,7 +9,7 @@ import subprocess
 
 import pytest
 
-from gpu_helpers import UNSLICED
+from gpu_helpers import DRAW_SHAPES, UNSLICED
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -48,3 +48,8 @@ def test_shapes_of_the_gpu_tests(split):
     n, nd = UNSLICED
     rows = [(n, nd, K, what) for K in range(1, 17) for what in ("loglik", "step", "init")]
     assert split(rows) == [(4, 0)] * len(rows)
+
+
+def test_shapes_of_the_draws(split):
+    rows = [(n, nd, K, "step") for n, nd, K, _ in DRAW_SHAPES]
+    assert split(rows) == [(W, 0) for _, _, _, W in DRAW_SHAPES]

@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 
 import synth
-from gpu_helpers import (UNSLICED, assert_ancestors, assert_close_l1, assert_gmm_run_matches,
+from gpu_helpers import (DRAW_SHAPES, UNSLICED, assert_ancestors, assert_close_l1, assert_gmm_run_matches,
                          decision_matches)
 
 pytestmark = pytest.mark.gpu
@@ -529,6 +529,38 @@ def test_few_data_points_fill_the_chip(lib):
         torch.cuda.synchronize()
         ms.append(float(np.median(L.smc_profile_read(s.ctx, 12))))
     assert ms[1] < 1.6 * ms[0], ms
+
+
+@pytest.mark.parametrize("move", ["rw", "mala"])
+@pytest.mark.parametrize("n,nd,K,W", DRAW_SHAPES)
+def test_lockstep_draws_by_block(lib, orc, n, nd, K, W, move):
+    # W waves of one lane a particle: the shapes at the lines where a workgroup
+    # draws for one block at a time
+    y, _ = synth.gmm_data_spaced(nd, K, 13)
+    if n < 1000:
+        _lockstep_gmm(lib, orc, n, K, nd, 3, move, sweeps=2)
+    else:
+        _lockstep_gmm_sampled(lib, orc, n, K, nd, np.array([0.0, 0.05, 0.3]), move, y, m=256)
+
+
+def test_few_data_points_restore_the_workgroups(lib):
+    # with 50 data points the tiles of 2^16 particles run at once, or nearly,
+    # for every K whose workgroup is short enough for four on a compute unit:
+    # 1024 tiles against 625 (1.1 times here; where only three fit, 2.5)
+    pkg, L = lib
+    for K, move in ((11, "rw"), (16, "rw"), (8, "mala")):
+        y, _ = synth.gmm_data_spaced(50, K, 3)
+        ms = []
+        for n in (40000, 65536):
+            s = pkg.GmmSampler(n, y, K, 12, seed=3, move=move)
+            alphas = [(t / 12) ** 4 for t in range(13)]
+            s.run(alphas, monitor=False)
+            L.smc_profile_start(s.ctx, 12)
+            s.run(alphas, monitor=False)
+            torch.cuda.synchronize()
+            ms.append(float(np.median(L.smc_profile_read(s.ctx, 12))))
+        print(K, move, ms, flush=True)
+        assert ms[1] < 1.7 * ms[0], (K, move, ms)
 
 
 @pytest.mark.parametrize("n,nd,Ks,most", [(20000, 400, (15, 14), 1.8)])
