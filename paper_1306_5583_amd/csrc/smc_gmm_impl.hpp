@@ -1145,10 +1145,15 @@ unsigned gmm_step_lds(int W, int lsl)
 }
 
 // Waves a SIMD holds of gmm_step_kernel.  A random walk with K <= 4 fits two
-// workgroups of eight waves on a compute unit (128 registers); MALA with K <= 2
+// workgroups of eight waves on a compute unit (128 registers); MALA with K <= 3
 // three waves (K = 2, 2^16 particles of 200 points: 95 us at the 171 registers
-// it would take, 87 at 168).
-constexpr int gmm_step_waves(int K, bool MALA) { return K <= 4 && !MALA ? 4 : (K <= 2 ? 3 : 2); }
+// it would take, 87 at 168; K = 3, 200000 of 200, 450 us at 192 registers, 373
+// at 168), but for K = 3 where lanes share a particle (256 of 1000 points 7 %
+// slower so).
+constexpr int gmm_step_waves(int K, bool MALA, bool SLICED)
+{
+    return K <= 4 && !MALA ? 4 : (K <= 2 || (K == 3 && !SLICED) ? 3 : 2);
+}
 
 // All Metropolis blocks of a step (every sweep) in one launch: the tile's
 // workgroup runs the blocks one after the other.  The first block reads
@@ -1158,7 +1163,7 @@ constexpr int gmm_step_waves(int K, bool MALA) { return K <= 4 && !MALA ? 4 : (K
 // barrier), and the last one writes the whole state to `dst`.
 template <int K, bool MALA, bool SLICED>
 __global__ __launch_bounds__(GMM_MAXW *WAVE,
-                             gmm_step_waves(K, MALA)) void gmm_step_kernel(
+                             gmm_step_waves(K, MALA, SLICED)) void gmm_step_kernel(
     Prob P, const double *__restrict__ src, double *__restrict__ dst, int full, int W, int lsl,
     uint32_t t, int sweeps, double alpha, double s0, double s1, double s2, int32_t step)
 {
