@@ -153,7 +153,7 @@ __device__ __forceinline__ void gmm_item_dispatch(const Prob &P, int64_t tile0, 
 // after a resample, else exp(lw_i - M)) in the tile's wave, written
 // column-major to the problem's monitor partials, then combined over the
 // tiles in a fixed order by the workgroup.
-__device__ __forceinline__ void gmm_path_monitor(const Prob &P, int32_t t)
+__device__ __attribute__((noinline)) void gmm_path_monitor(const Prob &P, int32_t t)
 {
     const int64_t n = P.n, t64 = ceil_div(n, WAVE);
     const int D = 3 * P.K - 1;
@@ -203,6 +203,33 @@ __device__ __forceinline__ void gmm_path_monitor(const Prob &P, int32_t t)
     md.scalars = P.scalars;
     md.alpha = fmin(fmax(P.sched[4 * (int64_t)t], 0.0), 1.0);
     mon_combine<TPB>(P.mon, t64, md, P.hist, P.hist_len, red, col);
+}
+
+// The kinds of item are functions of their own, like the Metropolis items: in
+// one function the kernel spilled registers (137 vector, 440 scalar; 64 and 119
+// so) that every item paid for.  Seven steps of 20 filters of 2000 to 7700
+// particles: 352 us inlined, 298 so; of one sampler of 1000 particles and 1000
+// points 506 / 475.
+template <typename T>
+__device__ __attribute__((noinline)) void move_item(const Prob &P, int64_t tile, int32_t t,
+                                                    const double *y)
+{
+    pf_move_tile<T, true, true>(P, (const T *)P.state[(t - 1) & 1], (T *)P.state[t & 1], tile,
+                                (uint32_t)t, y, true, true);
+}
+
+__device__ __attribute__((noinline)) void resample_sys_item(const Prob &P, int64_t tile, int32_t t)
+{
+    resample_sys_tile(P, tile, (uint32_t)t, 0);
+}
+
+// (`lds` comes from LDS: its accesses need not be generic ones)
+__device__ __attribute__((noinline)) void resample_strat_item(const Prob &P, int64_t tile,
+                                                              int32_t t, double *lds)
+{
+    typedef __attribute__((address_space(3))) double lds_double;
+    resample_tile<SMC_RS_STRATIFIED>(P, tile, (uint32_t)t, 0, MultiSums{},
+                                     (double *)(lds_double *)lds);
 }
 
 __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restrict__ probs,
@@ -275,13 +302,9 @@ __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restri
             const int32_t obs = t < P.n_data ? t : (int32_t)P.n_data - 1;
             const double *y = P.data + 2 * (int64_t)obs;
             if (P.elem_bytes == 4)
-                pf_move_tile<float, true, true>(P, (const float *)P.state[(t - 1) & 1],
-                                                (float *)P.state[t & 1], it.tile, (uint32_t)t, y,
-                                                true, true);
+                move_item<float>(P, it.tile, t, y);
             else
-                pf_move_tile<double, true, true>(P, (const double *)P.state[(t - 1) & 1],
-                                                 (double *)P.state[t & 1], it.tile, (uint32_t)t,
-                                                 y, true, true);
+                move_item<double>(P, it.tile, t, y);
             release = DEP_A;
             break;
         }
@@ -314,9 +337,9 @@ __global__ __launch_bounds__(TPB, 2) void batch_step_kernel(const Prob *__restri
         }
         case IT_RESAMPLE:
             if (P.scheme == SMC_RS_STRATIFIED)
-                resample_tile<SMC_RS_STRATIFIED>(P, it.tile, (uint32_t)t, 0, MultiSums{}, arena);
+                resample_strat_item(P, it.tile, t, arena);
             else
-                resample_sys_tile(P, it.tile, (uint32_t)t, 0);
+                resample_sys_item(P, it.tile, t);
             release = P.kind == SMC_MODEL_GMM_TEMPERED ? DEP_R : -1;
             break;
         case IT_GMM_STEP:
