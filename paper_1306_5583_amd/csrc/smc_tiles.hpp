@@ -718,8 +718,9 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
     // first, a chunk a lane.  The waves fill those that lie in a single
     // particle without drawing their uniforms, a chunk each; the others are
     // searched between their two owners only.  A million particles, stratified,
-    // one with all the weight: 1905 us, most of it one workgroup's, -> 138 (as a
-    // merge 1420); a sixteenth of them with all of it 69 -> 60 (61).
+    // us a call: one with all the weight 1955, most of it one workgroup's, -> 141
+    // (as a merge 1458); a sixty-fourth of them with all of it 138 -> 105 (112),
+    // a sixteenth 47 -> 42 (44).
     constexpr int ROUND = TPB - 1;  // chunks to a round of ends
     __shared__ int ends[TPB];
     __shared__ unsigned long long mixed[NWAVES];  // chunks of more than one owner
@@ -767,17 +768,18 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
                     u[k] = pred(ic + min(tid + k * TPB, m - 1));
                     j[k] = jlo;
                 }
+                // (S_jhi is above every u of the chunk, so a step that would
+                // pass it is not taken, or all end there)
                 for (int h = 1 << (31 - __clz(max(jhi - jlo, 1))); h > 0; h >>= 1)
 #pragma unroll
-                    for (int k = 0; k < MSLOTS; ++k) {
-                        const bool in = j[k] + h <= jhi;
-                        j[k] += in & (sS[in ? j[k] + h - 1 : 0] <= u[k]) ? h : 0;
-                    }
+                    for (int k = 0; k < MSLOTS; ++k)
+                        j[k] += sS[min(j[k] + h, TILE) - 1] <= u[k] ? h : 0;
 #pragma unroll
-                for (int k = 0; k < MSLOTS; ++k)
+                for (int k = 0; k < MSLOTS; ++k) {
+                    const int o = min(j[k], jhi);
                     if (tid + k * TPB < m)
-                        anc[ic + tid + k * TPB] =
-                            (int32_t)(base + (j[k] < len ? j[k] : jstar));
+                        anc[ic + tid + k * TPB] = (int32_t)(base + (o < len ? o : jstar));
+                }
             }
         }
     }

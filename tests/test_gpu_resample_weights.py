@@ -165,6 +165,21 @@ def test_concentrated_weights_cost_their_stores(L, scheme):
     assert t[1] < 10.0 * t[0], t
 
 
+@pytest.mark.parametrize("scheme", ["stratified", "multinomial"])
+@pytest.mark.parametrize("part", [9, 16, 33, 64, 250])
+def test_weights_on_a_part_of_the_population(L, orc, scheme, part):
+    # a stretch of the particles with all the weight, equal: every chunk of the
+    # slots has many owners and each slot is searched, in the last tile of the
+    # stretch up to the tile's end
+    n = 70001
+    for first in (n // 5, n - n // part):
+        lw = np.full(n, -800.0)
+        lw[first:first + n // part] = 0.0
+        anc, sm = _run(L, lw, scheme, threshold=0.0, force=1)
+        anc_o, S_o, u_o = orc.resample(scheme, 17, 5, lw)
+        assert_ancestors(anc, anc_o, S_o, u_o)
+
+
 def test_invalid_arguments(L):
     from paper_1306_5583_amd import SmcError
     lw = torch.zeros(100, dtype=torch.float64, device="cuda")
