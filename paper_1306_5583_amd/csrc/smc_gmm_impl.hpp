@@ -834,12 +834,12 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE) void gmm_init_batch_kernel(
 // history[step][ACC0 + block] (integer-valued, so the order of the additions
 // does not matter).
 // ---------------------------------------------------------------------------
-// The proposal of particle i for one block: loads phi, draws the normals,
-// adds the drift (MALA).  Deterministic, so it is rebuilt after the data
-// loop instead of being kept in registers across it.  All array indices are
-// compile-time (the block's coordinates are selected by uniform branches), so
-// the arrays are registers, not scratch.  fwd = sum over the block of
-// (phi' - phi - drift)^2, the forward proposal term of MALA.
+// The proposal of particle i for one block: loads phi, takes the normals, adds
+// the drift (MALA).  Not kept across the data loop: what the decision needs of
+// it is stashed in LDS.  All array indices are compile-time (the block's
+// coordinates are selected by uniform branches), so the arrays are registers,
+// not scratch.  fwd = sum over the block of (phi' - phi - drift)^2, the forward
+// proposal term of MALA.
 template <int K, bool MALA>
 struct Proposal {
     static constexpr int D = 3 * K - 1;
@@ -966,10 +966,10 @@ __device__ __forceinline__ void block_draws(const Prob &P, int W, int64_t tile, 
 }
 
 // `draws` (coordinate q in row q + z0) and `logu` (the block's numbers), `red`
-// (gmm_red_doubles(W)), `stash` (gmm_stash_doubles<K, MALA>()) and, for the LDS hand-off modes `io`, `hand`
-// (gmm_hand_doubles(K, MALA)) are the caller's LDS.  With GMM_IO_GLOBAL the
-// block reads `src` and writes `dst` (every row when `full`, else the accepted
-// rows in place).
+// (gmm_red_doubles(W)), `stash` (gmm_stash_doubles<K, MALA>()) and, for the LDS
+// hand-off modes `io`, `hand` (gmm_hand_doubles(K, MALA)) are the caller's LDS.
+// With GMM_IO_GLOBAL the block reads `src` and writes `dst` (every row when
+// `full`, else the accepted rows in place).
 template <int K, bool MALA, bool SLICED>
 __device__ __forceinline__ void gmm_block_tile(const Prob &P, const double *__restrict__ src,
                                                double *__restrict__ dst, int full, int W, int lsl,
@@ -1196,8 +1196,7 @@ __global__ __launch_bounds__(GMM_MAXW *WAVE,
             gmm_block_tile<K, MALA, SLICED>(
                 P, src, dst, first ? full : 0, W, lsl, blockIdx.x, b, alpha,
                 b == 0 ? s0 : (b == 1 ? s1 : s2), step, z, by_block ? -b * K : 0, logu, red,
-                stash,
-                first ? GMM_IO_FIRST : (last ? GMM_IO_LAST : GMM_IO_LDS), hand);
+                stash, first ? GMM_IO_FIRST : (last ? GMM_IO_LAST : GMM_IO_LDS), hand);
         }
     }
 }

@@ -11,8 +11,8 @@ import numpy as np
 import pytest
 
 import synth
-from gpu_helpers import (DRAW_SHAPES, UNSLICED, assert_ancestors, assert_close_l1, assert_gmm_run_matches,
-                         decision_matches)
+from gpu_helpers import (DRAW_SHAPES, UNSLICED, assert_ancestors, assert_close_l1,
+                         assert_gmm_run_matches, decision_matches)
 
 pytestmark = pytest.mark.gpu
 
