@@ -712,15 +712,17 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
     // tile's S, four slots of a lane at a time.  A million particles: 16 us of
     // dependent loads and steps; as a merge of slots and owners, each lane
     // walking its share of both after a search for its start, 18.
-    constexpr int SLOTS = 4, MSLOTS = 8, CHUNK = MSLOTS * TPB;
+    constexpr int SLOTS = 4, MSLOTS = 6, CHUNK = MSLOTS * TPB;
     // A tile that owns many times its share of the slots (weights concentrated
     // on few particles) finds the owners at the ends of the chunks of slots
     // first, a chunk a lane.  The waves fill those that lie in a single
     // particle without drawing their uniforms, a chunk each; the others are
     // searched between their two owners only.  A million particles, stratified,
-    // us a call: one with all the weight 1955, most of it one workgroup's, -> 141
-    // (as a merge 1458); a sixty-fourth of them with all of it 138 -> 105 (112),
-    // a sixteenth 47 -> 42 (44).
+    // us a call: one with all the weight 1955, most of it one workgroup's, -> 170
+    // (as a merge 1458); a sixty-fourth of them with all of it 138 -> 104 (112),
+    // a sixteenth 47 -> 42 (44).  Six slots a lane and short unrolling leave the
+    // kernel six or seven waves a SIMD: at eight slots and five waves these took
+    // 140, 105 and 42, but even weights of four million 52.9 instead of 50.8.
     constexpr int ROUND = TPB - 1;  // chunks to a round of ends
     __shared__ int ends[TPB];
     __shared__ unsigned long long mixed[NWAVES];  // chunks of more than one owner
@@ -731,6 +733,7 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
         {
             const double v = pred(min(i0 + (int64_t)tid * CHUNK, hi - 1));
             int j = 0;
+#pragma nounroll
             for (int h = TILE / 2; h > 0; h >>= 1)
                 j += sS[j + h - 1] <= v ? h : 0;
             ends[tid] = j + (sS[j] <= v ? 1 : 0);
@@ -746,7 +749,7 @@ __device__ __forceinline__ void resample_tile(const Prob &P, int64_t b, uint32_t
             int32_t *__restrict__ dst = anc + i0 + (int64_t)c * CHUNK;
             if (jlo == ends[c + 1]) {
                 const int32_t own = (int32_t)(base + (jlo < len ? jlo : jstar));
-#pragma unroll
+#pragma unroll 2
                 for (int k = 0; k < CHUNK; k += WAVE)
                     if (k + lane_id() < m)
                         dst[k + lane_id()] = own;
